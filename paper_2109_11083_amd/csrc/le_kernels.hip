@@ -1769,73 +1769,111 @@ __global__ void k_ctrl_copy(const Ctrl* __restrict__ src, Ctrl* __restrict__ dst
 }
 
 // ---------------------------------------------------------- observables
-// Per block: bin of each particle (its image in the box, with the matching
-// lab u_x), then one thread per bin sums the block's particles of that bin in
-// index order; kinetic and centre-of-mass sums by wave shuffles.  The final
-// kernel adds the block partials in block order.
+// Each wave adds its particles' bins (their images in the box, with the
+// matching lab u_x) to its own row of LDS sums, the waves of a block are added
+// in wave order and the blocks in a fixed tree, so the sums are reproducible.
+// Cell-sorted particles of one wave fall into a few bins, so a wave takes one
+// bin at a time: all lanes of that bin by one butterfly.  At most kObsBlocks
+// blocks (two a CU; a block takes several rounds of kBlock particles), and a
+// final pass over many blocks: with one thread per bin over the particles of
+// a block and one block over all partial rows, 256,000 particles and 50 bins took
+// 28 + 250 us.
 constexpr int kObsStride = 3 * LE_MAX_BINS + 4;
+constexpr int kObsBlocks = 512;
+constexpr int kObsCols = 16;  // columns per block of the final pass
+constexpr int kObsRows = kBlock / kObsCols;
 
-__global__ void __launch_bounds__(kBlock) k_obs_partial(Dev d, int nbins) {
-  __shared__ int sbin[kBlock];
-  __shared__ double sux[kBlock], smc[kBlock];
-  __shared__ double red[kBlock / 64][4];
+static inline int obs_blocks(int n) {
+  const int nb = (n + kBlock - 1) / kBlock;
+  return nb < kObsBlocks ? nb : kObsBlocks;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+__global__ void __launch_bounds__(kBlock) k_obs_partial(Dev d, int nbins, int nblk) {
+  constexpr int kW = kBlock / 64;
+  __shared__ double acc[kW][3 * LE_MAX_BINS];
+  __shared__ double red[kW][4];
   if (d.flags->status) return;
   const Ctrl* c = d.ctrl;
-  const int i = blockIdx.x * kBlock + threadIdx.x;
   const int np = d.np;
-  int b = -1;
-  double ux = 0.0, mc2 = 0.0, v[4] = {0.0, 0.0, 0.0, 0.0};
-  if (i < d.n) {
-    const double4 p = reinterpret_cast<const double4*>(d.pos[c->pos_cur])[i];
-    const double* U = d.vel[c->aux_cur];
-    const double u0 = U[i], u1 = U[np + i], u2 = U[2 * np + i];
-    double y = p.y;
-    const double ky = wrap1(y, d.Ly);
-    ux = (u0 - ky * d.jump_sv) + d.drift_sr * (y - 0.5 * d.Ly);  // lab u_x of the in-box image
-    b = (int)(y / d.Ly * (double)nbins);
-    if (b < 0) b = 0;
-    if (b > nbins - 1) b = nbins - 1;
-    const double cx = u0 - d.c_sr * (p.y - 0.5 * d.Ly);
-    mc2 = d.mass * (cx * cx + u1 * u1 + u2 * u2);
-    v[0] = mc2;
-    v[1] = ux; v[2] = u1; v[3] = u2;
-  }
-  sbin[threadIdx.x] = b;
-  sux[threadIdx.x] = ux;
-  smc[threadIdx.x] = mc2;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  for (int k = lane; k < 3 * nbins; k += 64) acc[wid][k] = 0.0;
+  const double4* P = reinterpret_cast<const double4*>(d.pos[c->pos_cur]);
+  const double* U = d.vel[c->aux_cur];
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  const int rounds = (d.n + nblk * kBlock - 1) / (nblk * kBlock);
+  for (int rd = 0; rd < rounds; ++rd) {
+    const int i = ((int)blockIdx.x * rounds + rd) * kBlock + (int)threadIdx.x;
+    int b = -1;
+    double ux = 0.0, mc2 = 0.0;
+    if (i < d.n) {
+      const double4 p = P[i];
+      const double u0 = U[i], u1 = U[np + i], u2 = U[2 * np + i];
+      double y = p.y;
+      const double ky = wrap1(y, d.Ly);
+      ux = (u0 - ky * d.jump_sv) + d.drift_sr * (y - 0.5 * d.Ly);  // lab u_x of the in-box image
+      b = (int)(y / d.Ly * (double)nbins);
+      if (b < 0) b = 0;
+      if (b > nbins - 1) b = nbins - 1;
+      const double cx = u0 - d.c_sr * (p.y - 0.5 * d.Ly);
+      mc2 = d.mass * (cx * cx + u1 * u1 + u2 * u2);
+      v[0] += mc2;
+      v[1] += ux; v[2] += u1; v[3] += u2;
+    }
+    unsigned long long rem = __ballot(b >= 0);
+    while (rem) {
+      const int bb = __builtin_amdgcn_readlane(b, __builtin_ctzll(rem));
+      const bool mine = b == bb;
+      const unsigned long long m = __ballot(mine);
+      rem &= ~m;
+      const double su = wave_sum(mine ? ux : 0.0), sk = wave_sum(mine ? mc2 : 0.0);
+      if (lane == 0) {
+        acc[wid][bb] += (double)__popcll(m);
+        acc[wid][nbins + bb] += su;
+        acc[wid][2 * nbins + bb] += sk;
+      }
+    }
+  }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    double t = v[k];
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    const double t = wave_sum(v[k]);
     if (lane == 0) red[wid][k] = t;
   }
   __syncthreads();
   double* out = d.obs_part + (size_t)blockIdx.x * kObsStride;
-  for (int bb = threadIdx.x; bb < nbins; bb += kBlock) {
-    double cnt = 0.0, sum = 0.0, sk = 0.0;
-    for (int q = 0; q < kBlock; ++q)
-      if (sbin[q] == bb) { cnt += 1.0; sum += sux[q]; sk += smc[q]; }
-    out[bb] = cnt;
-    out[nbins + bb] = sum;
-    out[2 * nbins + bb] = sk;
+  for (int k = threadIdx.x; k < 3 * nbins; k += kBlock) {
+    double t = 0.0;
+    for (int w = 0; w < kW; ++w) t += acc[w][k];
+    out[k] = t;
   }
   if (threadIdx.x < 4) {
     double t = 0.0;
-    for (int w = 0; w < kBlock / 64; ++w) t += red[w][threadIdx.x];
+    for (int w = 0; w < kW; ++w) t += red[w][threadIdx.x];
     out[3 * nbins + threadIdx.x] = t;
   }
 }
 
+// kObsCols columns per block, kObsRows threads per column: each adds every
+// kObsRows-th block's partial, then the threads of a column are added in order.
 __global__ void __launch_bounds__(kBlock) k_obs_final(Dev d, int nbins, int nblk, double* out) {
+  __shared__ double part[kObsRows][kObsCols];
   if (d.flags->status) return;
-  for (int k = threadIdx.x; k < 3 * nbins + 4; k += kBlock) {
-    double t = 0.0;
-    for (int b = 0; b < nblk; ++b) t += d.obs_part[(size_t)b * kObsStride + k];
-    if (k == 3 * nbins) t = t / (3.0 * (double)d.n - 3.0);
-    else if (k > 3 * nbins) t = t / (double)d.n;
-    out[k] = t;
-  }
+  const int col = threadIdx.x % kObsCols, row = threadIdx.x / kObsCols;
+  const int k = (int)blockIdx.x * kObsCols + col;
+  double t = 0.0;
+  if (k < 3 * nbins + 4)
+    for (int b = row; b < nblk; b += kObsRows) t += d.obs_part[(size_t)b * kObsStride + k];
+  part[row][col] = t;
+  __syncthreads();
+  if (row != 0 || k >= 3 * nbins + 4) return;
+  for (int r = 1; r < kObsRows; ++r) t += part[r][col];
+  if (k == 3 * nbins) t = t / (3.0 * (double)d.n - 3.0);
+  else if (k > 3 * nbins) t = t / (double)d.n;
+  out[k] = t;
 }
 
 // Unwrapped y, z of every particle (slot order in, tag order out).
@@ -2099,9 +2137,10 @@ hipError_t launch_ctrl_copy(const Ctrl* src, Ctrl* dst, const unsigned long long
   return hipGetLastError();
 }
 hipError_t launch_observables(const Dev& d, hipStream_t s, int nbins, double* out) {
-  const int nblk = blocks_for(d.n);
-  hipLaunchKernelGGL(k_obs_partial, dim3(nblk), dim3(kBlock), 0, s, d, nbins);
-  hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(kBlock), 0, s, d, nbins, nblk, out);
+  const int nblk = obs_blocks(d.n), ncol = 3 * nbins + 4;
+  hipLaunchKernelGGL(k_obs_partial, dim3(nblk), dim3(kBlock), 0, s, d, nbins, nblk);
+  hipLaunchKernelGGL(k_obs_final, dim3((ncol + kObsCols - 1) / kObsCols), dim3(kBlock), 0, s, d, nbins, nblk,
+                     out);
   return hipGetLastError();
 }
 hipError_t launch_unwrapped(const Dev& d, hipStream_t s, double* out) {
