@@ -4,6 +4,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -44,18 +45,65 @@ struct le_sim {
 namespace {
 
 constexpr size_t kAlign = 256;
+// particles up to which a system takes small tiles, dense (kDensePartners
+// partners and more) and sparse
+constexpr int64_t kSmallDense = 10000, kSmallSparse = 2000;
+constexpr double kDensePartners = 40.0;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Geometry {
   int32_t nc[3];
   double rc, rlist;
-  int32_t K;
+  int32_t cap;                  // list capacity per particle
   int64_t np;
-  int32_t nblocks;
+  int32_t staged, tiles;        // pair layout and tile configuration (kTiles*)
+  int32_t tile, halo_cap, ntiles, nblocks;
+  int32_t by_sh, bz_sh;
   int32_t bcap;
   int32_t sp_cells, sp_blocks;  // scan-and-permute pass: cells per block, blocks
 };
+
+// Expected positions in the halo of a tile of T particles in beams of h x w
+// rows: the rows next to the stretch of the beam that the tile covers, with `more` cells
+// beyond what its particles fill (one on average, as it starts and ends
+// within a cell, and one at both ends; three more where a tile lies in two
+// beams and across a gradient face).  A tile should lie in at most two beams.
+double tile_halo(const Geometry& g, double cell_n, int T, int h, int w, double more) {
+  const double ph = std::min(h, g.nc[1]), pw = std::min(w, g.nc[2]);
+  const double len = T / (cell_n * ph * pw);
+  if (len > g.nc[0]) return 1e12 * len;
+  return (ph + 2.0) * (pw + 2.0) * (len + more) * cell_n;
+}
+
+// Tiles, beams and pair layout: pure functions of the parameters, so that a
+// simulation steps alike alone and in any batch.
+void plan_tiles(const le_params* p, Geometry* g, double list_pp) {
+  const double cell_n = (double)p->n / ((double)g->nc[0] * g->nc[1] * g->nc[2]);
+  const bool small = p->n <= (list_pp >= kDensePartners ? kSmallDense : kSmallSparse);
+  g->tile = small ? kTileSmall : kTile;
+  double best = 0.0;
+  for (int b = 0; b < 4; ++b)
+    for (int a = 0; a < 4; ++a) {
+      const double h = tile_halo(*g, cell_n, g->tile, 1 << a, 1 << b, 3.0);
+      if ((a == 0 && b == 0) || h < best) {
+        best = h;
+        g->by_sh = a;
+        g->bz_sh = b;
+      }
+    }
+  const double most = tile_halo(*g, cell_n, g->tile, 1 << g->by_sh, 1 << g->bz_sh, 6.0);
+  // (a tile keeps about three quarters of the positions of its halo's cells)
+  g->tiles = 0.8 * most <= TileSparse::HALO ? kTilesSparse : kTilesDense;
+  g->halo_cap = g->tiles == kTilesSparse ? TileSparse::HALO : TileDense::HALO;
+  // LDS halo at force time when partners per particle clearly outnumber the
+  // positions a tile must stage per particle
+  const double halo_pp = best / g->tile;
+  g->staged = (p->tune == 1) ? 1 : (p->tune == 2) ? 0 : (list_pp >= 3.0 * halo_pp ? 1 : 0);
+  if (p->thermostat == LE_THERMO_DPD || p->force_cap > 0.0) g->staged = 0;
+  g->ntiles = (int32_t)((p->n + g->tile - 1) / g->tile);
+  g->nblocks = g->staged ? g->ntiles : (int32_t)((p->n + kTile - 1) / kTile);
+}
 
 le_status validate(const le_params* p, Geometry* g) {
   if (!p) return LE_E_ARG;
@@ -101,18 +149,15 @@ le_status validate(const le_params* p, Geometry* g) {
   if ((int64_t)g->nc[0] * g->nc[1] * g->nc[2] > (int64_t)0x7fffffff - 1) return LE_E_GEOMETRY;
   g->rc = rc;
   g->rlist = rlist;
-  // capacity of each of a particle's two sub-lists (each holds about half of
-  // its partners; the first also the second's partial last block):
-  // max_neighbors / 2, or from the density with a margin
-  if (p->max_neighbors > 0) {
-    g->K = (p->max_neighbors + 1) / 2;
-  } else {
-    double rho = (double)p->n / (p->box[0] * p->box[1] * p->box[2]);
-    double mean = 4.0 / 3.0 * M_PI * rlist * rlist * rlist * rho;
-    g->K = (int32_t)ceil(mean) + 40;
+  // capacity of a particle's list: max_neighbors, or twice the mean of the
+  // density with a margin, in two halves of whole blocks of 8 entries
+  const double rho = (double)p->n / (p->box[0] * p->box[1] * p->box[2]);
+  const double list_pp = 4.0 / 3.0 * M_PI * rlist * rlist * rlist * rho;  // mean partners per particle
+  {
+    int32_t K = p->max_neighbors > 0 ? (p->max_neighbors + 1) / 2 : (int32_t)ceil(list_pp) + 40;
+    if (K > 4096) K = 4096;
+    g->cap = 2 * ((K + 7) / 8 * 8);
   }
-  if (g->K > 4096) g->K = 4096;
-  g->K = (g->K + 7) / 8 * 8;  // lists are stored in blocks of 8 (plain) and 4 (other) entries
   g->np = (p->n + 1 + kBlock - 1) / kBlock * kBlock;  // +1: sentinel slot
   {
     // bucket capacity: generous over the mean cell occupancy
@@ -120,7 +165,7 @@ le_status validate(const le_params* p, Geometry* g) {
     double cap = fmin(4.0 * mean + 32.0, (double)p->n);
     g->bcap = ((int32_t)ceil(cap) + 7) / 8 * 8;
   }
-  g->nblocks = (int32_t)((p->n + kTile - 1) / kTile);
+  plan_tiles(p, g, list_pp);
   {
     // about kSortParticles particles per block of the scan-and-permute pass
     const int64_t ncell = (int64_t)g->nc[0] * g->nc[1] * g->nc[2];
@@ -155,16 +200,19 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
   }
   t.vt = (p->thermostat == LE_THERMO_DPD) ? (double*)take(4 * np * sizeof(double)) : nullptr;
   t.slot_of_tag = (int32_t*)take(np * sizeof(int32_t));
-  t.bucket = (int2*)take(ncell * (size_t)g.bcap * sizeof(int2));
+  {
+    // the buckets of the sort and the halo tables of the lists (see Dev::halo)
+    const size_t halo_n = g.staged ? (size_t)g.ntiles * g.halo_cap : 0;
+    char* m = take(std::max(ncell * (size_t)g.bcap * sizeof(int2), halo_n * sizeof(uint32_t)));
+    t.bucket = (int2*)m;
+    t.halo = (uint32_t*)m;
+  }
   t.cell_count = (int32_t*)take(ncell * sizeof(int32_t));
   t.cell_start = (int32_t*)take((ncell + 1) * sizeof(int32_t));
-  t.nl16 = (uint16_t*)take((size_t)g.K * 2 * np * sizeof(uint16_t));
-  t.nlo = (uint32_t*)take((size_t)g.K * 2 * np * sizeof(uint32_t));
-  t.n_plain = (int32_t*)take(2 * np * sizeof(int32_t));
-  t.n_og = (int32_t*)take(2 * np * sizeof(int32_t));
-  t.halo_slot = (int32_t*)take((size_t)g.nblocks * kHalo * sizeof(int32_t));
-  t.halo_code = (uint8_t*)take((size_t)g.nblocks * kHalo);
-  t.tile_nstage = (int32_t*)take((size_t)g.nblocks * sizeof(int32_t));
+  t.nl = (uint4*)take((size_t)(g.cap / 4) * np * sizeof(uint4));
+  t.n_plain = (int32_t*)take(np * sizeof(int32_t));
+  t.n_og = (int32_t*)take(np * sizeof(int32_t));
+  t.tile_nstage = (int32_t*)take((size_t)g.ntiles * sizeof(int32_t));
   t.bond = (p->chain_len > 0) ? (int32_t*)take(2 * np * sizeof(int32_t)) : nullptr;
   t.partials = (double*)take((size_t)g.nblocks * kStressComps * sizeof(double));
   t.obs_part = (double*)take((size_t)((p->n + kBlock - 1) / kBlock) * (3 * LE_MAX_BINS + 4) *
@@ -184,9 +232,9 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
     d->vt = t.vt;
     d->slot_of_tag = t.slot_of_tag; d->bucket = t.bucket;
     d->cell_count = t.cell_count; d->cell_start = t.cell_start;
-    d->nl16 = t.nl16; d->nlo = t.nlo;
+    d->nl = t.nl;
     d->n_plain = t.n_plain; d->n_og = t.n_og;
-    d->halo_slot = t.halo_slot; d->halo_code = t.halo_code; d->tile_nstage = t.tile_nstage;
+    d->halo = t.halo; d->tile_nstage = t.tile_nstage;
     d->bond = t.bond;
     d->partials = t.partials;
     d->obs_part = t.obs_part;
@@ -230,26 +278,22 @@ void fill_geometry(const le_params* p, const Geometry& g, Dev* d) {
   d->mass = p->mass;
   d->eps24 = 24.0 * p->eps;
   d->sig2 = p->sigma * p->sigma;
+  d->lj_b = d->eps24 * (d->sig2 * d->sig2 * d->sig2);
+  d->lj_a = 2.0 * d->lj_b * (d->sig2 * d->sig2 * d->sig2);
   d->rc2 = g.rc * g.rc;
   d->rlist = g.rlist;
   d->rlist2 = g.rlist * g.rlist;
   {
-    // Bound on |r2_f32 - r2_f64| for a pair near the list radius.  Staged
-    // coordinates are relative to a tile particle and image-shifted, so each
-    // lies within 4 L_max + r_list of zero; rounding each to float moves it by
-    // at most 2^-24 of that, a displacement component by delta = twice that,
-    // r2 by 2 sqrt(3) (r_list + delta) delta + 3 delta^2, and the three float
-    // operations forming r2 add 3 ulps of r_list^2.  Doubled for safety.
+    // thresholds of the search's FP32 pre-test: r_list^2 with the rounding of
+    // the FP64 coordinates about a tile origin, and the relative band (64 u, u = 2^-24, and
+    // the rounding of the thresholds themselves)
     const double lmax = fmax(p->box[0], fmax(p->box[1], p->box[2]));
-    const double u = ldexp(1.0, -24);
-    const double delta = 2.0 * u * (4.0 * lmax + g.rlist);
     const double rl2 = g.rlist * g.rlist;
-    const double margin = 2.0 * (2.0 * sqrt(3.0) * (g.rlist + delta) * delta + 3.0 * delta * delta +
-                                 4.0 * u * rl2 * 1.01) + 1e-12 * rl2;
+    const double margin = 1e-12 * rl2 + ldexp(64.0 * lmax * g.rlist, -52);
     d->nb_lo = nextafterf((float)(rl2 - margin), 0.0f);
     d->nb_hi = nextafterf((float)(rl2 + margin), INFINITY);
-    if ((double)d->nb_lo + margin > rl2) d->nb_lo = nextafterf(d->nb_lo, 0.0f);
-    if ((double)d->nb_hi - margin < rl2) d->nb_hi = nextafterf(d->nb_hi, INFINITY);
+    d->nb_rel = ldexpf(72.0f, -24);
+    d->rlist_f = nextafterf((float)g.rlist, INFINITY);
   }
   d->fene_k = p->fene_k;
   d->fene_r02 = p->fene_r0 * p->fene_r0;
@@ -258,8 +302,10 @@ void fill_geometry(const le_params* p, const Geometry& g, Dev* d) {
   d->inv_vol = 1.0 / (p->box[0] * p->box[1] * p->box[2]);
   d->n = (int32_t)p->n;
   d->np = (int32_t)g.np;
-  d->K = g.K;
-  d->np2 = (int32_t)(2 * g.np);
+  d->cap = g.cap;
+  d->by_sh = g.by_sh; d->bz_sh = g.bz_sh;
+  d->tile = g.tile; d->tile_sh = __builtin_ctz((unsigned)g.tile); d->halo_cap = g.halo_cap;
+  d->staged = g.staged; d->tiles = g.tiles;
   d->chain_len = p->n_chains > 0 ? p->chain_len : 0;
   d->n_bonded = (int32_t)(p->n_chains * (int64_t)p->chain_len);
   d->precision = p->precision;
@@ -267,25 +313,10 @@ void fill_geometry(const le_params* p, const Geometry& g, Dev* d) {
   d->seed_hi = (uint32_t)(p->seed >> 32);
   d->dpd_key_hi = d->seed_hi ^ 0x44504421u;
   d->nblocks = g.nblocks;
-  d->ntiles = g.nblocks;
+  d->ntiles = g.ntiles;
   d->bcap = g.bcap;
   d->sp_cells = g.sp_cells;
   d->sp_blocks = g.sp_blocks;
-  {
-    // LDS halo at force time when partners per particle clearly outnumber the
-    // positions a tile must stage per particle (strip tile of kTile particles:
-    // 9 neighbouring rows of (tile cells + 2) cells)
-    const double rho = (double)p->n / (p->box[0] * p->box[1] * p->box[2]);
-    const double cell_n = rho * (p->box[0] / g.nc[0]) * (p->box[1] / g.nc[1]) * (p->box[2] / g.nc[2]);
-    const double tile_cells = kTile / fmax(cell_n, 1e-9);
-    const double halo_pp = 9.0 * (tile_cells + 2.0) * cell_n / kTile;
-    const double list_pp = 4.0 / 3.0 * M_PI * g.rlist * g.rlist * g.rlist * rho;
-    d->staged = (p->tune == 1) ? 1 : (p->tune == 2) ? 0 : (list_pp >= 3.0 * halo_pp ? 1 : 0);
-    if (p->thermostat == LE_THERMO_DPD || p->force_cap > 0.0) d->staged = 0;
-    // a sparse system's tile halo (with a margin) fits the smaller search
-    // halo, which leaves room for more resident blocks
-    d->small_halo = (!d->staged && 1.15 * halo_pp * kTile <= kHaloSearch) ? 1 : 0;
-  }
 }
 
 le_status hip_check(hipError_t e) { return e == hipSuccess ? LE_OK : LE_E_HIP; }
@@ -374,51 +405,60 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 namespace {
 
 // ---------------------------------------------------------------------------
-// Batched stepping: simulations that share a kernel configuration form a
-// group; each step launches every kernel once per group (at most kMaxBatch
-// simulations per launch), the blocks of all members in one grid.
+// Batched stepping: each step launches every kernel once for all members (at
+// most kMaxBatch per launch), their blocks in one grid; the list search and
+// the force kernel, which differ by kernel configuration, once per group of
+// members that share one.
 
 struct BatchGroup {
   Dev cfg;                     // host descriptor of the first member (kernel configuration)
   std::vector<le_sim*> sims;
-  Batch par[2], bin[2], scan[2], tile[2], one[2];  // [v]: v = 0 descriptors of the copies current at the call
+  Batch par[2], bin[2], scan[2], tile[2], blk[2], one[2];  // [v]: v = 0 descriptors of the copies current at the call
+};
+
+struct BatchPlan {
+  std::vector<BatchGroup> groups;  // by kernel configuration
+  std::vector<BatchGroup> all;     // every member (cfg unused)
 };
 
 bool same_config(const Dev& a, const Dev& b) {
-  return a.staged == b.staged && a.small_halo == b.small_halo && a.precision == b.precision &&
+  return a.staged == b.staged && a.tiles == b.tiles && a.precision == b.precision &&
          (a.chain_len > 0) == (b.chain_len > 0) && (a.force_cap > 0.0) == (b.force_cap > 0.0) &&
          (a.thermostat == LE_THERMO_DPD) == (b.thermostat == LE_THERMO_DPD);
 }
 
 void fill_group(BatchGroup& g) {
   for (int v = 0; v < 2; ++v) {
-    Batch* bs[5] = {&g.par[v], &g.bin[v], &g.scan[v], &g.tile[v], &g.one[v]};
+    Batch* bs[6] = {&g.par[v], &g.bin[v], &g.scan[v], &g.tile[v], &g.blk[v], &g.one[v]};
     for (Batch* b : bs) {
       memset(b, 0, sizeof(Batch));
       b->nsims = (int32_t)g.sims.size();
     }
-    int32_t op = 0, ob = 0, os = 0, ot = 0;
+    int32_t op = 0, ob = 0, os = 0, ot = 0, of = 0;
     for (size_t k = 0; k < g.sims.size(); ++k) {
       le_sim* s = g.sims[k];
       const int cur = s->d.ctrl == s->ctrl_base ? 0 : 1;
       const Dev* dv = s->dev_dev + (cur ^ v);
       g.par[v].start[k] = op; g.bin[v].start[k] = ob; g.scan[v].start[k] = os; g.tile[v].start[k] = ot;
+      g.blk[v].start[k] = of;
       g.one[v].start[k] = (int32_t)k;
-      g.par[v].dev[k] = g.bin[v].dev[k] = g.scan[v].dev[k] = g.tile[v].dev[k] = g.one[v].dev[k] = dv;
+      for (Batch* b : bs) b->dev[k] = dv;
       op += (s->d.n + kBlock - 1) / kBlock;
       ob += (s->d.n + kBinBlock - 1) / kBinBlock;
       os += s->d.sp_blocks;
       ot += s->d.ntiles;
+      of += s->d.nblocks;
     }
     const size_t m = g.sims.size();
     g.par[v].start[m] = op; g.bin[v].start[m] = ob; g.scan[v].start[m] = os; g.tile[v].start[m] = ot;
+    g.blk[v].start[m] = of;
     g.one[v].start[m] = (int32_t)m;
   }
 }
 
 // Group the simulations (at most kMaxBatch per group).  LE_E_ARG for a null,
 // repeated or foreign-stream simulation.
-le_status plan_batch(le_sim* const* sims, int32_t nsims, std::vector<BatchGroup>& groups) {
+le_status plan_batch(le_sim* const* sims, int32_t nsims, BatchPlan& plan) {
   if (!sims || nsims < 1) return LE_E_ARG;
   for (int32_t a = 0; a < nsims; ++a) {
     if (!sims[a] || sims[a]->stream != sims[0]->stream) return LE_E_ARG;
@@ -428,21 +468,26 @@ le_status plan_batch(le_sim* const* sims, int32_t nsims, std::vector<BatchGroup>
   for (int32_t a = 0; a < nsims; ++a) {
     le_sim* s = sims[a];
     if (s->host_status) continue;  // latched: its kernels would be no-ops anyway
-    BatchGroup* g = nullptr;
-    for (BatchGroup& c : groups)
-      if (c.sims.size() < (size_t)kMaxBatch && same_config(c.cfg, s->d)) { g = &c; break; }
-    if (!g) {
-      groups.emplace_back();
-      g = &groups.back();
-      g->cfg = s->d;
-    }
-    g->sims.push_back(s);
+    auto add = [&](std::vector<BatchGroup>& to, bool by_config) {
+      BatchGroup* g = nullptr;
+      for (BatchGroup& c : to)
+        if (c.sims.size() < (size_t)kMaxBatch && (!by_config || same_config(c.cfg, s->d))) { g = &c; break; }
+      if (!g) {
+        to.emplace_back();
+        g = &to.back();
+        g->cfg = s->d;
+      }
+      g->sims.push_back(s);
+    };
+    add(plan.groups, true);
+    add(plan.all, false);
   }
-  for (BatchGroup& g : groups) fill_group(g);
+  for (BatchGroup& g : plan.groups) fill_group(g);
+  for (BatchGroup& g : plan.all) fill_group(g);
   return LE_OK;
 }
 
-le_status step_batch(std::vector<BatchGroup>& groups, hipStream_t q, int64_t nsteps, int32_t sample_every,
+le_status step_batch(BatchPlan& plan, hipStream_t q, int64_t nsteps, int32_t sample_every,
                      double* const* rings, int64_t ring_cap, le_sim* const* order, int32_t norder) {
   // ring of each member: the caller's rings are indexed like `order`
   auto ring_of = [&](le_sim* s) -> double* {
@@ -452,40 +497,42 @@ le_status step_batch(std::vector<BatchGroup>& groups, hipStream_t q, int64_t nst
   };
   int v = 0;  // which descriptor set is current
   le_status st = LE_OK;
-  for (BatchGroup& g : groups)
+  auto rebuild_all = [&]() {
+    for (BatchGroup& g : plan.all)
+      if (st == LE_OK) st = hip_check(launch_sort_b(g.bin[v], g.scan[v ^ 1], q));
+    for (BatchGroup& g : plan.groups)
+      if (st == LE_OK) st = hip_check(launch_search_b(g.tile[v ^ 1], g.cfg, q));
+    v ^= 1;
+  };
+  for (BatchGroup& g : plan.all)
     if (st == LE_OK) st = hip_check(launch_kick_drift_b(g.par[v], q));
-  for (BatchGroup& g : groups)
-    if (st == LE_OK) st = hip_check(launch_rebuild_b(g.bin[v], g.scan[v ^ 1], g.tile[v ^ 1], g.cfg, q));
-  v ^= 1;
+  rebuild_all();
   int64_t ns = 0;
   for (int64_t k = 1; k <= nsteps && st == LE_OK; ++k) {
     const bool last = (k == nsteps);
     const bool sample = sample_every > 0 && (k % sample_every) == 0;
-    for (BatchGroup& g : groups) {
+    for (BatchGroup& g : plan.groups) {
       if (st != LE_OK) break;
       if (g.cfg.thermostat == LE_THERMO_DPD) {
-        st = hip_check(launch_force_b(g.tile[v], g.par[v], g.cfg, q, kDpdForce, sample));
-        if (st == LE_OK) st = hip_check(launch_integrate_b(g.tile[v], q, last, sample));
+        st = hip_check(launch_force_b(g.blk[v], g.par[v], g.cfg, q, kDpdForce, sample));
+        if (st == LE_OK) st = hip_check(launch_integrate_b(g.blk[v], q, last, sample));
       } else {
-        st = hip_check(launch_force_b(g.tile[v], g.par[v], g.cfg, q, last ? kStepLast : kStepFused, sample));
+        st = hip_check(launch_force_b(g.blk[v], g.par[v], g.cfg, q, last ? kStepLast : kStepFused, sample));
       }
-      if (st == LE_OK && sample) {
-        BatchOut out;
-        memset(&out, 0, sizeof(out));
-        for (size_t m = 0; m < g.sims.size(); ++m) out.ptr[m] = ring_of(g.sims[m]) + 6 * (ns % ring_cap);
-        st = hip_check(launch_stress_final_b(g.one[v], out, q));
-      }
+    }
+    for (BatchGroup& g : plan.all) {
+      if (st != LE_OK || !sample) break;
+      BatchOut out;
+      memset(&out, 0, sizeof(out));
+      for (size_t m = 0; m < g.sims.size(); ++m) out.ptr[m] = ring_of(g.sims[m]) + 6 * (ns % ring_cap);
+      st = hip_check(launch_stress_final_b(g.one[v], out, q));
     }
     if (sample) ++ns;
-    if (st == LE_OK && !last) {
-      for (BatchGroup& g : groups)
-        if (st == LE_OK) st = hip_check(launch_rebuild_b(g.bin[v], g.scan[v ^ 1], g.tile[v ^ 1], g.cfg, q));
-      v ^= 1;
-    }
+    if (st == LE_OK && !last) rebuild_all();
   }
   // every member's control copy alternated once per rebuild test (nsteps times)
   if (nsteps & 1)
-    for (BatchGroup& g : groups)
+    for (BatchGroup& g : plan.all)
       for (le_sim* s : g.sims) {
         const bool first = s->d.ctrl == s->ctrl_base;
         s->d.ctrl = first ? s->ctrl_base + 1 : s->ctrl_base;
@@ -676,14 +723,14 @@ le_status le_step_batch(le_sim* const* sims, int32_t nsims, int64_t nsteps, int3
                         double* const* stress_rings, int64_t ring_cap) {
   if (nsteps < 0) return LE_E_ARG;
   if (sample_every > 0 && (!stress_rings || ring_cap <= 0)) return LE_E_ARG;
-  std::vector<BatchGroup> groups;
-  le_status st = plan_batch(sims, nsims, groups);
+  BatchPlan plan;
+  le_status st = plan_batch(sims, nsims, plan);
   if (st != LE_OK) return st;
   if (sample_every > 0)
     for (int32_t k = 0; k < nsims; ++k)
       if (!stress_rings[k]) return LE_E_ARG;
-  if (nsteps == 0 || groups.empty()) return LE_OK;
-  return step_batch(groups, sims[0]->stream, nsteps, sample_every, stress_rings, ring_cap, sims, nsims);
+  if (nsteps == 0 || plan.all.empty()) return LE_OK;
+  return step_batch(plan, sims[0]->stream, nsteps, sample_every, stress_rings, ring_cap, sims, nsims);
 }
 
 le_status le_batch_graph_create(le_sim* const* sims, int32_t nsims, int64_t nsteps, int32_t sample_every,
@@ -691,10 +738,10 @@ le_status le_batch_graph_create(le_sim* const* sims, int32_t nsims, int64_t nste
   if (!out || nsteps <= 0 || (nsteps & 1)) return LE_E_ARG;
   *out = nullptr;
   if (sample_every > 0 && (!stress_rings || ring_cap <= 0)) return LE_E_ARG;
-  std::vector<BatchGroup> groups;
-  le_status st = plan_batch(sims, nsims, groups);
+  BatchPlan plan;
+  le_status st = plan_batch(sims, nsims, plan);
   if (st != LE_OK) return st;
-  if (groups.empty()) return LE_E_STATE;
+  if (plan.all.empty()) return LE_E_STATE;
   if (sample_every > 0)
     for (int32_t k = 0; k < nsims; ++k)
       if (!stress_rings[k]) return LE_E_ARG;
@@ -703,14 +750,14 @@ le_status le_batch_graph_create(le_sim* const* sims, int32_t nsims, int64_t nste
   le_graph* g = new (std::nothrow) le_graph();
   if (!g) return LE_E_ARG;
   g->stream = q;
-  for (BatchGroup& b : groups)
+  for (BatchGroup& b : plan.all)
     for (le_sim* s : b.sims) {
       g->sims.push_back(s);
       g->ctrl_at.push_back(s->d.ctrl);
     }
   st = hip_check(hipStreamBeginCapture(q, hipStreamCaptureModeThreadLocal));
   if (st == LE_OK) {
-    le_status st_step = step_batch(groups, q, nsteps, sample_every, stress_rings, ring_cap, sims, nsims);
+    le_status st_step = step_batch(plan, q, nsteps, sample_every, stress_rings, ring_cap, sims, nsims);
     le_status st_end = hip_check(hipStreamEndCapture(q, &g->graph));
     st = st_step != LE_OK ? st_step : st_end;
   }

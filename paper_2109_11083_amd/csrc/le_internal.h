@@ -10,18 +10,27 @@
 namespace le {
 
 constexpr int kBlock = 256;        // threads per block of the streaming per-particle kernels
-constexpr int kTile = 128;         // particles (= threads) per tile of the pair kernels
-constexpr int kHalo = 2560;        // positions a tile stages in LDS (slot kHalo: far sentinel)
-constexpr int kHaloSearch = 1536;  // the same for the list search alone (systems without a force-time halo)
-static_assert(kHaloSearch <= kHalo, "the halo tables are sized for kHalo");
-static_assert(kHalo % (4 * kTile) == 0, "halo staging loops assume whole rounds of the tile");
-constexpr int kForceTPP = 4;       // threads per particle of the halo-layout force kernel
-constexpr int kGlobalTPP = 1;      // threads per particle of the global-layout force kernel (2: one per sub-list)
-static_assert(kHalo % (kForceTPP * kTile) == 0, "halo staging rounds of the force kernel");
-constexpr int kMaxRows = 3;        // cell rows a tile may span and still be staged
-constexpr int kPieces = 4;         // x-image pieces per (row, dy, dz) of a tile
-constexpr int kPlainBatch = 8;     // padding of the plain list (LDS gathers in flight)
-constexpr int kOtherBatch = 4;     // padding of the imaged / global lists
+// Particles per tile of the list search and of the force kernel with the LDS
+// halo (Dev::tile), and per block of the pair kernels without it (kTile).  Small
+// systems take small tiles, as many more blocks: 1000 particles are 8 tiles of
+// 128, on 8 of 256 CUs.
+constexpr int kTile = 128, kTileSmall = 32;
+constexpr int kSearchThreads = 512;
+// Tile configurations: positions a tile may stage (LDS slot HALO: far
+// sentinel), threads per block of the force kernel (shared among the tile's particles),
+// whether a batch spreads its blocks over the XCDs.  Sparse systems stage and
+// list far fewer partners than dense ones, so they take a smaller halo (more blocks
+// per CU) and fewer threads per particle.
+struct TileDense { static constexpr int HALO = 2048, kForceThreads = 512; static constexpr bool kSpread = true; };
+struct TileSparse { static constexpr int HALO = 1024, kForceThreads = 256; static constexpr bool kSpread = false; };
+// without a force-time halo: the dense list search (two blocks per CU beside the
+// table of entries it keeps), and the blocks of the force kernel
+struct TileDenseGlobal { static constexpr int HALO = 2048; };
+struct TileNone { static constexpr int HALO = 0, kForceThreads = kTile; static constexpr bool kSpread = false; };
+enum { kTilesDense = 0, kTilesSparse = 1 };
+constexpr int kCells = 512;        // cells a tile's halo may have (entries of the staging table)
+constexpr int kPlainBatch = 8;     // padding of the lists of LDS indices (one 16-byte block)
+constexpr int kOtherBatch = 4;     // padding of the lists of global slots
 constexpr int kStressComps = 12;   // 6 kinetic + 6 virial partial sums per block
 constexpr int kSlots = 64;         // words (one per 128-byte line) a block maximum is spread over
 constexpr int kLineInts = 32;      // 32-bit words per 128-byte line
@@ -74,6 +83,7 @@ struct Dev {
   double dpd_rc2, dpd_inv_rc;      // DPD: r_c^2 and 1 / r_c of the weight omega
   double mass;
   double eps24, sig2;              // 24 eps, sigma^2
+  double lj_a, lj_b;               // 48 eps sigma^12, 24 eps sigma^6
   double rc2, rlist, rlist2;       // cutoff^2, list radius, list radius^2
   double fene_k, fene_r02;
   double angle_k;                  // cosine angle term of the chains (0: none)
@@ -81,21 +91,23 @@ struct Dev {
   double inv_vol;
   int32_t nx, ny, nz, ncell;
   int32_t n, np;                   // particles, padded stride (np > n: slot n is a far-away sentinel)
-  int32_t K;                       // capacity of each of a particle's two sub-lists
-  int32_t np2;                     // 2 * np: sub-list v = h * np + i of particle i, h = 0, 1
+  int32_t cap;                     // capacity of a particle's list (a multiple of 8)
+  int32_t by_sh, bz_sh;            // log2 of the rows of a beam along y and z (see cell_slot)
+  int32_t tile, tile_sh, halo_cap; // particles per tile and their log2, positions it may stage
   int32_t chain_len;
   int32_t n_bonded;                 // n_chains * chain_len (tags >= n_bonded are free)
   int32_t precision;
   int32_t staged;                  // 1: partners in the tile's LDS halo; 0: all from global memory
-  int32_t small_halo;              // 1: the list search stages at most kHaloSearch positions per tile
-  // FP32 pre-test of the list build: r2 (float, tile-relative coordinates)
-  // below nb_lo is certainly inside r_list^2, at or above nb_hi certainly
-  // outside; in between the plain FP64 displacement decides.
-  float nb_lo, nb_hi;
+  int32_t tiles;                   // tile configuration (kTiles*)
+  // FP32 pre-test of the list build: r^2 (float) below nb_lo - nb_rel S is
+  // certainly inside r_list^2, at or above nb_hi + nb_rel S certainly outside (S:
+  // the squared extent of the pair's coordinates, see neighbors_body); in
+  // between the plain FP64 displacement decides.
+  float nb_lo, nb_hi, nb_rel, rlist_f;
   uint32_t seed_lo, seed_hi;
   uint32_t dpd_key_hi;             // seed_hi ^ 0x44504421: key word of the DPD pair noise
   int32_t thermostat;              // LE_THERMO_*
-  int32_t nblocks;                 // blocks of the pair kernels (= ntiles)
+  int32_t nblocks;                 // blocks of the force kernel (ntiles, or one per kTile particles without the halo)
   // buffers (device)
   double* pos[2];                  // double4 [np] each (x, y, z, wrap counts along y and z)
   double* vel[2];                  // [3][np]
@@ -109,25 +121,22 @@ struct Dev {
                                    // cell, in arrival order
   int32_t* cell_count;             // [ncell]
   int32_t* cell_start;             // [ncell + 1]
-  // Neighbour lists: two sub-lists per particle (v = h * np + i, h = 0, 1,
-  // alternate batches of 8 candidates of each stencil range).  Entry k of sub-list v lives in a
-  // block of consecutive entries: blocks of 8 (one 16-byte load) for nl16, of
-  // 4 for nlo; block b of sub-lists v, v+1, ... is contiguous.
-  //   nl16  partners staged in the tile's LDS halo (any image): LDS index,
-  //         element k at ((k/8)*np2 + v)*8 + k%8
-  //   nlo   partners not staged: slot in global memory in the low kSlotBits
-  //         bits, image code (pack_img) above them; element k at
-  //         ((k/4)*np2 + v)*4 + k%4
-  uint16_t* nl16;
-  uint32_t* nlo;
-  int32_t* n_plain;                // [np2] staged entries per sub-list, multiple of kPlainBatch
-  int32_t* n_og;                   // [np2] global entries per sub-list, multiple of kOtherBatch
-  int32_t* halo_slot;              // [ntiles][kHalo] slot staged at each LDS position
-  uint8_t* halo_code;              // [ntiles][kHalo] image code of each staged position
+  // Neighbour lists: cap / 4 units of 16 bytes per particle, unit u of particles
+  // i, i + 1, ... contiguous (u np + i).
+  //   partners found in the tile's staged halo, from unit 0 up: LDS indices, 8 (16-bit)
+  //     per unit (halo layout), or slots in global memory in the low kSlotBits bits with
+  //     the image code (pack_img) above them, 4 per unit (global layout)
+  //   partners of rows that did not fit, from the last unit down: slots and codes
+  uint4* nl;
+  int32_t* n_plain;                // [np] entries from the front, a multiple of 8 (halo layout) or 4
+  int32_t* n_og;                   // [np] entries from the back, a multiple of 4
+  // [ntiles][halo_cap] slot and image code (og_entry) of each LDS position.  Shares its memory with
+  // the buckets, which only hold values from the binning to the end of the sort.
+  uint32_t* halo;
   int32_t* tile_nstage;            // [ntiles] staged positions per tile
   int32_t ntiles;
   int32_t* bond;                   // [2][np] slot of the chain neighbour below/above, -1 if none
-  double* partials;                // [nblocks][kStressComps] (nblocks = ntiles)
+  double* partials;                // [nblocks][kStressComps]
   double* obs_part;                // [ceil(n / kBlock)][3 * LE_MAX_BINS + 4] observable partials
   Ctrl* ctrl;                      // current control copy (see Ctrl)
   Ctrl* ctrl_other;                // the other control copy (written by a batched rebuild test)
@@ -204,16 +213,16 @@ hipError_t launch_status_out(const Dev& d, hipStream_t s, int32_t* out);
 // batch (all of one kernel configuration, given by `cfg`, the host copy of any
 // member's descriptor).  Batches by block kind: `par` one block per kBlock
 // particles, `bin` one per kBinBlock particles, `scan` one per sp_cells cells,
-// `tile` one per kTile particles,
+// `tile` one per tile, `blk` one per block of the force kernel,
 // `one` one block per simulation; `cur` and `nxt` name the descriptors of the
 // current and the other control copy.
 hipError_t launch_store_dev(const Dev& a, const Dev& b, Dev* dst, hipStream_t s);
 hipError_t launch_kick_drift_b(const Batch& par_cur, hipStream_t s);
-hipError_t launch_rebuild_b(const Batch& bin_cur, const Batch& scan_nxt, const Batch& tile_nxt,
-                            const Dev& cfg, hipStream_t s);
-hipError_t launch_force_b(const Batch& tile_cur, const Batch& par_cur, const Dev& cfg, hipStream_t s,
+hipError_t launch_sort_b(const Batch& bin_cur, const Batch& scan_nxt, hipStream_t s);
+hipError_t launch_search_b(const Batch& tile_nxt, const Dev& cfg, hipStream_t s);
+hipError_t launch_force_b(const Batch& blk_cur, const Batch& par_cur, const Dev& cfg, hipStream_t s,
                           ForceMode mode, bool sample);
-hipError_t launch_integrate_b(const Batch& tile_cur, hipStream_t s, bool last, bool sample);
+hipError_t launch_integrate_b(const Batch& blk_cur, hipStream_t s, bool last, bool sample);
 hipError_t launch_stress_final_b(const Batch& one_cur, const BatchOut& out, hipStream_t s);
 hipError_t launch_offsets(double sr, double Lx, double Ly, double dt, int64_t step0, int64_t count,
                           double* out, hipStream_t s);

@@ -6,13 +6,14 @@
 // are requested explicitly (fma) only where results are compared with a
 // tolerance (force law, accumulations).
 //
-// Data layout (all cell-sorted by (cell id, tag), re-sorted at every
-// neighbour-list build):
-//   positions  double4 AoS (x, y, z, unused) -- one 32-byte gather per neighbour
+// Data layout (all sorted by (cell, tag) at every neighbour-list build, the
+// cells in beam order, see cell_slot):
+//   positions  double4 AoS (x, y, z, wrap counts) -- one 32-byte gather per neighbour
 //   velocities, forces  float64 SoA [3][np] -- streamed, coalesced
-//   neighbour list  int32 [K][np] (row-major by neighbour index, so that the
-//                   k-th entries of 64 consecutive particles are contiguous)
+//   neighbour lists  units of 16 bytes, unit u of consecutive particles contiguous
 #include <math.h>
+
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -99,6 +100,21 @@ __device__ __forceinline__ int cell_index(double v, double inv, int n) {
   if (k < 0) k = 0;
   if (k > n - 1) k = n - 1;
   return k;
+}
+
+// Place of a cell in the order of the slots.  Rows along x are grouped into
+// beams of 2^by_sh x 2^bz_sh rows (narrower at the box's upper faces); the
+// beams follow one another along y, then z, a beam's cells run slice by slice
+// along x, and the rows of a slice in a serpentine (y up and down along z, every
+// other slice backwards), so that consecutive slots lie in adjacent cells and a tile
+// of consecutive slots is compact.
+__device__ __forceinline__ int cell_slot(const Dev& d, int ix, int iy, int iz) {
+  const int y0 = iy >> d.by_sh << d.by_sh, z0 = iz >> d.bz_sh << d.bz_sh;
+  const int h = min(1 << d.by_sh, d.ny - y0), w = min(1 << d.bz_sh, d.nz - z0);
+  const int zz = iz - z0;
+  int r = (zz & 1) ? (zz + 1) * h - 1 - (iy - y0) : zz * h + (iy - y0);
+  if (ix & 1) r = h * w - 1 - r;
+  return d.nx * (z0 * d.ny + w * y0) + ix * (h * w) + r;
 }
 
 __device__ __forceinline__ int floor_div(int a, int b) {
@@ -297,7 +313,7 @@ __device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict_
       int ix = cell_index(x, d.inv_lx, d.nx);
       int iy = cell_index(y, d.inv_ly, d.ny);
       int iz = cell_index(z, d.inv_lz, d.nz);
-      cell = (iz * d.ny + iy) * d.nx + ix;
+      cell = cell_slot(d, ix, iy, iz);
     }
     // runs of equal cells among consecutive lanes share one atomic
     const int lane = threadIdx.x & 63;
@@ -508,24 +524,21 @@ __global__ void __launch_bounds__(kBlock) k_scan_permute_b(Batch b) {
 // (cell, image) pair is visited once; with L > 2 r_list at most one image of
 // a particle can lie within r_list, so no pair is counted twice.
 //
-// Tiles.  The particles of one tile (kTile consecutive cell-sorted slots)
-// span a few cell rows.  For every covered row r, offset (dy, dz) and x-image
-// sx, the cells the tile's stencils can reach in the neighbouring row form a
-// contiguous slot range (a "piece").  The pieces are staged into LDS in a
-// fixed order while they fit (kHalo positions).  With the halo layout,
-// halo_slot / halo_code record the slot and image of every LDS position so
-// that the force kernel can restage the same halo each step; the global
-// layout keeps that table in LDS for the search alone.  Pairs whose partner
-// is staged without image store its LDS index (16 bits, halo layout); the
-// others store the partner's slot and image code in one 32-bit word.  Lists
-// are padded with sentinels (LDS index kHalo, slot n) to whole batches.
+// Tiles.  A tile is T consecutive slots (kTile, or kTileSmall in small systems).  The slots follow the beam order of
+// the cells (cell_slot), so a tile covers a stretch [xa, xb] of one beam, or
+// the end of one and the start of the next (its segments).  The cells that a
+// segment's stencils reach, row by row, are staged into LDS in a fixed order
+// while they fit (HALO positions).  With the halo layout, d.halo
+// records the slot and image of every LDS position so that the force kernel can
+// restage the same halo each step, and the lists hold LDS indices
+// (16 bits); the global layout's lists hold slot and image code in one word.
+// Lists are padded with sentinels (LDS index HALO, slot n) to whole batches.
 
-// Element k of particle i in the blocked list layouts (see Dev).
-__device__ __forceinline__ size_t idx8(int k, int i, int np) {
-  return ((size_t)(k >> 3) * np + i) * 8 + (k & 7);
-}
-__device__ __forceinline__ size_t idx4(int k, int i, int np) {
-  return ((size_t)(k >> 2) * np + i) * 4 + (k & 3);
+// Units of particle i's list (see Dev): block b from the front, block b of
+// walked entries from the back.
+__device__ __forceinline__ size_t unit_front(const Dev& d, int b, int i) { return (size_t)b * d.np + i; }
+__device__ __forceinline__ size_t unit_back(const Dev& d, int b, int i) {
+  return (size_t)(d.cap / 4 - 1 - b) * d.np + i;
 }
 
 // Unwrapped x-cell range [klo, khi] reached from cells xa..xb of a row across
@@ -541,27 +554,6 @@ __device__ __forceinline__ void x_range(const Dev& d, int xa, int xb, int sy, do
   }
 }
 
-__device__ __forceinline__ int cell_of_pos(const Dev& d, double4 p) {
-  return (cell_index(p.z, d.inv_lz, d.nz) * d.ny + cell_index(p.y, d.inv_ly, d.ny)) * d.nx +
-         cell_index(p.x, d.inv_lx, d.nx);
-}
-
-constexpr int kWaves = kTile / 64;
-
-// Tile halo pieces: for each covered row r of the tile, offset (dy, dz) and
-// x-image sx, the slot range of the neighbouring row reached by the tile.
-// Fills the piece tables, assigns LDS offsets in a fixed order while they
-// fit, stages the positions and records their slots.  Called by all threads.
-struct Pieces {
-  int start[kMaxRows * 9][kPieces];
-  int count[kMaxRows * 9][kPieces];
-  int off[kMaxRows * 9][kPieces];  // LDS offset, -1 if not staged
-  int sx0[kMaxRows * 9];
-  int npc[kMaxRows * 9];
-  int code[kMaxRows * 9];          // image code (sy, sz) of the row; sx added per piece
-  int nseg, ntot;
-};
-
 // Exact list test of one pair: the plain-definition displacement between
 // particle i and slot q under image (sx, sy, sz), r^2 < r_list^2.
 __device__ __forceinline__ bool in_list_exact(const Dev& d, double4 pi, double4 pj, double shx,
@@ -574,411 +566,613 @@ __device__ __forceinline__ bool in_list_exact(const Dev& d, double4 pi, double4 
   return r2 < d.rlist2;
 }
 
-// Two threads per particle: thread t (half 0) and t + kTile (half 1) split
-// each (dy, dz) range in two and write two sub-lists, which the force kernel
-// reads as one sequence of batches.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kCand = 256;  // candidates a wave keeps before it tests them
+
+// Bounding box (x, y, z minima, then the negated maxima), and the square of
+// the distance from it within which a point may be within r_list of one of
+// its points (rounding of the floats included: they are within 2^-24 of their
+// values).
+struct Box { float v[6], reach2; };
+__device__ __forceinline__ float reach2_of(const Box& b, float rlist) {
+  const float ext = fmaxf(fmaxf(fmaxf(fabsf(b.v[0]), fabsf(b.v[1])), fmaxf(fabsf(b.v[2]), fabsf(b.v[3]))),
+                          fmaxf(fabsf(b.v[4]), fabsf(b.v[5])));
+  const float reach = rlist * 1.00001f + 1e-6f * (ext + rlist);
+  return reach * reach;
+}
+__device__ __forceinline__ bool in_reach(const Box& b, float x, float y, float z) {
+  const float dx = fmaxf(fmaxf(b.v[0] - x, x + b.v[3]), 0.0f);
+  const float dy = fmaxf(fmaxf(b.v[1] - y, y + b.v[4]), 0.0f);
+  const float dz = fmaxf(fmaxf(b.v[2] - z, z + b.v[5]), 0.0f);
+  return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)) <= b.reach2;
+}
+
+// Minimum over each row of 16 lanes (rotations within the row).
+__device__ __forceinline__ float row16_min(float v) {
+  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, false)));
+  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xf, 0xf, false)));
+  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x122, 0xf, 0xf, false)));
+  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xf, 0xf, false)));
+  return v;
+}
+
+// One stretch of a beam covered by a tile.  Its halo is the rows (y0 - 1 + ry,
+// z0 - 1 + rz), ry in [0, h + 2), rz in [0, w + 2); row (rz (h + 2) + ry) has
+// the nk cells klo[sy + 1] .. of the staging table from entry tb + row nk on.
+struct Seg {
+  int y0, z0, h, w;   // first row and height / width of the beam
+  int xa, xb;         // cells of the stretch along x
+  int klo[3], khi[3]; // unwrapped cells along x of its halo rows, by image sy = -1, 0, 1
+  int nk, tb;
+  double ox, oy, oz;  // origin of the staged floats: a particle of the stretch
+};
+
+// The lists of one tile by one block: a wave takes a cluster of 16 consecutive
+// slots.  All four 16-lane rows hold the same 16 particles.
+// The cluster's candidates are the staged cells of its bounding box in cells,
+// 16 at a time: r^2 = s_i + s_j - 2 x_i x_j with s = |x|^2 is one 16x16x4
+// FP32 matrix product (A: x, y, z, s of the candidates, B: -2x, -2y, -2z, 1 of
+// the particles, C: s_i), 256 pairs in 32 cycles, and lane (q, p) receives the
+// four candidates 4q .. 4q+3 of particle p.  An LDS ring per lane collects
+// what it accepts; a full block of eight leaves as one 16-byte store at the
+// particle's next block, and the four lanes' last, partial blocks are joined
+// at the end, so that a list carries one padding.
+//
+// FP32 pre-test.  The staged floats are within u = 2^-24 (relative) of the
+// coordinates about the segment's origin, and the product adds four rounded
+// terms of at most 4 S, S = (|x_i| + r_list)^2, so r^2 is within 64 u S of its
+// FP64 value for every candidate near r_list (farther ones are off by less
+// than their distance from r_list).  Outside that band the FP32 value decides,
+// inside it the plain FP64 displacement, so the list is exactly
+// {r^2 < r_list^2}.
+//
+// Bound by the vector unit (LJ, 256,000 particles, r_list 3.05: 3200 vector
+// instructions per cluster, 133 us) and, in small systems, by the chain of
+// phases: against one lane per particle half with the tests on the vector unit, 1000
+// particles take 38 instead of 111 us, 27,000 take 27 instead of 87, 256,000 as long
+// as before and 400,000 beads of a melt 123 instead of 112; the compact halo that it
+// leaves to the force kernel is what the large systems gain from.
 template <int HALO, bool GL>
 __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
-  // staged positions: floats relative to the tile's first particle, image
-  // added (8 spare entries: a batch may read up to 7 past the halo)
-  __shared__ float hx[HALO + 8], hy[HALO + 8], hz[HALO + 8];
-  __shared__ Pieces pc;
-  // The staging table (one entry per piece: LDS offset, first slot, image
-  // code; read only while the halo is staged) and the per-thread ring of list
-  // entries (LDS indices of the halo layout, left as whole blocks; used only
-  // by the scan after the staging barrier) share their LDS.
-  union StageRing {
-    struct {
-      int off[kMaxRows * 9 * kPieces + 1];
-      int start[kMaxRows * 9 * kPieces];
-      int code[kMaxRows * 9 * kPieces];
-    } st;
-    uint16_t ring[GL ? 1 : 2 * kTile][16];
+  constexpr int TH = kSearchThreads, NW = TH / 64;
+  static_assert(NW * 16 == kTile && TH == kCells, "one cluster per wave, one table entry per thread");
+  constexpr int kLook = 6, kSeen = kLook * TH;  // positions a thread, a tile looks at
+  static_assert(kLook * NW <= 64 && kSeen <= 0xffff, "one lane per (round, wave); 16-bit offsets");
+  constexpr int kCut = 1 << 30;
+  const int T = d.tile;  // (of small tiles the first waves take the clusters)
+  constexpr int RS = 13;            // words per lane of the ring: 26 LDS indices, odd stride (banks)
+  constexpr int PAD = GL ? 4 : 8;  // list padding (entries per 16-byte block)
+  // x, y, z, |x|^2 (spare entries: a round may read up to 31 past the halo; the
+  // stride keeps the four components on different banks)
+  __shared__ float hc[4][HALO + 48];
+  static_assert((HALO + 48) % 64 == 48, "components 16 banks apart");
+  constexpr int kPad = HALO + 40;  // a candidate that no particle accepts (r^2 = 1e30)
+  __shared__ uint32_t hent[GL ? HALO + 1 : 1];  // global-list entry of every staged position, sentinel last
+  __shared__ int coff[kCells + 1];       // LDS offset of every cell of the halo
+  __shared__ uint32_t cent[kCells];      // its first slot and image (og_entry)
+  __shared__ __align__(16) uint16_t cand[NW][kCand];  // the candidates a wave has kept
+  union Ring {
+    uint32_t w[NW][64 * RS];
+    uint16_t map[kSeen];  // staging: table entry of each position looked at, then the kept ones before it
   };
-  __shared__ __align__(16) StageRing sr;
-  auto& lbuf = sr.ring;
-  // with GL: the ring of list entries (slot and image code) of lists of
-  // global slots, and the entry of every staged position (the lists need no
-  // halo tables in global memory then)
-  __shared__ __align__(16) uint32_t gslot[GL ? 2 * kTile : 1][kOtherBatch];
-  __shared__ uint32_t hent[GL ? HALO + 8 : 1];
+  __shared__ __align__(16) Ring ring;
+  __shared__ Seg sgs[2];
+  __shared__ Box wbox[NW][2], tbox[2];
+  __shared__ int wkept[64], kept_sh;
+  __shared__ int wsum[NW], wmax[NW], tot_sh, nseg_sh, nent_sh;
   Ctrl* c = d.ctrl;
-  if (rebuild_off(d)) return;  // (the same two words for every wave)
-  const int np = d.np, np2 = d.np2, K = d.K, n = d.n;
-  const int s0 = tile * kTile;
-  const int half = (int)(threadIdx.x / kTile);
-  const int tl = (int)threadIdx.x - half * kTile;
-  const int i = s0 + tl;
-  const int v = half * np + i;  // this thread's sub-list
-  const bool valid = i < n;
+  const int np = d.np, n = d.n, cap = d.cap;
+  const int s0 = tile * T;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int pn = c->pos_cur, an = c->aux_cur;  // sorted buffers of the new state
   const double4* P = reinterpret_cast<const double4*>(d.pos[pn]);
   const double Delta = c->Delta;
   const double rmarg = d.rlist * (1.0 + 1e-12) + 1e-12 * (d.Lx + d.Ly + d.Lz);
 
-  // ---- tile geometry (every thread: the cells of the tile's first and last
-  // particle, read through the scalar cache)
-  const int c_first = cell_of_pos(d, P[s0]), c_last = cell_of_pos(d, P[min(s0 + kTile, n) - 1]);
-  const int row_first = c_first / d.nx, nrows = c_last / d.nx - row_first + 1;
-  const bool staged_ok = nrows <= kMaxRows;
-  if (threadIdx.x == 0) {
-    pc.nseg = 0;  // (no piece staged unless the first fits)
-    pc.ntot = 0;
-  }
-  // ---- pieces: one thread per (covered row, dz, dy)
-  const int ncombo = staged_ok ? nrows * 9 : 0;
-  for (int t = threadIdx.x; t < ncombo; t += blockDim.x) {
-    int r = t / 9, rem = t % 9;
-    int dzc = rem / 3 - 1, dyc = rem % 3 - 1;
-    int row = row_first + r;
-    int iy = row % d.ny, iz = row / d.ny;
-    int xa = (r == 0) ? c_first % d.nx : 0;
-    int xb = (r == nrows - 1) ? c_last % d.nx : d.nx - 1;
-    int jz = iz + dzc, sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
-    jz -= sz * d.nz;
-    int jy = iy + dyc, sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0);
-    jy -= sy * d.ny;
-    int klo, khi;
-    x_range(d, xa, xb, sy, Delta, rmarg, klo, khi);
-    int sxa = floor_div(klo, d.nx), sxb = floor_div(khi, d.nx);
-    int npc = sxb - sxa + 1;
-    pc.sx0[t] = sxa;
-    pc.code[t] = (sy + 1) | ((sz + 1) << 2);
-    pc.npc[t] = npc <= kPieces ? npc : 0;  // 0: not staged (too many images)
-    const int rowbase = (jz * d.ny + jy) * d.nx;
-    for (int q = 0; q < kPieces; ++q) {
-      pc.start[t][q] = 0;
-      pc.count[t][q] = 0;
-      if (q < pc.npc[t]) {
-        int sx = sxa + q;
-        int ka = max(klo, sx * d.nx), kb = min(khi, sx * d.nx + d.nx - 1);
-        int c0 = rowbase + (ka - sx * d.nx), c1 = rowbase + (kb - sx * d.nx);
-        pc.start[t][q] = d.cell_start[c0];
-        pc.count[t][q] = d.cell_start[c1 + 1] - d.cell_start[c0];
+  // ---- segments, from the tile's first and last particle (thread g: segment g)
+  const int send = min(s0 + T, n) - 1;
+  if (threadIdx.x < 64) {
+    const int g = threadIdx.x & 1;
+    const double4 p0 = P[g == 0 ? s0 : send], pm = P[(s0 + send) >> 1];
+    Seg s;
+    const int cx = cell_index(p0.x, d.inv_lx, d.nx), cy = cell_index(p0.y, d.inv_ly, d.ny),
+              cz = cell_index(p0.z, d.inv_lz, d.nz);
+    const int nby = (d.ny + (1 << d.by_sh) - 1) >> d.by_sh;
+    const int beam = (cz >> d.bz_sh) * nby + (cy >> d.by_sh);
+    const int other = __shfl_xor(beam, 1, 64), ox = __shfl_xor(cx, 1, 64);
+    const int step = g == 0 ? other - beam : beam - other;  // beams from the first to the last particle
+    const int ns = step == 0 ? 1 : (step == 1 ? 2 : 0);     // 0: more than two, nothing is staged
+    s.y0 = cy >> d.by_sh << d.by_sh;
+    s.z0 = cz >> d.bz_sh << d.bz_sh;
+    s.h = min(1 << d.by_sh, d.ny - s.y0);
+    s.w = min(1 << d.bz_sh, d.nz - s.z0);
+    s.xa = g == 0 ? cx : 0;
+    s.xb = ns == 1 ? ox : (g == 0 ? d.nx - 1 : cx);
+    s.nk = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      // rows across a gradient face only where the beam touches it
+      const bool used = k == 1 || (k == 0 ? s.y0 == 0 : s.y0 + s.h == d.ny);
+      s.klo[k] = s.khi[k] = 0;
+      if (used) {
+        x_range(d, s.xa, s.xb, k - 1, Delta, rmarg, s.klo[k], s.khi[k]);
+        s.nk = max(s.nk, s.khi[k] - s.klo[k] + 1);
       }
+    }
+    // origin of the floats: the middle of the tile (the smallest coordinates), or an end
+    s.ox = ns == 1 ? pm.x : p0.x; s.oy = ns == 1 ? pm.y : p0.y; s.oz = ns == 1 ? pm.z : p0.z;
+    const int cells = (s.h + 2) * (s.w + 2) * s.nk, first = __shfl(cells, 0, 64);
+    s.tb = g == 0 ? 0 : first;
+    if (threadIdx.x < 2) sgs[threadIdx.x] = s;
+    if (threadIdx.x == 1) {
+      nseg_sh = ns;
+      nent_sh = ns == 0 ? 0 : min(ns == 1 ? first : first + cells, kCells);
     }
   }
   __syncthreads();
-  // ---- LDS offsets in a fixed order (prefix sum over the pieces); pieces that
-  // do not fit stay global.  One piece per thread of the first kWaves waves.
-  {
-    static_assert(kMaxRows * 9 * kPieces <= kTile, "one piece per thread of the first kTile");
-    __shared__ int wsum[kWaves];
-    const int npieces = ncombo * kPieces;
-    const int e = (int)threadIdx.x;
-    const bool pe = e < npieces;
-    const int t = pe ? e / kPieces : 0, q = e % kPieces;
-    const bool real = pe && q < pc.npc[t];
-    const int cnt = real ? pc.count[t][q] : 0;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    int incl = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int u = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += u;
-    }
-    if (lane == 63 && wv < kWaves) wsum[wv] = incl;
-    __syncthreads();
-    for (int w2 = 0; w2 < kWaves; ++w2)
-      if (w2 < wv) incl += wsum[w2];
-    // a piece is staged iff it ends within the halo; the staged set is a
-    // prefix of the pieces (the running offsets only grow).  The staging
-    // table is that prefix, one entry per piece in order (empty ones too:
-    // the search below skips them), written by the piece's own thread; the
-    // last piece that fits records the prefix's length and size.
-    if (pe) {
-      const int start_off = incl - cnt;
-      const bool fits = incl <= HALO;
-      pc.off[t][q] = (real && fits) ? start_off : -1;
-      sr.st.off[e] = start_off;
-      sr.st.start[e] = real ? pc.start[t][q] : 0;
-      sr.st.code[e] = real ? pack_img(pc.sx0[t] + q, (pc.code[t] & 3) - 1, (pc.code[t] >> 2) - 1) : 0;
-      bool next_fits = false;
-      if (e + 1 < npieces) {
-        const int t1 = (e + 1) / kPieces, q1 = (e + 1) % kPieces;
-        next_fits = incl + (q1 < pc.npc[t1] ? pc.count[t1][q1] : 0) <= HALO;
-      }
-      if (fits && !next_fits) {
-        pc.nseg = e + 1;
-        pc.ntot = incl;
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) d.tile_nstage[tile] = pc.ntot;
-  }
-  // ---- stage positions and record their slots (flat, kStageLoads loads in
-  // flight per thread: the search halo in one round)
-  const double4 org = P[s0];
-  {
-    const int tot = pc.ntot, nseg = pc.nseg;
-    constexpr int kStageLoads = 6;
-    for (int h0 = threadIdx.x; h0 < tot; h0 += kStageLoads * blockDim.x) {
-      int slot[kStageLoads], code[kStageLoads];
-#pragma unroll
-      for (int u = 0; u < kStageLoads; ++u) {
-        int h = h0 + u * blockDim.x;
-        slot[u] = n;
-        code[u] = 0;
-        if (h < tot) {
-          int lo = 0, hi = nseg - 1;  // last segment with s_off <= h
-          while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (sr.st.off[mid] <= h) lo = mid; else hi = mid - 1;
-          }
-          slot[u] = sr.st.start[lo] + (h - sr.st.off[lo]);
-          code[u] = sr.st.code[lo];
-        }
-      }
-      double4 pj[kStageLoads];
-#pragma unroll
-      for (int u = 0; u < kStageLoads; ++u) pj[u] = P[slot[u]];
-#pragma unroll
-      for (int u = 0; u < kStageLoads; ++u) {
-        const int h = h0 + u * blockDim.x;
-        // written unconditionally (past the halo: a spare entry) so that the
-        // loads above are not sunk into the condition one by one
-        const int hw = h < tot ? h : HALO + 7;
-        int sx, sy, sz;
-        unpack_img((uint8_t)code[u], sx, sy, sz);
-        hx[hw] = (float)((pj[u].x + ((double)sy * Delta + (double)sx * d.Lx)) - org.x);
-        hy[hw] = (float)((pj[u].y + (double)sy * d.Ly) - org.y);
-        hz[hw] = (float)((pj[u].z + (double)sz * d.Lz) - org.z);
-        if constexpr (GL) {
-          hent[hw] = og_entry((uint32_t)slot[u], (uint8_t)code[u]);
-        } else if (h < tot) {
-          d.halo_slot[(size_t)tile * kHalo + h] = slot[u];
-          d.halo_code[(size_t)tile * kHalo + h] = (uint8_t)code[u];
-        }
-      }
-    }
-  }
+  const int nseg = nseg_sh, nent = nent_sh, tb1 = sgs[1].tb;
 
-  __syncthreads();
-
-  // ---- scan: each lane walks its own stencil.  For each (dy, dz) the x-cells
-  // the particle reaches in that row form one contiguous LDS range (the row's
-  // x-image pieces are staged back to back, images already added), so a lane
-  // tests [a, b) with eight candidates per batch, the particle's two threads
-  // taking alternate batches (each sub-list then holds partners from all
-  // over the row: fewer padding entries and gathers spread alike); the wave
-  // runs to its longest range.  Lanes whose row was not staged walk the cells
-  // in global memory with the exact test instead.
+  // ---- the wave's particles (the same 16 in each row of 16 lanes), and the
+  // bounding box of the tile's particles of each segment
+  const int p16 = lane & 15, q = lane >> 4;
+  const int i = s0 + wv * 16 + p16;
+  const bool valid = wv * 16 < T && i < n;
   const double4 pi = P[valid ? i : s0];
-  const float pix = (float)(pi.x - org.x), piy = (float)(pi.y - org.y), piz = (float)(pi.z - org.z);
   const int ix = cell_index(pi.x, d.inv_lx, d.nx);
   const int iy = cell_index(pi.y, d.inv_ly, d.ny);
   const int iz = cell_index(pi.z, d.inv_lz, d.nz);
-  const int rt = (iz * d.ny + iy) - row_first;  // tile row of the particle
-  const bool row_staged = valid && staged_ok && rt >= 0 && rt < nrows;
-  int self_h = -1;  // LDS position of the particle itself (plain image)
-  if (row_staged) {
-    const int t = rt * 9 + 4;  // dz = dy = 0
-    const int q = -pc.sx0[t];  // sx = 0
-    if (q >= 0 && q < pc.npc[t] && pc.off[t][q] >= 0) self_h = i - pc.start[t][q] + pc.off[t][q];
+  const int gi = nseg == 2 && !(iy >= sgs[0].y0 && iy < sgs[0].y0 + sgs[0].h && iz >= sgs[0].z0 &&
+                                iz < sgs[0].z0 + sgs[0].w) ? 1 : 0;
+  const float fx = (float)(pi.x - sgs[gi].ox), fy = (float)(pi.y - sgs[gi].oy), fz = (float)(pi.z - sgs[gi].oz);
+  for (int g = 0; g < nseg; ++g) {
+    const bool in = valid && gi == g;
+    const Box b = {{row16_min(in ? fx : 1e30f), row16_min(in ? fy : 1e30f), row16_min(in ? fz : 1e30f),
+                    row16_min(in ? -fx : 1e30f), row16_min(in ? -fy : 1e30f), row16_min(in ? -fz : 1e30f)}, 0.0f};
+    if (lane == 0) wbox[wv][g] = b;
   }
-  const float tlo = d.nb_lo, thi = d.nb_hi;
-  const size_t hbase = (size_t)tile * kHalo;
-  int npl = 0, nog = 0;
-  // one global-list entry (og_entry: slot and image code in one word): with
-  // GL into the lane's ring, a completed block of four leaving as one 16-byte
-  // store; otherwise (rows beyond the halo of a halo-layout list) straight to
-  // global memory
-  auto og_append = [&](uint32_t e) {
-    if constexpr (GL) {
-      gslot[threadIdx.x][nog & 3] = e;
-      ++nog;
-      if ((nog & 3) == 0 && nog <= K) {
-        const size_t b = (size_t)((nog >> 2) - 1) * np2 + v;
-        reinterpret_cast<uint4*>(d.nlo)[b] = *reinterpret_cast<const uint4*>(gslot[threadIdx.x]);
-      }
-    } else {
-      if (nog < K) d.nlo[idx4(nog, v, np2)] = e;
-      ++nog;
-    }
-  };
-  for (int c9 = 0; c9 < 9; ++c9) {
-    const int dzc = c9 / 3 - 1, dyc = c9 % 3 - 1;
-    int jz = iz + dzc, sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
-    jz -= sz * d.nz;
-    int jy = iy + dyc, sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0);
-    jy -= sy * d.ny;
-    int klo, khi;
-    x_range(d, ix, ix, sy, Delta, rmarg, klo, khi);
-    const int rowbase = (jz * d.ny + jy) * d.nx;
-    int a = 0, b = 0;
-    bool walk_global = valid;
-    if (row_staged) {
-      const int t = rt * 9 + c9;
-      const int sxa = floor_div(klo, d.nx), sxb = floor_div(khi, d.nx);
-      const int qa = sxa - pc.sx0[t], qb = sxb - pc.sx0[t];
-      // staged pieces form a prefix, so the last one staged implies the rest
-      if (qa >= 0 && qb < pc.npc[t] && pc.off[t][qb] >= 0) {
-        a = d.cell_start[rowbase + (klo - sxa * d.nx)] + (pc.off[t][qa] - pc.start[t][qa]);
-        b = d.cell_start[rowbase + (khi - sxb * d.nx) + 1] + (pc.off[t][qb] - pc.start[t][qb]);
-        // the two threads of the particle take alternate batches of the range
-        a += 8 * half;
-        walk_global = false;
-      }
-    }
-    int wlen = b - a;
-    for (int o = 32; o > 0; o >>= 1) wlen = max(wlen, __shfl_xor(wlen, o, 64));
-    wlen = __builtin_amdgcn_readfirstlane(wlen);
-    const int sq = (c9 == 4) ? self_h : -1;
-    for (int j0 = 0; j0 < wlen; j0 += 16) {
-      const int h0 = a + j0;
-      // candidates past the lane's range are read (in bounds) and masked off
-      const int lim = b - h0;
-      unsigned keep = lim >= 8 ? 0xffu : (lim > 0 ? (1u << lim) - 1u : 0u);
-      if (sq >= h0 && sq < h0 + 8) keep &= ~(1u << (sq - h0));
-      const int hc = min(h0, HALO);
-      unsigned m_in = 0u, m_band = 0u;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float dx = pix - hx[hc + u];
-        const float dy = piy - hy[hc + u];
-        const float dz = piz - hz[hc + u];
-        const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-        m_in |= (r2 < tlo ? 1u : 0u) << u;
-        m_band |= (r2 < thi ? 1u : 0u) << u;
-      }
-      m_in &= keep;
-      m_band &= keep & ~m_in;
-      while (m_band) {  // rare: FP32 r^2 within the rounding band of r_list^2
-        const int u = __builtin_ctz(m_band);
-        m_band &= m_band - 1u;
-        const int h = h0 + u;
-        int q2;
-        uint8_t c2;
-        if constexpr (GL) {
-          q2 = (int)(hent[h] & kSlotMask);
-          c2 = (uint8_t)(hent[h] >> kSlotBits);
-        } else {
-          q2 = d.halo_slot[hbase + h];
-          c2 = d.halo_code[hbase + h];
-        }
-        int sx2, sy2, sz2;
-        unpack_img(c2, sx2, sy2, sz2);
-        if (in_list_exact(d, pi, P[q2], (double)sx2 * d.Lx, (double)sy2 * d.Ly, (double)sz2 * d.Lz,
-                          (double)sy2 * Delta))
-          m_in |= 1u << u;
-      }
-      if constexpr (GL) {
-        // lists without a force-time halo: the partner's slot and image code
-        while (m_in) {
-          const int u = __builtin_ctz(m_in);
-          m_in &= m_in - 1u;
-          og_append(hent[h0 + u]);
-        }
-      } else {
-        // append the accepted LDS indices into a ring of 16 per lane: every
-        // candidate is written at the next free entry and the count advances
-        // only for accepted ones (a rejected one is overwritten by the next
-        // write); a completed block of 8 leaves as one 16-byte store
-        int nn = npl;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          lbuf[threadIdx.x][nn & 15] = (uint16_t)(h0 + u);
-          nn += (int)((m_in >> u) & 1u);
-        }
-        if ((nn >> 3) != (npl >> 3)) {
-          const int blk = npl >> 3;
-          if ((blk + 1) * 8 <= K)
-            reinterpret_cast<uint4*>(d.nl16)[(size_t)blk * np2 + v] =
-                *reinterpret_cast<const uint4*>(&lbuf[threadIdx.x][(blk & 1) * 8]);
-        }
-        npl = nn;
-      }
-    }
-    if (walk_global) {
-      // this particle's cells of the row, read from global memory; the two
-      // threads of the particle take the lower and the upper cells
-      const int kmid = klo + (khi - klo) / 2;
-      const int ka = half == 0 ? klo : kmid + 1, kb = half == 0 ? kmid : khi;
-      for (int k = ka; k <= kb; ++k) {
+
+  // ---- staging table: one cell per thread, then the cells' offsets
+  int all;
+  {
+    const int e = (int)threadIdx.x;
+    int st = 0, code = 0, cnt = 0;
+    if (e < nent) {
+      const Seg& s = sgs[nseg == 2 && e >= tb1 ? 1 : 0];
+      const int h2 = s.h + 2, el = e - s.tb;
+      const int row = el / s.nk, kk = el - row * s.nk;
+      const int rz = row / h2, ry = row - rz * h2;
+      int jy = s.y0 - 1 + ry, jz = s.z0 - 1 + rz;
+      const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
+      jy -= sy * d.ny;
+      jz -= sz * d.nz;
+      const int k = s.klo[sy + 1] + kk;
+      if (k <= s.khi[sy + 1]) {
         const int sx = floor_div(k, d.nx);
-        const int cell = rowbase + (k - sx * d.nx);
-        const bool plain = (sx == 0 && sy == 0 && sz == 0);
-        const uint8_t code = pack_img(sx, sy, sz);
-        for (int q = d.cell_start[cell]; q < d.cell_start[cell + 1]; ++q) {
-          if (plain && q == i) continue;
-          if (in_list_exact(d, pi, P[q], (double)sx * d.Lx, (double)sy * d.Ly, (double)sz * d.Lz,
-                            (double)sy * Delta)) {
-            og_append(og_entry((uint32_t)q, code));
+        const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
+        st = d.cell_start[cell];
+        cnt = d.cell_start[cell + 1] - st;
+        code = pack_img(sx, sy, sz);
+      }
+    }
+    cent[e] = og_entry((uint32_t)st, (uint8_t)code);
+    int incl = cnt;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) wsum[wv] = incl;
+    if (threadIdx.x == 0) tot_sh = 0;
+    __syncthreads();
+    int off = incl - cnt;
+    all = 0;
+    for (int w2 = 0; w2 < NW; ++w2) {
+      if (w2 < wv) off += wsum[w2];
+      all += wsum[w2];
+    }
+    coff[e] = off;
+    const bool fits = off + cnt <= kSeen;  // the cells looked at are a prefix of the table
+    if (fits)
+      for (int k = 0; k < cnt; ++k) ring.map[off + k] = (uint16_t)e;
+    if (fits && all > kSeen) atomicMax(&tot_sh, off + cnt);
+    if (threadIdx.x == 0 && all <= kSeen) tot_sh = all;
+    if (threadIdx.x == TH - 1) coff[kCells] = off + cnt;
+    if (threadIdx.x < 2 && (int)threadIdx.x < nseg) {  // the tile's boxes: minimum over the waves
+      Box b = wbox[0][threadIdx.x];
+      for (int w2 = 1; w2 < NW; ++w2)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) b.v[k] = fminf(b.v[k], wbox[w2][threadIdx.x].v[k]);
+      b.reach2 = reach2_of(b, d.rlist_f);
+      tbox[threadIdx.x] = b;
+    }
+  }
+  __syncthreads();
+  const int seen = tot_sh;
+  // ---- stage the positions within reach of the segment's box: LDS position =
+  // the number of kept ones before it, in the order of the table
+  {
+    int slot[kLook], code[kLook];
+    float x[kLook], y[kLook], z[kLook];
+    unsigned long long kept[kLook];
+#pragma unroll
+    for (int u0 = 0; u0 < kLook; u0 += 2) {  // two loads in flight per thread, while there are positions
+#pragma unroll
+      for (int u = u0; u < u0 + 2; ++u) kept[u] = 0ull;
+      if (u0 * TH >= seen) continue;
+      double4 pj[2];
+      int sgi[2];
+#pragma unroll
+      for (int u = u0; u < u0 + 2; ++u) {
+        const int h = (int)threadIdx.x + u * TH;
+        slot[u] = n;
+        code[u] = pack_img(0, 0, 0);
+        sgi[u - u0] = 0;
+        if (h < seen) {
+          const int e = ring.map[h];
+          slot[u] = (int)(cent[e] & kSlotMask) + (h - coff[e]);
+          code[u] = (int)(cent[e] >> kSlotBits);
+          sgi[u - u0] = nseg == 2 && e >= tb1 ? 1 : 0;
+        }
+        pj[u - u0] = P[slot[u]];
+      }
+#pragma unroll
+      for (int u = u0; u < u0 + 2; ++u) {
+        const Seg& s = sgs[sgi[u - u0]];
+        const double4 p = pj[u - u0];
+        int sx, sy, sz;
+        unpack_img((uint8_t)code[u], sx, sy, sz);
+        x[u] = (float)((p.x + ((double)sy * Delta + (double)sx * d.Lx)) - s.ox);
+        y[u] = (float)((p.y + (double)sy * d.Ly) - s.oy);
+        z[u] = (float)((p.z + (double)sz * d.Lz) - s.oz);
+        const bool keep = (int)threadIdx.x + u * TH < seen && in_reach(tbox[sgi[u - u0]], x[u], y[u], z[u]);
+        kept[u] = __ballot(keep);
+        if (lane == 0) wkept[u * NW + wv] = __popcll(kept[u]);
+      }
+    }
+    __syncthreads();
+    // kept positions before each (round, wave)
+    const int v = lane < (seen + TH - 1) / TH * NW ? wkept[lane] : 0;
+    int before = v;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(before, o, 64);
+      if (lane >= o) before += t;
+    }
+    if (threadIdx.x == 63) kept_sh = before;
+    before -= v;
+#pragma unroll
+    for (int u = 0; u < kLook; ++u) {
+      if (u * TH >= seen) break;
+      const int h = (int)threadIdx.x + u * TH;
+      const int pos = __builtin_amdgcn_readlane(before, u * NW + wv) + __popcll(kept[u] & ((1ull << lane) - 1ull));
+      if (h < seen) ring.map[h] = (uint16_t)pos;
+      if (!((kept[u] >> lane) & 1ull) || pos >= HALO) continue;
+      hc[0][pos] = x[u];
+      hc[1][pos] = y[u];
+      hc[2][pos] = z[u];
+      hc[3][pos] = (float)((double)x[u] * (double)x[u] + (double)y[u] * (double)y[u] + (double)z[u] * (double)z[u]);
+      const uint32_t e = og_entry((uint32_t)slot[u], (uint8_t)code[u]);
+      if constexpr (GL) hent[pos] = e;
+      else d.halo[(size_t)tile * HALO + pos] = e;
+    }
+  }
+  if (threadIdx.x < 4) hc[threadIdx.x][kPad] = threadIdx.x == 3 ? 1e30f : 0.0f;
+  if (GL && threadIdx.x == 0) hent[HALO] = og_entry((uint32_t)n, pack_img(0, 0, 0));
+  __syncthreads();
+  const int kept_all = kept_sh;
+  if (threadIdx.x == 0) d.tile_nstage[tile] = min(kept_all, HALO);
+  // the particle's own LDS position (its plain image), and the cells' offsets
+  // among the kept positions (kCut: beyond what was looked at)
+  int self_h = -1;
+  if (valid && nseg > 0) {
+    const Seg& s = sgs[gi];
+    const int e = s.tb + ((iz - s.z0 + 1) * (s.h + 2) + (iy - s.y0 + 1)) * s.nk + (ix - s.xa + 1);
+    const int h = e < nent ? coff[e] + (i - (int)(cent[e] & kSlotMask)) : seen;
+    if (h < seen) self_h = ring.map[h];
+  }
+  {
+    const int e = (int)threadIdx.x;
+    const int o0 = coff[e], o1 = coff[kCells];
+    const int n0 = o0 < seen ? ring.map[o0] : (o0 == seen ? kept_all : kCut);
+    const int n1 = o1 == seen ? kept_all : kCut;
+    __syncthreads();
+    coff[e] = n0;
+    if (e == 0) coff[kCells] = n1;
+  }
+  __syncthreads();
+
+  // ---- scan
+  uint32_t* const rw = ring.w[wv] + (p16 * 4 + q) * RS;  // the four lanes of a particle are neighbours
+  uint16_t* const r16 = reinterpret_cast<uint16_t*>(rw);
+  int cnt = 0;   // entries in this lane's ring
+  int nblk = 0;  // blocks of eight written for the particle (the same in its four lanes)
+  int nog = 0;   // entries of rows that were not staged (the same in the four lanes)
+  uint32_t walked = 0;
+  auto og_store = [&](int k, uint32_t e) {
+    if (k < cap) reinterpret_cast<uint32_t*>(d.nl + unit_back(d, k >> 2, i))[k & 3] = e;
+  };
+  // full blocks leave the rings, lanes of a particle in order of q (called by the whole wave)
+  auto flush = [&]() {
+    const unsigned long long full = __ballot(cnt >= 8);
+    const unsigned long long mine = (full >> p16) & 0x0001000100010001ull;
+    if (cnt >= 8) {
+      const int blk = nblk + __popcll(mine & ((1ull << (16 * q)) - 1ull));
+      uint32_t t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) t[k] = rw[k];
+      if ((blk + 1) * 8 <= cap) {
+        if constexpr (GL) {
+          d.nl[unit_front(d, 2 * blk, i)] = make_uint4(hent[t[0] & 0xffff], hent[t[0] >> 16], hent[t[1] & 0xffff],
+                                                          hent[t[1] >> 16]);
+          d.nl[unit_front(d, 2 * blk + 1, i)] = make_uint4(hent[t[2] & 0xffff], hent[t[2] >> 16],
+                                                              hent[t[3] & 0xffff], hent[t[3] >> 16]);
+        } else {
+          d.nl[unit_front(d, blk, i)] = make_uint4(t[0], t[1], t[2], t[3]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) rw[k] = rw[k + 4];
+      cnt -= 8;
+    }
+    nblk += __popcll(mine);
+  };
+  const size_t hbase = (size_t)tile * HALO;
+  auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  for (int g = 0; g < (nseg == 0 ? 1 : nseg); ++g) {
+    const Seg& s = sgs[g];
+    const int y0 = uni(s.y0), z0 = uni(s.z0), h2 = uni(s.h) + 2, nk = uni(s.nk), stb = uni(s.tb);
+    const bool low = y0 == 0, high = y0 + h2 - 2 == d.ny;  // the beam touches a gradient face
+    const bool in_seg = valid && gi == g;
+    const unsigned long long lanes = __ballot(in_seg);
+    if (!lanes) continue;
+    // bounding box of the cluster's cells: x from its first and last particle
+    // (sorted along the beam), rows of y and z from their masks
+    const int first = __builtin_ctzll(lanes), last = 15 - __builtin_clz((unsigned)(lanes & 0xffffull) << 16);
+    const int xlo = __builtin_amdgcn_readlane(ix, first), xhi = __builtin_amdgcn_readlane(ix, last);
+    int ym = 0;
+    if (nseg > 0) {
+      ym = in_seg ? (1 << (iy - y0)) | (1 << (16 + iz - z0)) : 0;
+      for (int o = 8; o > 0; o >>= 1) ym |= __shfl_xor(ym, o, 64);
+      ym = __builtin_amdgcn_readfirstlane(ym);
+    }
+    const int ylo = __builtin_ctz((ym & 0xffff) | 0x10000), yhi = 31 - __builtin_clz((ym & 0xffff) | 1);
+    const int zlo = __builtin_ctz(((unsigned)ym >> 16) | 0x10000), zhi = 31 - __builtin_clz(((unsigned)ym >> 16) | 1);
+    // cells along x of the cluster's rows, by image sy
+    int ka[3], kb[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      ka[k] = kb[k] = 0;
+      if (k == 1 || (k == 0 ? low : high)) x_range(d, xlo, xhi, k - 1, Delta, rmarg, ka[k], kb[k]);
+    }
+    // matrix operands and thresholds of the lane's particle
+    const float si = (float)((double)fx * (double)fx + (double)fy * (double)fy + (double)fz * (double)fz);
+    const float bv = q == 0 ? -2.0f * fx : (q == 1 ? -2.0f * fy : (q == 2 ? -2.0f * fz : 1.0f));
+    const float c0 = in_seg ? si : 1e30f;
+    const f32x4 cv = {c0, c0, c0, c0};
+    const float R = __builtin_sqrtf(si) + d.rlist_f;
+    const float margin = d.nb_rel * R * R;
+    const float tlo = d.nb_lo - margin, thi = d.nb_hi + margin;
+    // bounding box of the cluster's particles, and the distance from it beyond
+    // which a candidate is out of every particle's reach (rounding included)
+    Box box = {{row16_min(in_seg ? fx : 1e30f), row16_min(in_seg ? fy : 1e30f), row16_min(in_seg ? fz : 1e30f),
+                      row16_min(in_seg ? -fx : 1e30f), row16_min(in_seg ? -fy : 1e30f),
+                      row16_min(in_seg ? -fz : 1e30f)}, 0.0f};
+    box.reach2 = reach2_of(box, d.rlist_f);
+    // the first `count` kept candidates against the cluster's particles, 32 a
+    // round (the particles themselves are among the first `own`)
+    auto test = [&](int count, int own) {
+      if (lane < 32) cand[wv][count + lane] = (uint16_t)kPad;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      for (int c0 = 0; c0 < count; c0 += 32) {
+        const int j0 = cand[wv][c0 + p16], j1 = cand[wv][c0 + 16 + p16];
+        const uint2 e0 = *reinterpret_cast<const uint2*>(&cand[wv][c0 + 4 * q]);
+        const uint2 e1 = *reinterpret_cast<const uint2*>(&cand[wv][c0 + 16 + 4 * q]);
+        const uint16_t hv[8] = {(uint16_t)e0.x, (uint16_t)(e0.x >> 16), (uint16_t)e0.y, (uint16_t)(e0.y >> 16),
+                                (uint16_t)e1.x, (uint16_t)(e1.x >> 16), (uint16_t)e1.y, (uint16_t)(e1.y >> 16)};
+        const f32x4 w0 = __builtin_amdgcn_mfma_f32_16x16x4f32(hc[q][j0], bv, cv, 0, 0, 0);
+        const f32x4 w1 = __builtin_amdgcn_mfma_f32_16x16x4f32(hc[q][j1], bv, cv, 0, 0, 0);
+        float rr[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
+        if (c0 < own) {
+#pragma unroll
+          for (int v = 0; v < 8; ++v)
+            if (hv[v] == self_h) rr[v] = 1e30f;
+        }
+        // every candidate is written at the ring's next entry, and the count
+        // moves on only past the accepted ones
+        unsigned long long band = 0;
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+          r16[cnt] = hv[v];
+          const bool in = rr[v] < tlo;
+          cnt += in ? 1 : 0;
+          band |= __ballot(in) ^ __ballot(rr[v] < thi);
+        }
+        if (band) {  // rare: the FP64 displacement decides
+          unsigned todo = 0;
+#pragma unroll
+          for (int v = 0; v < 8; ++v) todo |= (rr[v] >= tlo && rr[v] < thi ? 1u : 0u) << v;
+          while (todo) {
+            const int v = __builtin_ctz(todo);
+            todo &= todo - 1u;
+            const int h = cand[wv][c0 + 16 * (v >> 2) + 4 * q + (v & 3)];
+            uint32_t e;
+            if constexpr (GL) e = hent[h];
+            else e = d.halo[hbase + h];
+            int sx2, sy2, sz2;
+            unpack_img((uint8_t)(e >> kSlotBits), sx2, sy2, sz2);
+            if (in_list_exact(d, pi, P[e & kSlotMask], (double)sx2 * d.Lx, (double)sy2 * d.Ly,
+                              (double)sz2 * d.Lz, (double)sy2 * Delta)) {
+              r16[cnt] = (uint16_t)h;
+              ++cnt;
+            }
+          }
+        }
+        // (two rounds fill the ring: 7 + 16 of its 26 entries)
+        if ((c0 & 32) || c0 + 32 >= count)
+          while (__any(cnt >= 8)) flush();
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    // rows of the box: lane r finds the LDS range of row r (and whether it was
+    // staged)
+    const int ry0 = nseg > 0 ? ylo : 0, nry = nseg > 0 ? yhi - ylo + 3 : 3;
+    const int rz0 = nseg > 0 ? zlo : 0, nrz = nseg > 0 ? zhi - zlo + 3 : 3;
+    const int nrow = nry * nrz;
+    for (int r0 = 0; r0 < nrow; r0 += 64) {
+      int row_a = 0, row_b = 0, row_ry = 0, row_rz = 0;
+      bool row_staged = false;
+      if (r0 + lane < nrow) {
+        row_rz = (r0 + lane) / nry;
+        row_ry = ry0 + (r0 + lane) - row_rz * nry;
+        row_rz += rz0;
+        if (nseg > 0) {
+          const int jy0 = y0 - 1 + row_ry;
+          const int syu = jy0 < 0 ? -1 : (jy0 >= d.ny ? 1 : 0);
+          const int rb = stb + (row_rz * h2 + row_ry) * nk;
+          const int lo = s.klo[syu + 1];
+          const int k0 = syu == 0 ? ka[1] : (syu < 0 ? ka[0] : ka[2]);
+          const int k1 = syu == 0 ? kb[1] : (syu < 0 ? kb[0] : kb[2]);
+          row_staged = rb + nk <= nent && coff[min(rb + nk, kCells)] <= HALO;
+          if (row_staged) {
+            row_a = coff[rb + (k0 - lo)];
+            row_b = coff[rb + (k1 - lo) + 1];
           }
         }
       }
-    }
-  }
-  {
-    // the second sub-list's last, partial block (still in its thread's ring)
-    // moves to the end of the first: the two sub-lists then carry one padding
-    // instead of two (the force kernels read them as one sequence).  Entries
-    // of the halo layout's rows beyond the halo went straight to global
-    // memory and stay where they are.
-    // entries of the partial block | its ring half << 8, where the staged y
-    // coordinates were (every wave has left the scan after this barrier)
-    int* tail = reinterpret_cast<int*>(hy);
-    __syncthreads();
-    if (half == 1)
-      tail[tl] = GL ? (nog & (kOtherBatch - 1)) : ((npl & (kPlainBatch - 1)) | (((npl >> 3) & 1) << 8));
-    __syncthreads();
-    const int r = tail[tl] & 0xff;
-    const int pt = (int)threadIdx.x + kTile;  // the particle's second thread
-    if (half == 0) {
-      if constexpr (GL) {
-        for (int k = 0; k < r; ++k) og_append(gslot[pt][k]);
-      } else {
-        const int src = (tail[tl] >> 8) * 8;
-        for (int k = 0; k < r; ++k) {
-          lbuf[threadIdx.x][npl & 15] = lbuf[pt][src + k];
-          ++npl;
-          const int blk = (npl >> 3) - 1;  // completed by this entry
-          if ((npl & 7) == 0 && (blk + 1) * 8 <= K)
-            reinterpret_cast<uint4*>(d.nl16)[(size_t)blk * np2 + v] =
-                *reinterpret_cast<const uint4*>(&lbuf[threadIdx.x][(blk & 1) * 8]);
+      const bool row_self = row_ry > ylo && row_ry < yhi + 2 && row_rz > zlo && row_rz < zhi + 2;
+      // Candidates of the staged rows within reach of the bounding box, four
+      // rows at a time (one per 16 lanes), the particles' own rows first; then
+      // the kept ones against the particles.
+      int nc = 0, nself = 0;  // kept candidates; of which may hold the particles themselves
+      for (int pass = 0; pass < 2; ++pass) {
+        unsigned long long rows = __ballot(row_staged && row_self == (pass == 0) && row_a < row_b);
+        while (rows) {
+          int rsel = -1;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (rows) {
+              const int r = __builtin_ctzll(rows);
+              rows &= rows - 1ull;
+              if (q == k) rsel = r;
+            }
+          }
+          // (both shuffles by the whole wave: a lane without a row still serves its own)
+          const int ra = __shfl(row_a, rsel & 63, 64), rb = __shfl(row_b, rsel & 63, 64);
+          int h = ra + p16;
+          const int hb = rsel >= 0 ? rb : 0;
+          while (__any(h < hb)) {
+            const int hh = min(h, HALO);
+            const bool keep = h < hb && in_reach(box, hc[0][hh], hc[1][hh], hc[2][hh]);
+            const unsigned long long m = __ballot(keep);
+            if (keep) cand[wv][nc + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0))] = (uint16_t)h;
+            nc += __popcll(m);
+            h += 16;
+            if (nc > kCand - 96) {  // (room for another 64 and the padding)
+              test(nc, pass == 0 ? nc : nself);
+              nc = nself = 0;
+            }
+          }
+        }
+        if (pass == 0) nself = nc;
+      }
+      test(nc, nself);
+      unsigned long long walk = __ballot(r0 + lane < nrow && !row_staged);
+      while (walk) {
+        // a row that was not staged: the four lanes of each particle walk the
+        // cells of its own stencil in global memory with the exact test
+        const int r = __builtin_ctzll(walk);
+        walk &= walk - 1ull;
+        const int ry = __builtin_amdgcn_readlane(row_ry, r), rz = __builtin_amdgcn_readlane(row_rz, r);
+        const int dyc = nseg > 0 ? y0 - 1 + ry - iy : ry - 1, dzc = nseg > 0 ? z0 - 1 + rz - iz : rz - 1;
+        bool more = in_seg && dyc >= -1 && dyc <= 1 && dzc >= -1 && dzc <= 1;
+        int jy = iy + dyc, jz = iz + dzc;
+        const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
+        jy -= sy * d.ny;
+        jz -= sz * d.nz;
+        int k = 0, khi = -1, slot = 0, end = 0, sx = 0;
+        if (more) x_range(d, ix, ix, sy, Delta, rmarg, k, khi);
+        while (__any(more)) {
+          bool in = false;
+          if (more && slot >= end) {
+            if (k > khi) {
+              more = false;
+            } else {
+              sx = floor_div(k, d.nx);
+              const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
+              slot = d.cell_start[cell] + q;
+              end = d.cell_start[cell + 1];
+              ++k;
+            }
+          } else if (more) {
+            in = !(slot == i && sx == 0 && sy == 0 && sz == 0) &&
+                 in_list_exact(d, pi, P[slot], (double)sx * d.Lx, (double)sy * d.Ly, (double)sz * d.Lz,
+                               (double)sy * Delta);
+            walked = og_entry((uint32_t)slot, pack_img(sx, sy, sz));
+            slot += 4;
+          }
+          const unsigned long long mine = (__ballot(in) >> p16) & 0x0001000100010001ull;
+          if (in) og_store(nog + __popcll(mine & ((1ull << (16 * q)) - 1ull)), walked);
+          nog += __popcll(mine);
         }
       }
-    } else {
-      if constexpr (GL) nog -= r; else npl -= r;
     }
   }
-  {  // telemetry (entries per particle, both sub-lists): one atomic per block
-    __shared__ int wmax[2 * kTile / 64];
-    // the counts of the second halves go where the staged x coordinates
-    // were: every wave has left the scan after this barrier
-    __syncthreads();
-    int* cnt1 = reinterpret_cast<int*>(hx);
-    if (half == 1) cnt1[tl] = npl + nog;
-    __syncthreads();
-    int mx = half == 0 ? npl + nog + cnt1[tl] : 0;
-    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
+  // ---- the four partial blocks of each particle are joined (the particle's
+  // rings are neighbours in LDS: their first 16-byte aligned stretch holds them)
+  const int r0 = __shfl(cnt, p16, 64), r1 = __shfl(cnt, p16 + 16, 64), r2 = __shfl(cnt, p16 + 32, 64),
+            r3 = __shfl(cnt, p16 + 48, 64);
+  const int below = (q > 0 ? r0 : 0) + (q > 1 ? r1 : 0) + (q > 2 ? r2 : 0);
+  const int rest = r0 + r1 + r2 + r3;
+  const int restp = (rest + PAD - 1) / PAD * PAD;
+  {
+    uint32_t t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = rw[k];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t* const tw = ring.w[wv] + p16 * 4 * RS;
+    uint16_t* const t16 = reinterpret_cast<uint16_t*>(tw);
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+      if (k < cnt) t16[below + k] = (uint16_t)(t[k >> 1] >> (16 * (k & 1)));
+    for (int k = rest + q; k < restp; k += 4) t16[k] = (uint16_t)HALO;  // (with GL: hent[HALO], slot n)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int b0 = nblk * (8 / PAD);  // blocks of PAD entries written so far
+    if (valid) {
+      for (int b = q; b * PAD < restp; b += 4) {
+        if ((b0 + b + 1) * PAD > cap) continue;
+        if constexpr (GL) {
+          const uint16_t* e = t16 + 4 * b;
+          d.nl[unit_front(d, b0 + b, i)] = make_uint4(hent[e[0]], hent[e[1]], hent[e[2]], hent[e[3]]);
+        } else {
+          d.nl[unit_front(d, b0 + b, i)] = *reinterpret_cast<const uint4*>(tw + 4 * b);
+        }
+      }
+    }
+  }
+  const int entries = nblk * 8 + rest;
+  {  // telemetry (entries per particle): one atomic per block
+    int mx = q == 0 && valid ? entries + nog : 0;
+    for (int o = 8; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) wmax[wv] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
-      for (int w = 1; w < 2 * kTile / 64; ++w) mx = max(mx, wmax[w]);
+      for (int w = 1; w < NW; ++w) mx = max(mx, wmax[w]);
       atomicMax(&d.flags->max_nb_slot[(tile % kSlots) * kLineInts], mx);
     }
   }
-  if (!valid) return;
-  int npl_p = (npl + kPlainBatch - 1) / kPlainBatch * kPlainBatch;
-  int nog_p = (nog + kOtherBatch - 1) / kOtherBatch * kOtherBatch;
-  if (npl_p > K || nog_p > K) {
+  if (!valid || q != 0) return;
+  int nst = nblk * 8 + restp, nogp = (nog + kOtherBatch - 1) / kOtherBatch * kOtherBatch;
+  if (nst + nogp > cap) {
     latch(d.flags, LE_E_CAPACITY);
-    npl_p = nog_p = 0;
+    nst = nogp = 0;
   } else {
-    if constexpr (!GL) {
-      if (npl < npl_p) {  // pad and flush the partial block
-        const int blk = npl >> 3;
-        for (int r = npl; r < npl_p; ++r) lbuf[threadIdx.x][r & 15] = (uint16_t)kHalo;
-        reinterpret_cast<uint4*>(d.nl16)[(size_t)blk * np2 + v] =
-            *reinterpret_cast<const uint4*>(&lbuf[threadIdx.x][(blk & 1) * 8]);
-      }
-    }
-    const uint8_t zero = pack_img(0, 0, 0);
-    while (nog < nog_p) og_append(og_entry((uint32_t)n, zero));  // sentinel entries up to a whole block
+    for (; nog < nogp; ++nog) og_store(nog, og_entry((uint32_t)n, pack_img(0, 0, 0)));
   }
-  d.n_plain[v] = npl_p;
-  d.n_og[v] = nog_p;
-  if (d.chain_len > 0 && half == 0) {
+  d.n_plain[i] = nst;
+  d.n_og[i] = nogp;
+  if (d.chain_len > 0) {
     int tg_ = d.tag[an][i];
     int lo = -1, hi = -1;
     if (tg_ < d.n_bonded) {
@@ -991,9 +1185,10 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
   }
 }
 
-template <int HALO, bool GL>
-__global__ void __launch_bounds__(2 * kTile) k_neighbors(Dev d) {
-  neighbors_body<HALO, GL>(d, xcd_block(d.ntiles));
+template <class TC, bool GL>
+__global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) k_neighbors(Dev d) {
+  if (rebuild_off(d)) return;  // (the same two words for every wave)
+  neighbors_body<TC::HALO, GL>(d, xcd_block(d.ntiles));
 }
 
 constexpr int kSpreadRun = 4;  // consecutive tiles per run of the batched list search
@@ -1001,11 +1196,13 @@ constexpr int kSpreadRun = 4;  // consecutive tiles per run of the batched list 
 // Batched form: only the members that rebuild at this step have work, so the
 // blocks are spread over the XCDs in short runs (xcd_spread) rather than in
 // one contiguous range per XCD; then the tile is located.
-template <int HALO, bool GL>
-__global__ void __launch_bounds__(2 * kTile) k_neighbors_b(Batch b) {
+template <class TC, bool GL>
+__global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) k_neighbors_b(Batch b) {
   int sm, tile;
   locate(b, xcd_spread<kSpreadRun>((int)blockIdx.x, (int)gridDim.x), sm, tile);
-  neighbors_body<HALO, GL>(stage_dev(b.dev[sm]), tile);
+  const Dev& d = stage_dev(b.dev[sm]);
+  if (rebuild_off(d)) return;
+  neighbors_body<TC::HALO, GL>(d, tile);
 }
 
 // ---------------------------------------------------------- integrator
@@ -1013,14 +1210,17 @@ __global__ void __launch_bounds__(2 * kTile) k_neighbors_b(Batch b) {
 // thread of a block of exactly NTH threads (the LDS array holds one entry per
 // wave of that block; launches pass the kernel's own block size).
 template <int NTH>
-__device__ __forceinline__ void vmax_commit(const Dev& d, double v2, int lb) {
+__device__ __forceinline__ void vmax_commit(const Dev& d, double v2, int lb, int nw = NTH / 64) {
   static_assert(NTH % 64 == 0 && NTH <= 1024, "whole waves, at most 16");
   __shared__ double wm[NTH / 64];
-  double m = wave_max(v2);
-  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  double m = 0.0;
+  if ((int)(threadIdx.x >> 6) < nw) {
+    m = wave_max(v2);
+    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < NTH / 64; ++w) m = fmax(m, wm[w]);
+    for (int w = 1; w < nw; ++w) m = fmax(m, wm[w]);
     atomicMax(&d.vmax[(lb % kSlots) * kLineU64], (unsigned long long)__double_as_longlong(m));
   }
 }
@@ -1110,36 +1310,38 @@ __device__ __forceinline__ void add_pair(double f, double dx, double dy, double 
 }
 
 // Scalar LJ force factor f (force on i = f d) for r^2 = r2, zero outside the
-// cutoff.  Branch-free so that the candidates of one batch are independent
-// instruction streams the compiler can interleave.  With CAP (FP64 only) the
-// magnitude |f| r is limited to cap: |f| <= cap / r.
+// cutoff: f = r^-8 (A r^-6 - B), A = 48 eps sigma^12, B = 24 eps sigma^6.
+// Branch-free so that the candidates of one batch are independent
+// instruction streams the compiler can interleave.  The FP64 form is bound by
+// the vector unit's issue, so it counts instructions: 1/r^2 from the hardware
+// reciprocal (within 2^-22) and one third-order step (its residual e leaves
+// e^3), and the cutoff clears the high word of 1/r^2 alone, whose square
+// then underflows to zero.  With CAP (FP64 only) the magnitude |f| r is limited
+// to cap: |f| <= cap / r.
 template <bool MIXED, bool CAP = false>
-__device__ __forceinline__ double lj_masked(double r2, double rc2, double sig2, double eps24,
-                                            double cap = 0.0) {
+__device__ __forceinline__ double lj_masked(const Dev& d, double r2) {
   static_assert(!(MIXED && CAP), "the capped force law is FP64");
-  const bool in = r2 < rc2;
+  const bool in = r2 < d.rc2;
   if (MIXED) {
     float r2f = (float)r2;
     float inv = __builtin_amdgcn_rcpf(r2f);
     inv = inv * (2.0f - r2f * inv);  // one Newton step: ~1 ulp
-    float s2 = (float)sig2 * inv;
+    float s2 = (float)d.sig2 * inv;
     float s6 = s2 * s2 * s2;
-    float f = (float)eps24 * s6 * (2.0f * s6 - 1.0f) * inv;
-    return in ? (double)f : 0.0;
+    float f = (float)d.eps24 * s6 * (2.0f * s6 - 1.0f) * inv;
+    return (double)(in ? f : 0.0f);
   } else {
     double inv = __builtin_amdgcn_rcp(r2);
-    double e = fma(-r2, inv, 1.0);
-    inv = fma(inv, e, inv);
-    e = fma(-r2, inv, 1.0);
-    inv = fma(inv, e, inv);
-    double s2 = sig2 * inv;
-    double s6 = s2 * s2 * s2;
-    double f = s6 * fma(2.0 * eps24, s6, -eps24) * inv;  // 24 eps s6 (2 s6 - 1) / r^2
+    const double e = fma(-r2, inv, 1.0);
+    inv = fma(inv, fma(e, e, e), inv);
+    inv = __hiloint2double(in ? __double2hiint(inv) : 0, __double2loint(inv));
+    const double i2 = inv * inv;
+    double f = (i2 * i2) * fma(d.lj_a, i2 * inv, -d.lj_b);
     if (CAP) {
-      const double lim = cap / sqrt(r2);
+      const double lim = d.force_cap / sqrt(r2);
       f = fmin(fmax(f, -lim), lim);
     }
-    return in ? f : 0.0;
+    return f;
   }
 }
 
@@ -1209,20 +1411,22 @@ __device__ __forceinline__ void dpd_pair(const Dev& d, uint32_t s_lo, uint32_t s
 // of a block of exactly NTH threads (one LDS row per wave of that block).
 template <int NTH>
 __device__ __forceinline__ void block_partials(double* vals, double* out, int lb,
-                                               int nwrite = kStressComps) {
+                                               int nwrite = kStressComps, int nw = NTH / 64) {
   static_assert(NTH % 64 == 0 && NTH <= 1024, "whole waves, at most 16");
   __shared__ double red[NTH / 64][kStressComps];
   int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  if (wid < nw) {
 #pragma unroll
-  for (int k = 0; k < kStressComps; ++k) {
-    double v = vals[k];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane == 0) red[wid][k] = v;
+    for (int k = 0; k < kStressComps; ++k) {
+      double v = vals[k];
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      if (lane == 0) red[wid][k] = v;
+    }
   }
   __syncthreads();
   if (threadIdx.x < nwrite) {
     double s = 0.0;
-    for (int w = 0; w < NTH / 64; ++w) s += red[w][threadIdx.x];
+    for (int w = 0; w < nw; ++w) s += red[w][threadIdx.x];
     out[lb * kStressComps + threadIdx.x] = s;
   }
 }
@@ -1239,23 +1443,32 @@ __device__ __forceinline__ void block_partials(double* vals, double* out, int lb
 // Langevin force (Eq. langevin on the peculiar velocity, Eq. vi):
 //   F = F^c - gamma m c + sqrt(24 gamma m kT / dt) theta,  c = u - gamma_dot (y - L_y/2) e_x
 // (with the friction on the lab velocity, c = u of the image inside the box).
-// With the LDS halo the block has kForceTPP threads per particle: threads
-// t, t + kTile, ... take every kForceTPP-th batch of the particle's list (more
-// waves per CU for the same LDS), and hand their partial sums to the first
-// through LDS before the epilogue.  Without the halo the launch bound of four
-// tiles per block makes the compiler keep fewer registers (more waves; DPD
-// 138 -> 132 us); the launch itself uses one tile.
-template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, bool STAGED, bool CAP>
+// With the LDS halo the block has kForceThreads / tile threads per particle:
+// threads t, t + tile, ... take the particle's batches in turn (more waves per
+// CU for the same LDS), and hand their partial sums to the first through LDS
+// before the epilogue.  Staging what lies within reach of a compact tile (about
+// 1250 positions for 128 LJ particles instead of 1900, 550 for beads of a
+// melt), lists in blocks of 4 and 22 vector instructions per entry took the
+// plain step from 43 to 36.5 us for 256,000 LJ particles and, against gathers from
+// global memory, from 37 to 26.7 us for 400,000 beads (traced); it is bound by the vector unit's
+// issue (53% busy) and the waves' imbalance, six waves per SIMD in 80 registers.
+// Without the halo the launch bound of four tiles per block makes the
+// compiler keep fewer registers (more waves; DPD 138 -> 132 us); the launch
+// itself uses one tile.
+template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP>
 __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* __restrict__ f_out) {
+  constexpr bool STAGED = TC::HALO > 0;
   static_assert(!CAP || (!STAGED && !MIXED && MODE != kDpdForce), "capped forces: FP64, global layout");
   constexpr bool VIR = SAMPLE || (MODE == kForcesOnly);
   constexpr bool DPD = MODE == kDpdForce;
   static_assert(!DPD || !STAGED, "DPD partners come from global memory");
-  constexpr int kH = STAGED ? kHalo + 1 : 1;  // no halo: every partner from global memory
-  constexpr int TPP = STAGED ? kForceTPP : kGlobalTPP;  // threads per particle
-  constexpr int kTh = TPP * kTile;                      // threads per block
-  static_assert(STAGED || TPP <= 2, "global layout: at most one thread per sub-list");
-  static_assert(!STAGED || 3 * kH >= kTile * 9 * (kForceTPP - 1), "the halo holds the partial-sum exchange");
+  constexpr int kTh = TC::kForceThreads;                // threads per block
+  const int kP = STAGED ? d.tile : kTile;               // particles per block (a power of 2)
+  const int TPP = STAGED ? kTh / kP : 1;                // threads per particle
+  constexpr int HALO = TC::HALO;
+  constexpr int kH = STAGED ? HALO + 1 : 1;  // no halo: every partner from global memory
+  static_assert(HALO % kTh == 0, "whole staging rounds");
+  static_assert(!STAGED || 3 * kH >= kTh * 9, "the halo holds the partial-sum exchange");
   __shared__ double hbuf[3 * kH];
   double* const hx = hbuf;
   double* const hy = hbuf + kH;
@@ -1265,9 +1478,9 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   if (threadIdx.x == 0) skip = d.flags->status;
   __syncthreads();
   if (skip) return;
-  const int half = TPP > 1 ? (int)(threadIdx.x / kTile) : 0;
-  const int tl = (int)threadIdx.x - half * kTile;  // particle within the tile
-  const int i = lb * kTile + tl;
+  const int half = STAGED ? (int)threadIdx.x >> d.tile_sh : 0;
+  const int tl = (int)threadIdx.x & (kP - 1);  // particle within the tile
+  const int i = lb * kP + tl;
   const bool valid = i < d.n;
   const int np = d.np;
   const int pc = c->pos_cur, ac = c->aux_cur;
@@ -1278,23 +1491,16 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   // during the halo staging so that their latency overlaps it (loads use a
   // clamped index; values of invalid lanes are never used).
   const int ic = valid ? i : 0;
-  const int np2 = d.np2;
   const double4 pi_ld = P[ic];
-  const int npl0_ld = STAGED ? d.n_plain[ic] : 0, npl1_ld = STAGED ? d.n_plain[np + ic] : 0;
+  const int npl_ld = STAGED ? d.n_plain[ic] : 0;
   const double* Uv = d.vel[ac];
   const double u0_ld = Uv[ic], u1_ld = Uv[np + ic], u2_ld = Uv[2 * np + ic];
   const int tag_ld = d.tag[ac][ic];
-  const uint4* __restrict__ l8 = reinterpret_cast<const uint4*>(d.nl16) + ic;
-  const int last_blk = d.K / kPlainBatch - 1;
-  const int nb0 = STAGED ? npl0_ld / kPlainBatch : 0;
-  // offset (in uint4) of batch b of the particle's two sub-lists read as one
-  // sequence (sub-list 0, then sub-list 1)
-  auto boff = [&](int b) -> size_t {
-    const int sub = b < nb0 ? 0 : 1;
-    const int blk = min(b - sub * nb0, last_blk);
-    return (size_t)blk * np2 + (size_t)sub * np;
-  };
-  uint4 t0 = make_uint4(0u, 0u, 0u, 0u), t1 = t0;
+  // staged entries: block b of 4 (half a unit) of the particle's list
+  const uint2* __restrict__ l4s = reinterpret_cast<const uint2*>(d.nl + ic);
+  const int nb = STAGED ? npl_ld / 4 : 0;
+  auto boff = [&](int b) -> size_t { return b < nb ? (size_t)(b >> 1) * (2 * np) + (b & 1) : 0; };
+  uint2 t0 = make_uint2(0u, 0u), t1 = t0;
   // Stage the tile's halo: the slots recorded at the last build with their
   // current positions, each shifted by its periodic / Lees-Edwards image
   // (sy Delta + sx L_x, sy L_y, sz L_z; the x image absorbs the offset's
@@ -1302,41 +1508,54 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   // slot loads, then all position loads, are in flight together.
   if (STAGED) {
     const int nst = d.tile_nstage[lb];
-    const int* hs = d.halo_slot + (size_t)lb * kHalo;
-    const uint8_t* hc = d.halo_code + (size_t)lb * kHalo;
-    constexpr int U = kHalo / kTh;
-    int slot[U];
-    uint8_t code[U];
-    const int nsent = d.n;
+    const uint32_t* hs = d.halo + (size_t)lb * HALO;
+    constexpr int U = STAGED ? HALO / kTh : 1;
+    // the last round only where the tile has that many positions
+    constexpr int U0 = U > 1 ? U - 1 : 1;
+    const uint32_t sent = og_entry((uint32_t)d.n, pack_img(0, 0, 0));
+    auto stage = [&](auto r0, auto r1, bool lists) {
+      constexpr int R0 = decltype(r0)::value, N = decltype(r1)::value - R0;
+      uint32_t ent[N];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // always load from an index inside this tile's table, then select the value
-      int h = threadIdx.x + u * kTh;
-      int hh = h < nst ? h : 0;
-      int sv = hs[hh];
-      uint8_t cv = hc[hh];
-      slot[u] = (h < nst) ? sv : nsent;
-      code[u] = (h < nst) ? cv : pack_img(0, 0, 0);
+      for (int u = 0; u < N; ++u) {
+        // always load from an index inside this tile's table, then select the value
+        int h = threadIdx.x + (R0 + u) * kTh;
+        int hh = h < nst ? h : 0;
+        const uint32_t ev = hs[hh];
+        ent[u] = (h < nst) ? ev : sent;
+      }
+      if (lists) {
+        t0 = l4s[boff(half)];
+        t1 = l4s[boff(half + TPP)];
+      }
+      // every position is loaded and written (past nst: the sentinel slot, an
+      // unused LDS entry), so that no load is sunk into a condition and all of
+      // them are in flight together
+      double4 pj[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) pj[u] = P[ent[u] & kSlotMask];
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const int h = threadIdx.x + (R0 + u) * kTh;
+        const uint32_t code = ent[u] >> kSlotBits;
+        if (__any(code != pack_img(0, 0, 0))) {  // (no image of any: most waves away from the faces)
+          int sx, sy, sz;
+          unpack_img((uint8_t)code, sx, sy, sz);
+          sx += sy * W;
+          pj[u].x = pj[u].x + ((double)sy * Delta + (double)sx * d.Lx);
+          pj[u].y = pj[u].y + (double)sy * d.Ly;
+          pj[u].z = pj[u].z + (double)sz * d.Lz;
+        }
+        hx[h] = pj[u].x;
+        hy[h] = pj[u].y;
+        hz[h] = pj[u].z;
+      }
+    };
+    stage(std::integral_constant<int, 0>{}, std::integral_constant<int, U0>{}, true);
+    if constexpr (U > U0) {
+      if (nst > U0 * kTh) stage(std::integral_constant<int, U0>{}, std::integral_constant<int, U>{}, false);
     }
-    t0 = l8[boff(half)];
-    t1 = l8[boff(half + kForceTPP)];
-    // every position is loaded and written (past nst: the sentinel slot, an
-    // unused LDS entry), so that no load is sunk into a condition and all of
-    // them are in flight together
-    double4 pj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) pj[u] = P[slot[u]];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int h = threadIdx.x + u * kTh;
-      int sx, sy, sz;
-      unpack_img(code[u], sx, sy, sz);
-      sx += sy * W;
-      hx[h] = pj[u].x + ((double)sy * Delta + (double)sx * d.Lx);
-      hy[h] = pj[u].y + (double)sy * d.Ly;
-      hz[h] = pj[u].z + (double)sz * d.Lz;
-    }
-    if (threadIdx.x == 0) { hx[kHalo] = 1e100; hy[kHalo] = 1e100; hz[kHalo] = 1e100; }
+    if (threadIdx.x == 0) { hx[HALO] = 1e100; hy[HALO] = 1e100; hz[HALO] = 1e100; }
     __syncthreads();
   }
   double fx = 0.0, fy = 0.0, fz = 0.0;
@@ -1346,69 +1565,53 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   const uint32_t st_lo = (uint32_t)(uint64_t)c->step, st_hi = (uint32_t)((uint64_t)c->step >> 32);
   const double4* __restrict__ VT = reinterpret_cast<const double4*>(d.vt);
   if (valid) {
-    const double rc2 = d.rc2, sig2 = d.sig2, eps24 = d.eps24;
-    // staged partners (already shifted to their image): the particle's two
-    // sub-lists read as one sequence of batches of 8, of which this thread
-    // takes batches half, half + kForceTPP, ...; one 16-byte index load per
-    // batch, two of this thread's batches ahead.  Loads always read an existing block
-    // of the list array and the value is selected afterwards (a select between
-    // pointers would become a flat load).
-    const int nb = STAGED ? nb0 + npl1_ld / kPlainBatch : 0;
-    const uint4 zero4 = make_uint4(kHalo | (kHalo << 16), kHalo | (kHalo << 16), kHalo | (kHalo << 16),
-                                   kHalo | (kHalo << 16));
-    uint4 v0 = nb > half ? t0 : zero4;
-    uint4 v1 = nb > half + kForceTPP ? t1 : zero4;
-    for (int b = half; b < nb; b += kForceTPP) {
-      uint4 t2 = l8[boff(b + 2 * kForceTPP)];
-      uint4 v2 = (b + 2 * kForceTPP < nb) ? t2 : zero4;
-      int j[8] = {(int)(v0.x & 0xffff), (int)(v0.x >> 16), (int)(v0.y & 0xffff), (int)(v0.y >> 16),
-                  (int)(v0.z & 0xffff), (int)(v0.z >> 16), (int)(v0.w & 0xffff), (int)(v0.w >> 16)};
-      double xj[8], yj[8], zj[8];
+    // staged partners (already shifted to their image): the particle's list is
+    // a sequence of blocks of 4, of which this thread takes blocks half, half +
+    // TPP, ... (a wave runs to its longest list: with blocks of 8, lists of
+    // 100 entries ran as 128); one 8-byte index load per block, two of this
+    // thread's blocks ahead.  Past the list the first block is loaded and not used.
+    for (int b = half; b < nb; b += TPP) {
+      const uint2 t2 = l4s[boff(b + 2 * TPP)];
+      const int j[4] = {(int)(t0.x & 0xffff), (int)(t0.x >> 16), (int)(t0.y & 0xffff), (int)(t0.y >> 16)};
+      double xj[4], yj[4], zj[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) { xj[u] = hx[j[u]]; yj[u] = hy[j[u]]; zj[u] = hz[j[u]]; }
+      for (int u = 0; u < 4; ++u) { xj[u] = hx[j[u]]; yj[u] = hy[j[u]]; zj[u] = hz[j[u]]; }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < 4; ++u) {
         double dx = pi.x - xj[u], dy = pi.y - yj[u], dz = pi.z - zj[u];
         const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        add_pair<VIR>(lj_masked<MIXED>(r2, rc2, sig2, eps24), dx, dy, dz, fx, fy, fz, w);
+        add_pair<VIR>(lj_masked<MIXED>(d, r2), dx, dy, dz, fx, fy, fz, w);
       }
-      v0 = v1;
-      v1 = v2;
+      t0 = t1;
+      t1 = t2;
     }
     // partners that were not staged: global memory, exact image arithmetic;
-    // eight gathers in flight, the next eight indices requested ahead.  With
-    // the halo each thread takes its own sub-list; without, one thread per
-    // particle takes both as one sequence.
-    // the sub-lists this thread takes, read as one sequence of blocks of 4
-    // (sub-list s_lo, then s_hi) so that one prefetch pipeline runs across both
-    // (with the halo, threads 0 and 1 of a particle take one sub-list each)
-    const bool has_og = !STAGED || half < 2;
-    const int s_lo = TPP > 1 ? min(half, 1) : 0, s_hi = TPP > 1 ? s_lo : 1;
-    const int nbo0 = has_og ? d.n_og[s_lo * np + i] / kOtherBatch : 0;
-    const int nbo = nbo0 + (has_og && s_hi != s_lo ? d.n_og[s_hi * np + i] / kOtherBatch : 0);
-    const int last_ob = d.K / kOtherBatch - 1;
+    // the next round's indices requested ahead.  With the halo the threads of
+    // a particle take rounds in turn.
+    const int nfo = STAGED ? 0 : d.n_plain[i] / kOtherBatch;
+    const int nbo = nfo + d.n_og[i] / kOtherBatch;
+    const int last_ob = d.cap / kOtherBatch - 1;
     auto ooff = [&](int q) -> size_t {
-      const bool first = q < nbo0;
-      const int blk = min(first ? q : q - nbo0, last_ob);
-      return (size_t)blk * np2 + (size_t)(first ? s_lo : s_hi) * np + i;
+      const int b = STAGED || q >= nfo ? last_ob - min(q - nfo, last_ob) : q;
+      return (size_t)b * np + i;
     };
-    const uint4* __restrict__ l4 = reinterpret_cast<const uint4*>(d.nlo);
+    const uint4* __restrict__ l4 = d.nl;
     // GB blocks of 4 per round: one for the plain global layout (fewer
     // gathers in flight leave room for more waves: KG 49 -> 48 us), two with
     // the halo's remainder pieces and with DPD (one block: 138 -> 195 us)
-    constexpr int GB = (STAGED || DPD) ? 2 : 1;
+    constexpr int GB = DPD ? 2 : 1;
     uint4 jn[GB];
 #pragma unroll
-    for (int k = 0; k < GB; ++k) jn[k] = l4[ooff(k)];
+    for (int k = 0; k < GB; ++k) jn[k] = l4[ooff(half * GB + k)];
     {
-    for (int b = 0; b < nbo; b += GB) {
+    for (int b = half * GB; b < nbo; b += TPP * GB) {
       // slots, and the four image codes of a block repacked into one word
       // (fewer live registers while the gathers are in flight)
       uint32_t sl[4 * GB], cq[GB];
 #pragma unroll
       for (int k = 0; k < GB; ++k) {
         const uint4 jq = jn[k];
-        jn[k] = l4[ooff(b + GB + k)];
+        jn[k] = l4[ooff(b + TPP * GB + k)];
         const bool in = b + k < nbo;  // the entries of this block are the list's
         sl[4 * k] = (in ? jq.x : (uint32_t)d.n) & kSlotMask;
         sl[4 * k + 1] = (in ? jq.y : (uint32_t)d.n) & kSlotMask;
@@ -1441,7 +1644,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
         double dx = ((pi.x - pj[u].x) - (double)sy * Delta) - (double)sx * d.Lx;
         double dz = (pi.z - pj[u].z) - (double)sz * d.Lz;
         const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        add_pair<VIR>(lj_masked<MIXED, CAP>(r2, rc2, sig2, eps24, d.force_cap), dx, dy, dz, fx, fy, fz, w);
+        add_pair<VIR>(lj_masked<MIXED, CAP>(d, r2), dx, dy, dz, fx, fy, fz, w);
         if (DPD) {
           // the image s_y boxes up streams faster by s_y gamma_dot L_y
           const double vx = (u0_ld - vj[u].x) - (double)sy * d.sv;
@@ -1514,38 +1717,17 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
     // first adds them in thread order
     __syncthreads();
     if (half > 0) {
-      double* ex = hbuf + ((half - 1) * kTile + tl) * 9;
+      double* ex = hbuf + ((half - 1) * kP + tl) * 9;
       ex[0] = fx; ex[1] = fy; ex[2] = fz;
       if (VIR) for (int q = 0; q < 6; ++q) ex[3 + q] = w[q];
     }
     __syncthreads();
     if (half == 0) {
-      for (int t = 1; t < kForceTPP; ++t) {
-        const double* ex = hbuf + ((t - 1) * kTile + tl) * 9;
+      for (int t = 1; t < TPP; ++t) {
+        const double* ex = hbuf + ((t - 1) * kP + tl) * 9;
         fx += ex[0]; fy += ex[1]; fz += ex[2];
         if (VIR) for (int q = 0; q < 6; ++q) w[q] += ex[3 + q];
       }
-    } else {
-      for (int q = 0; q < 6; ++q) w[q] = 0.0;
-    }
-  }
-  if constexpr (!STAGED && TPP > 1) {
-    // the thread of sub-list 1 hands its sums (pair forces, virial, DPD terms)
-    // to the thread of sub-list 0, which adds them after its own
-    constexpr int XW = DPD ? 12 : 9;
-    __shared__ double xch[kTile * XW];
-    if (half == 1) {
-      double* ex = xch + tl * XW;
-      ex[0] = fx; ex[1] = fy; ex[2] = fz;
-      if (VIR) for (int q = 0; q < 6; ++q) ex[3 + q] = w[q];
-      if (DPD) { ex[9] = gx; ex[10] = gy; ex[11] = gz; }
-    }
-    __syncthreads();
-    if (half == 0) {
-      const double* ex = xch + tl * XW;
-      fx += ex[0]; fy += ex[1]; fz += ex[2];
-      if (VIR) for (int q = 0; q < 6; ++q) w[q] += ex[3 + q];
-      if (DPD) { gx += ex[9]; gy += ex[10]; gz += ex[11]; }
     } else {
       for (int q = 0; q < 6; ++q) w[q] = 0.0;
     }
@@ -1613,20 +1795,22 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
       U[i] = ux; U[np + i] = uy; U[2 * np + i] = uz;
     }
   }
-  if (MODE == kStepFused) vmax_commit<kTh>(d, v2, lb);
+  // (the waves of the threads that finish particles)
+  const int nw = (kP + 63) / 64;
+  if (MODE == kStepFused) vmax_commit<kTh>(d, v2, lb, nw);
   if (VIR) {
     double vals[kStressComps];
 #pragma unroll
     for (int k = 0; k < 6; ++k) { vals[k] = kin[k]; vals[6 + k] = 0.5 * w[k]; }
-    block_partials<kTh>(vals, d.partials, lb);
+    block_partials<kTh>(vals, d.partials, lb, kStressComps, nw);
   }
 }
 
-template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, bool STAGED, bool CAP = false>
-__global__ void __launch_bounds__(STAGED ? kForceTPP * kTile : 4 * kTile)
+template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
+__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, (TC::HALO && !SAMPLE && MODE != kForcesOnly) ? 6 : 1)
     k_force(Dev d, double* __restrict__ f_out, double* __restrict__ sample_out) {
   (void)sample_out;
-  force_body<MODE, MIXED, BONDS, SAMPLE, STAGED, CAP>(d, xcd_block(d.ntiles), f_out);
+  force_body<MODE, MIXED, BONDS, SAMPLE, TC, CAP>(d, xcd_block(d.nblocks), f_out);
 }
 
 // Batched form (the step modes; no per-particle output): one launch over the
@@ -1642,14 +1826,14 @@ template <bool MIXED, bool BONDS>
 __global__ void __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(3)))
     k_force_dpd(Dev d, double* __restrict__ f_out, double* __restrict__ sample_out) {
   (void)sample_out;
-  force_body<kDpdForce, MIXED, BONDS, false, false, false>(d, xcd_block(d.ntiles), f_out);
+  force_body<kDpdForce, MIXED, BONDS, false, TileNone, false>(d, xcd_block(d.nblocks), f_out);
 }
-template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, bool STAGED, bool CAP = false>
-__global__ void __launch_bounds__(STAGED ? kForceTPP * kTile : 4 * kTile) k_force_b(Batch b) {
+template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
+__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, (TC::HALO && !SAMPLE) ? 6 : 1) k_force_b(Batch b) {
   int sm, lb;
-  const int g = STAGED ? xcd_spread<16>((int)blockIdx.x, (int)gridDim.x) : xcd_map((int)blockIdx.x, (int)gridDim.x);
+  const int g = TC::kSpread ? xcd_spread<16>((int)blockIdx.x, (int)gridDim.x) : xcd_map((int)blockIdx.x, (int)gridDim.x);
   locate(b, g, sm, lb);
-  force_body<MODE, MIXED, BONDS, SAMPLE, STAGED, CAP>(stage_dev(b.dev[sm]), lb, nullptr);
+  force_body<MODE, MIXED, BONDS, SAMPLE, TC, CAP>(stage_dev(b.dev[sm]), lb, nullptr);
 }
 
 // DPD: pack the current velocities and tags of every slot (and zeros for the
@@ -1962,29 +2146,74 @@ __global__ void k_state_out(Dev d, double* x, double* u, int32_t* cell_of, int32
     int iz = cell_index(p.z, d.inv_lz, d.nz);
     cell_of[t] = (iz * d.ny + iy) * d.nx + ix;
   }
-  if (order) order[i] = t;
+  if (order) {
+    // slots follow the beam order; the reported order is by (cell id, tag): the
+    // first slot of the particle's cell in id order (in cell_count, see
+    // k_id_start) plus its rank within the cell
+    const int ix = cell_index(p.x, d.inv_lx, d.nx);
+    const int iy = cell_index(p.y, d.inv_ly, d.ny);
+    const int iz = cell_index(p.z, d.inv_lz, d.nz);
+    order[d.cell_count[(iz * d.ny + iy) * d.nx + ix] + (i - d.cell_start[cell_slot(d, ix, iy, iz)])] = t;
+  }
+}
+
+// First slot of every cell with the cells in the order of their ids, into
+// cell_count (cleared again by k_clear_counts once the order is written).  One
+// block; only le_build_cells with an order asks for it.
+__global__ void __launch_bounds__(1024) k_id_start(Dev d) {
+  __shared__ int ws[16];
+  if (d.flags->status) return;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  int base = 0;
+  for (int c0 = 0; c0 < d.ncell; c0 += 1024) {
+    const int c = c0 + (int)threadIdx.x;
+    int v = 0;
+    if (c < d.ncell) {
+      const int k = cell_slot(d, c % d.nx, c / d.nx % d.ny, c / d.nx / d.ny);
+      v = d.cell_start[k + 1] - d.cell_start[k];
+    }
+    int incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) ws[wid] = incl;
+    __syncthreads();
+    int off = base + incl - v, all = 0;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wid) off += ws[w];
+      all += ws[w];
+    }
+    if (c < d.ncell) d.cell_count[c] = off;
+    base += all;
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kBlock) k_clear_counts(Dev d) {
+  if (d.flags->status) return;
+  const int c = blockIdx.x * kBlock + threadIdx.x;
+  if (c < d.ncell) d.cell_count[c] = 0;
 }
 
 __global__ void k_pairs_out(Dev d, int64_t* pairs, int64_t cap, unsigned long long* counter) {
   if (d.flags->status) return;
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= d.n) return;
-  const int np = d.np;
   const int32_t* tag = d.tag[d.ctrl->aux_cur];
-  const int* hs = d.halo_slot + (size_t)(i / kTile) * kHalo;
+  const uint32_t* hs = d.halo + (size_t)(i / d.tile) * d.halo_cap;
   const int ti = tag[i];
-  const int np2 = d.np2;
-  for (int sub = 0; sub < 2; ++sub) {
-  const int v = sub * np + i;
-  const int npl = d.n_plain[v], nog = d.n_og[v];
+  const int npl = d.n_plain[i], nog = d.n_og[i];
   for (int k = 0; k < npl + nog; ++k) {
     int slot;
-    if (k < npl) {
-      int h = d.nl16[idx8(k, v, np2)];
-      if (h == kHalo) continue;
-      slot = hs[h];
+    if (k < npl && d.staged) {
+      const int h = reinterpret_cast<const uint16_t*>(d.nl + unit_front(d, k >> 3, i))[k & 7];
+      if (h == d.halo_cap) continue;
+      slot = (int)(hs[h] & kSlotMask);
     } else {
-      slot = (int)(d.nlo[idx4(k - npl, v, np2)] & kSlotMask);
+      const int m = k < npl ? k : k - npl;
+      const size_t u = k < npl ? unit_front(d, m >> 2, i) : unit_back(d, m >> 2, i);
+      slot = (int)(reinterpret_cast<const uint32_t*>(d.nl + u)[m & 3] & kSlotMask);
       if (slot == d.n) continue;
     }
     int tj = tag[slot];
@@ -1992,7 +2221,6 @@ __global__ void k_pairs_out(Dev d, int64_t* pairs, int64_t cap, unsigned long lo
       unsigned long long idx = atomicAdd(counter, 1ull);
       if ((int64_t)idx < cap) { pairs[2 * idx] = ti; pairs[2 * idx + 1] = tj; }
     }
-  }
   }
 }
 
@@ -2025,6 +2253,21 @@ hipError_t launch_load_state(const Dev& d, hipStream_t s, const double* x0, cons
   return hipGetLastError();
 }
 
+// Calls f with the tile configuration of the halo layout.
+template <typename F>
+static void with_halo_tiles(const Dev& d, F f) {
+  if (d.tiles == kTilesSparse) f(TileSparse{});
+  else f(TileDense{});
+}
+// The same for the list search of either layout, with whether its lists hold
+// global slots.
+template <typename F>
+static void with_search_tiles(const Dev& d, F f) {
+  if (d.staged) with_halo_tiles(d, [&](auto t) { f(t, std::false_type{}); });
+  else if (d.tiles == kTilesSparse) f(TileSparse{}, std::true_type{});
+  else f(TileDenseGlobal{}, std::true_type{});
+}
+
 hipError_t launch_rebuild(const Dev& d, Ctrl* next, unsigned long long* next_vmax, hipStream_t s,
                           bool force, bool control) {
   // kernels after the first see the control copy it writes
@@ -2034,12 +2277,10 @@ hipError_t launch_rebuild(const Dev& d, Ctrl* next, unsigned long long* next_vma
   hipLaunchKernelGGL(k_control_bin, dim3((d.n + kBinBlock - 1) / kBinBlock), dim3(kBlock), 0, s, d, next, next_vmax,
                      force ? 1 : 0, control ? 1 : 0);
   hipLaunchKernelGGL(k_scan_permute, dim3(d.sp_blocks), dim3(kBlock), 0, s, dn);
-  // the LDS halo of the search: full size, or smaller (more blocks per CU)
-  // for sparse systems whose lists hold global slots
-  if (dn.staged) hipLaunchKernelGGL((k_neighbors<kHalo, false>), dim3(d.ntiles), dim3(2 * kTile), 0, s, dn);
-  else if (dn.small_halo)
-    hipLaunchKernelGGL((k_neighbors<kHaloSearch, true>), dim3(d.ntiles), dim3(2 * kTile), 0, s, dn);
-  else hipLaunchKernelGGL((k_neighbors<kHalo, true>), dim3(d.ntiles), dim3(2 * kTile), 0, s, dn);
+  with_search_tiles(d, [&](auto t, auto gl) {
+    using TC = decltype(t);
+    hipLaunchKernelGGL((k_neighbors<TC, decltype(gl)::value>), dim3(d.ntiles), dim3(kSearchThreads), 0, s, dn);
+  });
   return hipGetLastError();
 }
 hipError_t launch_kick_drift(const Dev& d, hipStream_t s) {
@@ -2055,16 +2296,17 @@ static void launch_k(K k, dim3 g, dim3 b, hipStream_t s, hipEvent_t e0, hipEvent
   if (e0 || e1) hipExtLaunchKernelGGL(k, g, b, 0, s, e0, e1, 0, d, f_out, so);
   else hipLaunchKernelGGL(k, g, b, 0, s, d, f_out, so);
 }
-template <int MODE, bool SAMPLE, bool STAGED>
+template <int MODE, bool SAMPLE, class TC>
 static void launch_force_s(const Dev& d, hipStream_t s, double* f_out, double* so, hipEvent_t e0,
                            hipEvent_t e1) {
-  dim3 g(d.ntiles), b(STAGED ? kForceTPP * kTile : kGlobalTPP * kTile);
+  constexpr bool STAGED = TC::HALO > 0;
+  dim3 g(d.nblocks), b(TC::kForceThreads);
   const bool bonds = d.chain_len > 0;
   const bool mixed = d.precision == LE_MIXED;
   if constexpr (!STAGED && MODE != kDpdForce) {
     if (d.force_cap > 0.0) {  // the host guarantees FP64 and the global layout
-      if (bonds) launch_k(k_force<MODE, false, true, SAMPLE, false, true>, g, b, s, e0, e1, d, f_out, so);
-      else launch_k(k_force<MODE, false, false, SAMPLE, false, true>, g, b, s, e0, e1, d, f_out, so);
+      if (bonds) launch_k(k_force<MODE, false, true, SAMPLE, TileNone, true>, g, b, s, e0, e1, d, f_out, so);
+      else launch_k(k_force<MODE, false, false, SAMPLE, TileNone, true>, g, b, s, e0, e1, d, f_out, so);
       return;
     }
   }
@@ -2077,18 +2319,18 @@ static void launch_force_s(const Dev& d, hipStream_t s, double* f_out, double* s
       else launch_k(k_force_dpd<false, false>, g, b, s, e0, e1, d, f_out, so);
     }
   } else if (mixed) {
-    if (bonds) launch_k(k_force<MODE, true, true, SAMPLE, STAGED>, g, b, s, e0, e1, d, f_out, so);
-    else launch_k(k_force<MODE, true, false, SAMPLE, STAGED>, g, b, s, e0, e1, d, f_out, so);
+    if (bonds) launch_k(k_force<MODE, true, true, SAMPLE, TC>, g, b, s, e0, e1, d, f_out, so);
+    else launch_k(k_force<MODE, true, false, SAMPLE, TC>, g, b, s, e0, e1, d, f_out, so);
   } else {
-    if (bonds) launch_k(k_force<MODE, false, true, SAMPLE, STAGED>, g, b, s, e0, e1, d, f_out, so);
-    else launch_k(k_force<MODE, false, false, SAMPLE, STAGED>, g, b, s, e0, e1, d, f_out, so);
+    if (bonds) launch_k(k_force<MODE, false, true, SAMPLE, TC>, g, b, s, e0, e1, d, f_out, so);
+    else launch_k(k_force<MODE, false, false, SAMPLE, TC>, g, b, s, e0, e1, d, f_out, so);
   }
 }
 template <int MODE, bool SAMPLE>
 static void launch_force_t(const Dev& d, hipStream_t s, double* f_out, double* so, hipEvent_t e0,
                            hipEvent_t e1) {
-  if (d.staged) launch_force_s<MODE, SAMPLE, true>(d, s, f_out, so, e0, e1);
-  else launch_force_s<MODE, SAMPLE, false>(d, s, f_out, so, e0, e1);
+  if (!d.staged) launch_force_s<MODE, SAMPLE, TileNone>(d, s, f_out, so, e0, e1);
+  else with_halo_tiles(d, [&](auto t) { launch_force_s<MODE, SAMPLE, decltype(t)>(d, s, f_out, so, e0, e1); });
 }
 
 hipError_t launch_force(const Dev& d, hipStream_t s, ForceMode mode, bool sample, double* f_out,
@@ -2107,15 +2349,15 @@ hipError_t launch_force(const Dev& d, hipStream_t s, ForceMode mode, bool sample
     case kDpdForce:
       if (d.staged || !d.vt) return hipErrorInvalidValue;  // DPD partners come from global memory
       hipLaunchKernelGGL(k_pack_vt, dim3(blocks_for(d.n + 1)), dim3(kBlock), 0, s, d);
-      if (sample) launch_force_s<kDpdForce, true, false>(d, s, f_out, sample_out, e0, e1);
-      else launch_force_s<kDpdForce, false, false>(d, s, f_out, nullptr, e0, e1);
+      if (sample) launch_force_s<kDpdForce, true, TileNone>(d, s, f_out, sample_out, e0, e1);
+      else launch_force_s<kDpdForce, false, TileNone>(d, s, f_out, nullptr, e0, e1);
       break;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_integrate(const Dev& d, hipStream_t s, bool last, bool sample) {
-  dim3 g(d.ntiles), b(kTile);
+  dim3 g(d.nblocks), b(kTile);
   if (last) {
     if (sample) hipLaunchKernelGGL((k_integrate<true, true>), g, b, 0, s, d);
     else hipLaunchKernelGGL((k_integrate<true, false>), g, b, 0, s, d);
@@ -2155,7 +2397,9 @@ hipError_t launch_msd(const Dev& d, hipStream_t s, const double* ref, double* ou
 }
 hipError_t launch_state_out(const Dev& d, hipStream_t s, double* x, double* u, int32_t* cell_of,
                             int32_t* order) {
+  if (order) hipLaunchKernelGGL(k_id_start, dim3(1), dim3(1024), 0, s, d);
   hipLaunchKernelGGL(k_state_out, dim3(blocks_for(d.n)), dim3(kBlock), 0, s, d, x, u, cell_of, order);
+  if (order) hipLaunchKernelGGL(k_clear_counts, dim3(blocks_for(d.ncell)), dim3(kBlock), 0, s, d);
   return hipGetLastError();
 }
 
@@ -2185,59 +2429,64 @@ hipError_t launch_kick_drift_b(const Batch& par_cur, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_rebuild_b(const Batch& bin_cur, const Batch& scan_nxt, const Batch& tile_nxt,
-                            const Dev& cfg, hipStream_t s) {
+hipError_t launch_sort_b(const Batch& bin_cur, const Batch& scan_nxt, hipStream_t s) {
   hipLaunchKernelGGL(k_control_bin_b, grid_of(bin_cur), dim3(kBlock), 0, s, bin_cur);
   hipLaunchKernelGGL(k_scan_permute_b, grid_of(scan_nxt), dim3(kBlock), 0, s, scan_nxt);
-  if (cfg.staged) hipLaunchKernelGGL((k_neighbors_b<kHalo, false>), grid_of(tile_nxt), dim3(2 * kTile), 0, s, tile_nxt);
-  else if (cfg.small_halo)
-    hipLaunchKernelGGL((k_neighbors_b<kHaloSearch, true>), grid_of(tile_nxt), dim3(2 * kTile), 0, s, tile_nxt);
-  else hipLaunchKernelGGL((k_neighbors_b<kHalo, true>), grid_of(tile_nxt), dim3(2 * kTile), 0, s, tile_nxt);
   return hipGetLastError();
 }
 
-template <int MODE, bool SAMPLE, bool STAGED>
+hipError_t launch_search_b(const Batch& tile_nxt, const Dev& cfg, hipStream_t s) {
+  with_search_tiles(cfg, [&](auto t, auto gl) {
+    using TC = decltype(t);
+    hipLaunchKernelGGL((k_neighbors_b<TC, decltype(gl)::value>), grid_of(tile_nxt), dim3(kSearchThreads), 0, s,
+                       tile_nxt);
+  });
+  return hipGetLastError();
+}
+
+template <int MODE, bool SAMPLE, class TC>
 static void launch_force_bs(const Batch& b, const Dev& cfg, hipStream_t s) {
-  const dim3 g = grid_of(b), blk(STAGED ? kForceTPP * kTile : kGlobalTPP * kTile);
+  constexpr bool STAGED = TC::HALO > 0;
+  const dim3 g = grid_of(b), blk(TC::kForceThreads);
   const bool bonds = cfg.chain_len > 0;
   if constexpr (!STAGED && MODE != kDpdForce) {
     if (cfg.force_cap > 0.0) {
-      if (bonds) hipLaunchKernelGGL((k_force_b<MODE, false, true, SAMPLE, false, true>), g, blk, 0, s, b);
-      else hipLaunchKernelGGL((k_force_b<MODE, false, false, SAMPLE, false, true>), g, blk, 0, s, b);
+      if (bonds) hipLaunchKernelGGL((k_force_b<MODE, false, true, SAMPLE, TileNone, true>), g, blk, 0, s, b);
+      else hipLaunchKernelGGL((k_force_b<MODE, false, false, SAMPLE, TileNone, true>), g, blk, 0, s, b);
       return;
     }
   }
   if (cfg.precision == LE_MIXED) {
-    if (bonds) hipLaunchKernelGGL((k_force_b<MODE, true, true, SAMPLE, STAGED>), g, blk, 0, s, b);
-    else hipLaunchKernelGGL((k_force_b<MODE, true, false, SAMPLE, STAGED>), g, blk, 0, s, b);
+    if (bonds) hipLaunchKernelGGL((k_force_b<MODE, true, true, SAMPLE, TC>), g, blk, 0, s, b);
+    else hipLaunchKernelGGL((k_force_b<MODE, true, false, SAMPLE, TC>), g, blk, 0, s, b);
   } else {
-    if (bonds) hipLaunchKernelGGL((k_force_b<MODE, false, true, SAMPLE, STAGED>), g, blk, 0, s, b);
-    else hipLaunchKernelGGL((k_force_b<MODE, false, false, SAMPLE, STAGED>), g, blk, 0, s, b);
+    if (bonds) hipLaunchKernelGGL((k_force_b<MODE, false, true, SAMPLE, TC>), g, blk, 0, s, b);
+    else hipLaunchKernelGGL((k_force_b<MODE, false, false, SAMPLE, TC>), g, blk, 0, s, b);
   }
 }
 
 template <int MODE, bool SAMPLE>
 static void launch_force_bt(const Batch& b, const Dev& cfg, hipStream_t s) {
-  if (cfg.staged) launch_force_bs<MODE, SAMPLE, true>(b, cfg, s);
-  else launch_force_bs<MODE, SAMPLE, false>(b, cfg, s);
+  if (!cfg.staged) launch_force_bs<MODE, SAMPLE, TileNone>(b, cfg, s);
+  else with_halo_tiles(cfg, [&](auto t) { launch_force_bs<MODE, SAMPLE, decltype(t)>(b, cfg, s); });
 }
 
-hipError_t launch_force_b(const Batch& tile_cur, const Batch& par_cur, const Dev& cfg, hipStream_t s,
+hipError_t launch_force_b(const Batch& blk_cur, const Batch& par_cur, const Dev& cfg, hipStream_t s,
                           ForceMode mode, bool sample) {
   switch (mode) {
     case kStepLast:
-      if (sample) launch_force_bt<kStepLast, true>(tile_cur, cfg, s);
-      else launch_force_bt<kStepLast, false>(tile_cur, cfg, s);
+      if (sample) launch_force_bt<kStepLast, true>(blk_cur, cfg, s);
+      else launch_force_bt<kStepLast, false>(blk_cur, cfg, s);
       break;
     case kStepFused:
-      if (sample) launch_force_bt<kStepFused, true>(tile_cur, cfg, s);
-      else launch_force_bt<kStepFused, false>(tile_cur, cfg, s);
+      if (sample) launch_force_bt<kStepFused, true>(blk_cur, cfg, s);
+      else launch_force_bt<kStepFused, false>(blk_cur, cfg, s);
       break;
     case kDpdForce:
       if (cfg.staged || !cfg.vt) return hipErrorInvalidValue;
       hipLaunchKernelGGL(k_pack_vt_b, grid_of(par_cur), dim3(kBlock), 0, s, par_cur);
-      if (sample) launch_force_bs<kDpdForce, true, false>(tile_cur, cfg, s);
-      else launch_force_bs<kDpdForce, false, false>(tile_cur, cfg, s);
+      if (sample) launch_force_bs<kDpdForce, true, TileNone>(blk_cur, cfg, s);
+      else launch_force_bs<kDpdForce, false, TileNone>(blk_cur, cfg, s);
       break;
     default:
       return hipErrorInvalidValue;  // the other modes are not batched
@@ -2245,14 +2494,14 @@ hipError_t launch_force_b(const Batch& tile_cur, const Batch& par_cur, const Dev
   return hipGetLastError();
 }
 
-hipError_t launch_integrate_b(const Batch& tile_cur, hipStream_t s, bool last, bool sample) {
-  const dim3 g = grid_of(tile_cur), b(kTile);
+hipError_t launch_integrate_b(const Batch& blk_cur, hipStream_t s, bool last, bool sample) {
+  const dim3 g = grid_of(blk_cur), b(kTile);
   if (last) {
-    if (sample) hipLaunchKernelGGL((k_integrate_b<true, true>), g, b, 0, s, tile_cur);
-    else hipLaunchKernelGGL((k_integrate_b<true, false>), g, b, 0, s, tile_cur);
+    if (sample) hipLaunchKernelGGL((k_integrate_b<true, true>), g, b, 0, s, blk_cur);
+    else hipLaunchKernelGGL((k_integrate_b<true, false>), g, b, 0, s, blk_cur);
   } else {
-    if (sample) hipLaunchKernelGGL((k_integrate_b<false, true>), g, b, 0, s, tile_cur);
-    else hipLaunchKernelGGL((k_integrate_b<false, false>), g, b, 0, s, tile_cur);
+    if (sample) hipLaunchKernelGGL((k_integrate_b<false, true>), g, b, 0, s, blk_cur);
+    else hipLaunchKernelGGL((k_integrate_b<false, false>), g, b, 0, s, blk_cur);
   }
   return hipGetLastError();
 }

@@ -39,3 +39,68 @@ def test_observables_rounds(n, nbins):
     assert np.abs(got["sum_mc2"] - ref["sum_mc2"]).max() <= 1e-12 * ref["sum_mc2"].max()
     assert abs(got["kT"] - ref["kT"]) <= 1e-12 * ref["kT"]
     assert np.abs(got["com"] - ref["com"]).max() <= 1e-12 * np.abs(u).mean()
+
+
+def _slab(seed):
+    """A lattice filling the lowest third of the box: about 80 particles per cell, so
+    that a tile's halo holds more positions than the search looks at."""
+    rng = np.random.default_rng(seed)
+    L = 20.0
+    g = [np.arange(26) * (L / 26), np.arange(26) * (L / 26), np.arange(12) * 0.5]
+    x = np.stack([a.ravel() for a in np.meshgrid(*g, indexing="ij")]) + rng.uniform(0.0, 0.02, (3, 26 * 26 * 12))
+    return x, dict(n=x.shape[1], box=(L, L, L), max_neighbors=900)
+
+
+def _gas(seed):
+    """A gas of 0.08 particles per cell: a tile covers many beams of cells, nothing is staged."""
+    rng = np.random.default_rng(seed)
+    return rng.uniform(0.0, 60.0, (3, 700)), dict(n=700, box=(60.0, 60.0, 60.0))
+
+
+def _fluid(n):
+    def make(seed):
+        w = inputs.lj_workload(n=n, shear_rate=0.2, seed=seed)
+        return w.x, dict(n=n, box=w.box)
+    return make
+
+
+def _melt(chains, length, skin):
+    def make(seed):
+        w = inputs.kg_workload(chains, length, shear_rate=0.2, seed=seed)
+        return w.x, dict(n=chains * length, box=w.box, rc=2.0 ** (1.0 / 6.0), pair="wca", n_chains=chains,
+                         chain_len=length, skin=skin)
+    return make
+
+
+# small tiles with a ragged end, the last size with small tiles and the first
+# with large ones (dense, sparse), a tile in two beams of two widths, and the
+# two ways out of the staged halo
+SEARCH = {"lj_1009": _fluid(1009), "lj_10000": _fluid(10000), "lj_10001": _fluid(10001), "lj_16500": _fluid(16500),
+          "kg_2000": _melt(20, 100, 0.6), "kg_2010": _melt(30, 67, 0.6), "kg_12000_wide": _melt(60, 200, 1.2),
+          "slab": _slab, "gas": _gas}
+
+
+@pytest.mark.parametrize("tune", [1, 2])
+@pytest.mark.parametrize("name", list(SEARCH))
+def test_list_search_and_forces_at_tile_edges(name, tune):
+    """The pair set is the oracle's, exactly; cells and order too; forces and virial within 1e-12."""
+    x, kw = SEARCH[name](3)
+    p = Params(shear_rate=0.2, seed=3, tune=tune, **{"rc": 2.5, "skin": 0.3, **kw})
+    step0 = 1237
+    sim = Sim(p, x, np.zeros_like(x), step0=step0)
+    out = sim.build_cells()
+    F, W = sim.forces()
+    sim.close()
+    op = _oracle_params(p)
+    Delta = O.offset(step0, p.dt, p.shear_rate, p.box[0], p.box[1])
+    xw, _ = O.le_wrap(x, np.zeros_like(x), Delta, op)
+    nc = tuple(int(np.floor(L / (p.rlist * (1 + 1e-9)))) for L in p.box)
+    cells, order = O.cells(xw, nc, p.box)
+    assert np.array_equal(out["cell_of"], cells) and np.array_equal(out["order"], order)
+    ref = O.pairs_cells(xw, Delta, p.box, p.rlist)
+    got = np.sort(out["pairs"][:, 0] * p.n + out["pairs"][:, 1])
+    lo, hi = ref.min(axis=1).astype(np.int64), ref.max(axis=1).astype(np.int64)
+    assert np.array_equal(got, np.sort(lo * p.n + hi))
+    Fr, Wr, _ = O.forces(xw, Delta, op)
+    assert np.sqrt(((F - Fr) ** 2).sum(axis=0)).max() <= 1e-12 * np.sqrt((Fr ** 2).sum(axis=0).mean())
+    assert np.abs(W - Wr).max() <= 1e-12 * np.abs(Wr[:3]).max()
