@@ -99,7 +99,9 @@ void plan_tiles(const le_params* p, Geometry* g, double list_pp) {
   // LDS halo at force time when partners per particle clearly outnumber the
   // positions a tile must stage per particle
   const double halo_pp = best / g->tile;
-  g->staged = (p->tune == 1) ? 1 : (p->tune == 2) ? 0 : (list_pp >= 3.0 * halo_pp ? 1 : 0);
+  // (a small dense system always: it has few tiles, and 1000 particles take 8 us a
+  // force evaluation with the halo, 19 without)
+  g->staged = (p->tune == 1) ? 1 : (p->tune == 2) ? 0 : (list_pp >= 3.0 * halo_pp || (small && list_pp >= kDensePartners));
   if (p->thermostat == LE_THERMO_DPD || p->force_cap > 0.0) g->staged = 0;
   g->ntiles = (int32_t)((p->n + g->tile - 1) / g->tile);
   g->nblocks = g->staged ? g->ntiles : (int32_t)((p->n + kTile - 1) / kTile);

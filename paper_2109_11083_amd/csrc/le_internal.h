@@ -52,9 +52,11 @@ struct alignas(64) Ctrl {
   double drift;          // sum over steps since the build of dt * max |peculiar velocity|
   int32_t pos_cur;       // which position buffer holds the current positions
   int32_t aux_cur;       // which velocity/force/tag buffer is current
-  int32_t rebuild;       // 1: the lists are (being) rebuilt for this state
+  int32_t rebuild;       // kRebuild*: the lists are (being) rebuilt for this state
   int32_t wraps;         // whole L_x folds of the offset since the build
 };
+
+enum { kRebuildDue = 1, kRebuildForced = 2 };
 
 // Sticky status and telemetry shared by both control copies.
 struct alignas(64) Flags {

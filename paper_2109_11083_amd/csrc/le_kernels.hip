@@ -221,10 +221,10 @@ __device__ __forceinline__ void control_advance(const Dev& d, Ctrl& c, unsigned 
 // The bookkeeping of a rebuild, applied to the state the rebuild produces:
 // sorted copies go to the other buffers, the offset and step become the
 // reference of the co-moving criterion.
-__device__ __forceinline__ void rebuild_adopt(Ctrl& c) {
+__device__ __forceinline__ void rebuild_adopt(Ctrl& c, bool forced) {
   c.pos_cur ^= 1;
   c.aux_cur ^= 1;
-  c.rebuild = 1;
+  c.rebuild = forced ? kRebuildForced : kRebuildDue;
   c.rebuild_step = c.step;
   c.Delta_ref = c.Delta;
   c.drift = 0.0;
@@ -240,11 +240,26 @@ __device__ __forceinline__ bool rebuild_off(const Dev& d) {
   return (status != 0) | (rebuild == 0);
 }
 
+// Boundary crossing of one particle (Lees-Edwards shift; the velocity jump is
+// -ky jump_sv) + periodic wrap of x and z.  Non-finite coordinates become 0.
+__device__ __forceinline__ bool cross_wrap(const Dev& d, double Delta, double& x, double& y, double& z,
+                                           double& ky, double& kz) {
+  ky = wrap1(y, d.Ly);
+  x = x - ky * Delta;
+  wrap1(x, d.Lx);
+  kz = wrap1(z, d.Lz);
+  const bool fine = isfinite(x) && isfinite(y) && isfinite(z);
+  if (!fine) { x = 0.0; y = 0.0; z = 0.0; }
+  return fine;
+}
+
 // (1) Reads control copy d.ctrl and writes the next one (block 0).  With
-// `control` the step is advanced first (after a drift).  On a rebuild:
-// boundary crossing (Lees-Edwards shift and velocity jump) + periodic wrap of
-// x and z in place, then each particle's tag and slot go into its cell's bucket at
-// its arrival rank.  Runs of equal cells within a wave take one atomic per run.
+// `control` the step is advanced first (after a drift).  On a rebuild: each
+// particle's tag and slot go into the bucket of the cell that its position
+// lies in after crossing and wrap, at its arrival rank.  Runs of equal cells
+// within a wave take one atomic per run.  Reads positions and tags alone: the
+// crossing is applied where the particle is copied, (2); applied and written
+// here it cost the pass 12.6 instead of 9 us (400,000 beads).
 __device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict__ next,
                                                  unsigned long long* __restrict__ next_vmax, int force,
                                                  int control, int bid) {
@@ -272,7 +287,7 @@ __device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict_
       if (threadIdx.x == 0) {
         Ctrl o = c;
         o.rebuild = 0;
-        if (rb) rebuild_adopt(o);
+        if (rb) rebuild_adopt(o, force != 0);
         *next = o;
       }
     }
@@ -282,34 +297,14 @@ __device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict_
   // the look-back words of the scan start cleared (spread over the blocks)
   const int nbb = (d.n + kBinBlock - 1) / kBinBlock;  // blocks of this pass
   for (int k = bid * kBlock + (int)threadIdx.x; k < d.sp_blocks; k += nbb * kBlock) d.scan_status[k] = 0ull;
-  const int np = d.np;
   for (int rd = 0; rd < kBinBlock / kBlock; ++rd) {
     const int i = bid * kBinBlock + rd * kBlock + (int)threadIdx.x;
     int cell = -1, tg = 0;
     if (i < d.n) {
       tg = d.tag[sc.aux_cur][i];
-      double4* P = reinterpret_cast<double4*>(d.pos[sc.pos_cur]);
-      double* U = d.vel[sc.aux_cur];
-      double4 p = P[i];
-      double x = p.x, y = p.y, z = p.z;
-      double ux = U[i];
-      const double Delta = sc.Delta;
-      double ky = wrap1(y, d.Ly);
-      x = x - ky * Delta;
-      ux = ux - ky * d.jump_sv;  // velocity jump (lab storage only)
-      wrap1(x, d.Lx);
-      double kz = wrap1(z, d.Lz);
-      int cy, cz;
-      img_get(p.w, cy, cz);
-      p.w = img_put(cy + (int)ky, cz + (int)kz);
-      double uy = U[np + i], uz = U[2 * np + i];
-      if (!(isfinite(x) && isfinite(y) && isfinite(z) && isfinite(ux) && isfinite(uy) && isfinite(uz))) {
-        latch(d.flags, LE_E_NONFINITE);
-        x = 0.0; y = 0.0; z = 0.0;
-      }
-      p.x = x; p.y = y; p.z = z;
-      P[i] = p;
-      U[i] = ux;
+      const double4 p = reinterpret_cast<const double4*>(d.pos[sc.pos_cur])[i];
+      double x = p.x, y = p.y, z = p.z, ky, kz;
+      cross_wrap(d, sc.Delta, x, y, z, ky, kz);
       int ix = cell_index(x, d.inv_lx, d.nx);
       int iy = cell_index(y, d.inv_ly, d.ny);
       int iz = cell_index(z, d.inv_lz, d.nz);
@@ -364,7 +359,7 @@ __global__ void __launch_bounds__(kBlock) k_control_bin_b(Batch b) {
 // final slot of a particle is its cell's start plus the number of cell-mates
 // with a smaller tag, so the order is (cell, tag) whatever the arrival order.
 // The bucket entry carries the particle's binned slot; its state is copied
-// from there to the final slot in the other buffers.  No block reads what
+// from there, crossed and wrapped, to the final slot in the other buffers.  No block reads what
 // another writes, so the sort needs no further pass.
 __device__ __forceinline__ unsigned long long scan_word(int flag, long long v) {
   return ((unsigned long long)flag << 62) | (unsigned long long)v;
@@ -476,20 +471,34 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, int b) {
       tg = e.x;
     }
   };
+  // The total forces move along only in a forced rebuild: one due within a
+  // step call comes after the first half-kick, and the call's last step writes them anew.
+  const bool with_f = c->rebuild == kRebuildForced;
+  const double Delta = c->Delta;
   struct St { double4 p; double v0, v1, v2, f0, f1, f2; };
   auto load = [&](int i) -> St {
     const double* V = d.vel[as];
     const double* F = d.frc[as];
-    return St{reinterpret_cast<const double4*>(d.pos[ps])[i], V[i], V[np + i], V[2 * np + i],
-              F[i], F[np + i], F[2 * np + i]};
+    St v{reinterpret_cast<const double4*>(d.pos[ps])[i], V[i], V[np + i], V[2 * np + i], 0.0, 0.0, 0.0};
+    if (with_f) { v.f0 = F[i]; v.f1 = F[np + i]; v.f2 = F[2 * np + i]; }
+    return v;
   };
-  auto store = [&](int ns, int tg, const St& v) {
+  auto store = [&](int ns, int tg, St v) {
     if (ns < 0) return;
+    double ky, kz;
+    const bool fine = cross_wrap(d, Delta, v.p.x, v.p.y, v.p.z, ky, kz);
+    v.v0 = v.v0 - ky * d.jump_sv;  // velocity jump (lab storage only)
+    int cy, cz;
+    img_get(v.p.w, cy, cz);
+    v.p.w = img_put(cy + (int)ky, cz + (int)kz);
+    if (!(fine && isfinite(v.v0) && isfinite(v.v1) && isfinite(v.v2))) latch(d.flags, LE_E_NONFINITE);
     reinterpret_cast<double4*>(d.pos[pd])[ns] = v.p;
     double* V = d.vel[ad];
-    double* F = d.frc[ad];
     V[ns] = v.v0; V[np + ns] = v.v1; V[2 * np + ns] = v.v2;
-    F[ns] = v.f0; F[np + ns] = v.f1; F[2 * np + ns] = v.f2;
+    if (with_f) {
+      double* F = d.frc[ad];
+      F[ns] = v.f0; F[np + ns] = v.f1; F[2 * np + ns] = v.f2;
+    }
     d.tag[ad][ns] = tg;
     d.slot_of_tag[tg] = ns;
   };
@@ -587,13 +596,16 @@ __device__ __forceinline__ bool in_reach(const Box& b, float x, float y, float z
   return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)) <= b.reach2;
 }
 
-// Minimum over each row of 16 lanes (rotations within the row).
-__device__ __forceinline__ float row16_min(float v) {
-  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, false)));
-  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xf, 0xf, false)));
-  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x122, 0xf, 0xf, false)));
-  v = fminf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x121, 0xf, 0xf, false)));
-  return v;
+// Floats as integers of the same order (its own inverse), and the minimum over
+// each row of 16 lanes by rotations within the row.
+__device__ __forceinline__ int order_key(int b) { return b ^ ((b >> 31) & 0x7fffffff); }
+__device__ __forceinline__ float row16_min(float f) {
+  int v = order_key(__float_as_int(f));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0x124, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0x122, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, 0x121, 0xf, 0xf, false));
+  return __int_as_float(order_key(v));
 }
 
 // One stretch of a beam covered by a tile.  Its halo is the rows (y0 - 1 + ry,
@@ -726,9 +738,12 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
   const float fx = (float)(pi.x - sgs[gi].ox), fy = (float)(pi.y - sgs[gi].oy), fz = (float)(pi.z - sgs[gi].oz);
   for (int g = 0; g < nseg; ++g) {
     const bool in = valid && gi == g;
-    const Box b = {{row16_min(in ? fx : 1e30f), row16_min(in ? fy : 1e30f), row16_min(in ? fz : 1e30f),
+    Box b = {{row16_min(in ? fx : 1e30f), row16_min(in ? fy : 1e30f), row16_min(in ? fz : 1e30f),
                     row16_min(in ? -fx : 1e30f), row16_min(in ? -fy : 1e30f), row16_min(in ? -fz : 1e30f)}, 0.0f};
-    if (lane == 0) wbox[wv][g] = b;
+    if (lane == 0) {
+      wbox[wv][g] = b;
+      wbox[wv][g].reach2 = reach2_of(b, d.rlist_f);
+    }
   }
 
   // ---- staging table: one cell per thread, then the cells' offsets
@@ -950,26 +965,24 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
     const float R = __builtin_sqrtf(si) + d.rlist_f;
     const float margin = d.nb_rel * R * R;
     const float tlo = d.nb_lo - margin, thi = d.nb_hi + margin;
-    // bounding box of the cluster's particles, and the distance from it beyond
-    // which a candidate is out of every particle's reach (rounding included)
-    Box box = {{row16_min(in_seg ? fx : 1e30f), row16_min(in_seg ? fy : 1e30f), row16_min(in_seg ? fz : 1e30f),
-                      row16_min(in_seg ? -fx : 1e30f), row16_min(in_seg ? -fy : 1e30f),
-                      row16_min(in_seg ? -fz : 1e30f)}, 0.0f};
-    box.reach2 = reach2_of(box, d.rlist_f);
+    const Box box = wbox[wv][g];
     // the first `count` kept candidates against the cluster's particles, 32 a
     // round (the particles themselves are among the first `own`)
     auto test = [&](int count, int own) {
       if (lane < 32) cand[wv][count + lane] = (uint16_t)kPad;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
+      float a0 = hc[q][cand[wv][p16]], a1 = hc[q][cand[wv][16 + p16]];
       for (int c0 = 0; c0 < count; c0 += 32) {
-        const int j0 = cand[wv][c0 + p16], j1 = cand[wv][c0 + 16 + p16];
         const uint2 e0 = *reinterpret_cast<const uint2*>(&cand[wv][c0 + 4 * q]);
         const uint2 e1 = *reinterpret_cast<const uint2*>(&cand[wv][c0 + 16 + 4 * q]);
         const uint16_t hv[8] = {(uint16_t)e0.x, (uint16_t)(e0.x >> 16), (uint16_t)e0.y, (uint16_t)(e0.y >> 16),
                                 (uint16_t)e1.x, (uint16_t)(e1.x >> 16), (uint16_t)e1.y, (uint16_t)(e1.y >> 16)};
-        const f32x4 w0 = __builtin_amdgcn_mfma_f32_16x16x4f32(hc[q][j0], bv, cv, 0, 0, 0);
-        const f32x4 w1 = __builtin_amdgcn_mfma_f32_16x16x4f32(hc[q][j1], bv, cv, 0, 0, 0);
+        const f32x4 w0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, bv, cv, 0, 0, 0);
+        const f32x4 w1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, bv, cv, 0, 0, 0);
+        const int cn = c0 + 32 < count ? c0 + 32 : c0;  // the next round's operands
+        a0 = hc[q][cand[wv][cn + p16]];
+        a1 = hc[q][cand[wv][cn + 16 + p16]];
         float rr[8] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3]};
         if (c0 < own) {
 #pragma unroll
