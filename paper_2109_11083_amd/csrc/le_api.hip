@@ -193,7 +193,8 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
   t.ctrl = (Ctrl*)take(2 * sizeof(Ctrl));
   t.flags = (Flags*)take(sizeof(Flags));
   t.vmax = (unsigned long long*)take(2 * kSlots * kLineU64 * sizeof(unsigned long long));
-  t.scan_status = (unsigned long long*)take((size_t)g.sp_blocks * sizeof(unsigned long long));
+  t.scan_status = (unsigned long long*)take((size_t)(g.sp_blocks + kLineU64) * sizeof(unsigned long long));
+  t.binned = t.scan_status + (g.sp_blocks + kLineU64 - 1);  // (a line's length from the first words)
   for (int b = 0; b < 2; ++b) {
     t.pos[b] = (double*)take(4 * np * sizeof(double));
     t.vel[b] = (double*)take(3 * np * sizeof(double));
@@ -228,6 +229,7 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
     d->flags = t.flags;
     d->vmax = t.vmax;
     d->scan_status = t.scan_status;
+    d->binned = t.binned;
     for (int b = 0; b < 2; ++b) {
       d->pos[b] = t.pos[b]; d->vel[b] = t.vel[b]; d->frc[b] = t.frc[b]; d->tag[b] = t.tag[b];
     }

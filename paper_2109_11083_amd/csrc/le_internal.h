@@ -36,6 +36,7 @@ constexpr int kSlots = 64;         // words (one per 128-byte line) a block maxi
 constexpr int kLineInts = 32;      // 32-bit words per 128-byte line
 constexpr int kLineU64 = 16;       // 64-bit words per 128-byte line
 constexpr int kSortParticles = 512;  // particles per block of the scan-and-permute pass (on average)
+constexpr int kSortOneLaunch = 65536;  // particles up to which a step sorts in one launch
 constexpr int kBinBlock = 2 * kBlock;  // particles per block of the binning pass (two per thread)
 
 // Mutable per-simulation scalars that live on the device so that a step
@@ -147,6 +148,7 @@ struct Dev {
   unsigned long long* vmax;
   unsigned long long* vmax_other;  // the speed-bound slots paired with ctrl_other
   unsigned long long* scan_status; // [sp_blocks] look-back words of the cell scan
+  unsigned long long* binned;      // blocks of a one-launch sort's binning that are done (zero between rebuilds)
   int32_t sp_cells, sp_blocks;     // cells per block of the scan-and-permute pass, and its blocks
   Flags* flags;
 };

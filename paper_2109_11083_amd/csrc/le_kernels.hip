@@ -184,6 +184,7 @@ __global__ void k_load_state(Dev d, const double* __restrict__ x0, const double*
     c->rebuild = 0;
     c->wraps = 0;
     d.flags->status = 0;
+    *d.binned = 0ull;
     for (int k = 0; k < kSlots * kLineInts; ++k) d.flags->max_nb_slot[k] = 0;
   }
   for (int k = i; k < kSlots * kLineU64; k += gridDim.x * blockDim.x) d.vmax[k] = 0ull;
@@ -260,10 +261,12 @@ __device__ __forceinline__ bool cross_wrap(const Dev& d, double Delta, double& x
 // within a wave take one atomic per run.  Reads positions and tags alone: the
 // crossing is applied where the particle is copied, (2); applied and written
 // here it cost the pass 12.6 instead of 9 us (400,000 beads).
-__device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict__ next,
-                                                 unsigned long long* __restrict__ next_vmax, int force,
-                                                 int control, int bid) {
-  __shared__ Ctrl sc;
+//
+// The control part: true on a rebuild, with the copies of the state being
+// binned (sc) and of the sorted one (sn) in shared memory.
+__device__ __forceinline__ bool sort_control(const Dev& d, Ctrl* __restrict__ next,
+                                             unsigned long long* __restrict__ next_vmax, int force, int control,
+                                             int bid, Ctrl& sc, Ctrl& sn) {
   __shared__ int go;
   if (threadIdx.x < 64) {
     // the drift's speed bound: max over the slot words (first wave)
@@ -277,23 +280,24 @@ __device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict_
     if (ok && control) control_advance(d, c, vb);
     const bool rb = ok && (force || c.rebuild);
     if (threadIdx.x == 0) {
-      sc = c;  // buffers and offset of the state being binned
+      sc = c;
+      c.rebuild = 0;
+      if (rb) rebuild_adopt(c, force != 0);
+      sn = c;
+      if (bid == 0) *next = c;
       go = rb ? 1 : 0;
     }
     if (bid == 0) {
       if (threadIdx.x < kSlots) next_vmax[threadIdx.x * kLineU64] = 0ull;
       if (rb)
         for (int k = threadIdx.x; k < kSlots * kLineInts; k += 64) d.flags->max_nb_slot[k] = 0;
-      if (threadIdx.x == 0) {
-        Ctrl o = c;
-        o.rebuild = 0;
-        if (rb) rebuild_adopt(o, force != 0);
-        *next = o;
-      }
     }
   }
   __syncthreads();
-  if (!go) return;
+  return go != 0;
+}
+
+__device__ __forceinline__ void bin_body(const Dev& d, const Ctrl& sc, int bid) {
   // the look-back words of the scan start cleared (spread over the blocks)
   const int nbb = (d.n + kBinBlock - 1) / kBinBlock;  // blocks of this pass
   for (int k = bid * kBlock + (int)threadIdx.x; k < d.sp_blocks; k += nbb * kBlock) d.scan_status[k] = 0ull;
@@ -332,16 +336,18 @@ __device__ __forceinline__ void control_bin_body(const Dev& d, Ctrl* __restrict_
 __global__ void __launch_bounds__(kBlock) k_control_bin(Dev d, Ctrl* __restrict__ next,
                                                         unsigned long long* __restrict__ next_vmax,
                                                         int force, int control) {
-  control_bin_body(d, next, next_vmax, force, control, blockIdx.x);
+  __shared__ Ctrl sc, sn;
+  if (sort_control(d, next, next_vmax, force, control, blockIdx.x, sc, sn)) bin_body(d, sc, blockIdx.x);
 }
 
 // Batched form: every simulation advances its step (control) and writes its
 // other control copy (named by its descriptor).
 __global__ void __launch_bounds__(kBlock) k_control_bin_b(Batch b) {
+  __shared__ Ctrl sc, sn;
   int sm, bid;
   locate(b, blockIdx.x, sm, bid);
   const Dev& d = stage_dev(b.dev[sm]);
-  control_bin_body(d, d.ctrl_other, d.vmax_other, 0, 1, bid);
+  if (sort_control(d, d.ctrl_other, d.vmax_other, 0, 1, bid, sc, sn)) bin_body(d, sc, bid);
 }
 
 // (2) One pass over the cells in blocks of sp_cells consecutive cells.  The
@@ -365,8 +371,7 @@ __device__ __forceinline__ unsigned long long scan_word(int flag, long long v) {
   return ((unsigned long long)flag << 62) | (unsigned long long)v;
 }
 
-__device__ __forceinline__ void scan_permute_body(const Dev& d, int b) {
-  if (rebuild_off(d)) return;
+__device__ __forceinline__ void scan_permute_body(const Dev& d, const Ctrl& cn, int b) {
   __shared__ int lpre[kBlock + 1];  // exclusive prefix of the block's counts, total last
   __shared__ int wsum[kBlock / 64];
   __shared__ long long base_sh;
@@ -442,9 +447,8 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, int b) {
   // the block's particles, two per thread and round (their loads overlap):
   // k-th cell of the block with lpre[k] <= f < lpre[k + 1], arrival rank
   // r = f - lpre[k]; the bucket entry holds the tag and the binned slot
-  const Ctrl* c = d.ctrl;
   const int np = d.np;
-  const int pd = c->pos_cur, ad = c->aux_cur;  // destination buffers
+  const int pd = cn.pos_cur, ad = cn.aux_cur;  // destination buffers
   const int ps = 1 - pd, as = 1 - ad;          // binned (source) buffers
   // the final slot (-1: none), binned slot and tag of the block's f-th particle
   auto locate_f = [&](int f, int& ns, int& src, int& tg) {
@@ -473,8 +477,8 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, int b) {
   };
   // The total forces move along only in a forced rebuild: one due within a
   // step call comes after the first half-kick, and the call's last step writes them anew.
-  const bool with_f = c->rebuild == kRebuildForced;
-  const double Delta = c->Delta;
+  const bool with_f = cn.rebuild == kRebuildForced;
+  const double Delta = cn.Delta;
   struct St { double4 p; double v0, v1, v2, f0, f1, f2; };
   auto load = [&](int i) -> St {
     const double* V = d.vel[as];
@@ -512,7 +516,10 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, int b) {
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_scan_permute(Dev d) { scan_permute_body(d, blockIdx.x); }
+__global__ void __launch_bounds__(kBlock) k_scan_permute(Dev d) {
+  if (rebuild_off(d)) return;
+  scan_permute_body(d, *d.ctrl, blockIdx.x);
+}
 
 // Batched form: the blocks of one simulation are consecutive in the grid, so
 // every block's predecessors were dispatched before it (the look-back waits
@@ -520,7 +527,46 @@ __global__ void __launch_bounds__(kBlock) k_scan_permute(Dev d) { scan_permute_b
 __global__ void __launch_bounds__(kBlock) k_scan_permute_b(Batch b) {
   int sm, bid;
   locate(b, blockIdx.x, sm, bid);
-  scan_permute_body(stage_dev(b.dev[sm]), bid);
+  const Dev& d = stage_dev(b.dev[sm]);
+  if (rebuild_off(d)) return;
+  scan_permute_body(d, *d.ctrl, bid);
+}
+
+// (1) and (2) in one launch: the blocks after the binning's wait until all of
+// those, dispatched before them, have counted themselves done, and then scan
+// and permute.  A step that rebuilds nothing pays one empty launch less (2.5
+// us); one that does pays the hand-over, a write-back and a refill of the L2s,
+// which grows with the system.
+__global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
+                                                 unsigned long long* __restrict__ next_vmax, int force,
+                                                 int control) {
+  __shared__ Ctrl sc, sn;
+  __shared__ int ready;
+  if (!sort_control(d, next, next_vmax, force, control, blockIdx.x, sc, sn)) return;
+  const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
+  if ((int)blockIdx.x < nbb) {
+    bin_body(d, sc, blockIdx.x);
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(d.binned, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  if (threadIdx.x == 0) {
+    // (the search sets the count back to zero)
+    const unsigned long long due = (unsigned long long)nbb;
+    long long spins = 0;
+    bool done = false, fault = false;
+    // (a block of the binning that finds a latched error counts nothing)
+    while (!(done = __hip_atomic_load(d.binned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= due) &&
+           !(fault = __hip_atomic_load(&d.flags->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) &&
+           ++spins < (1ll << 22))
+      __builtin_amdgcn_s_sleep(2);
+    if (!done && !fault) latch(d.flags, LE_E_STATE);
+    ready = done && __hip_atomic_load(&d.flags->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+  }
+  __syncthreads();
+  if (!ready) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  scan_permute_body(d, sn, (int)blockIdx.x - nbb);
 }
 
 // Neighbour lists of radius r_list through the Lees-Edwards cell stencil.
@@ -675,6 +721,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
   Ctrl* c = d.ctrl;
   const int np = d.np, n = d.n, cap = d.cap;
   const int s0 = tile * T;
+  if (tile == 0 && threadIdx.x == 0) *d.binned = 0ull;  // (k_sort's count, for the next rebuild)
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int pn = c->pos_cur, an = c->aux_cur;  // sorted buffers of the new state
   const double4* P = reinterpret_cast<const double4*>(d.pos[pn]);
@@ -2287,9 +2334,20 @@ hipError_t launch_rebuild(const Dev& d, Ctrl* next, unsigned long long* next_vma
   Dev dn = d;
   dn.ctrl = next;
   dn.vmax = next_vmax;
-  hipLaunchKernelGGL(k_control_bin, dim3((d.n + kBinBlock - 1) / kBinBlock), dim3(kBlock), 0, s, d, next, next_vmax,
-                     force ? 1 : 0, control ? 1 : 0);
-  hipLaunchKernelGGL(k_scan_permute, dim3(d.sp_blocks), dim3(kBlock), 0, s, dn);
+  const unsigned nbb = (d.n + kBinBlock - 1) / kBinBlock;
+  // One launch within the steps of up to kSortOneLaunch particles, measured per
+  // step: 65,536 lie between 64,000 LJ particles (32.2 with two launches, 31.4
+  // us with one; 50,000 beads 25.6 and 23.8, 1,000 particles 21.0 and 18.9) and
+  // 256,000 (62.2 and 66.1; 400,000 beads 64.6 and 79.3).  A forced rebuild has
+  // work for both (27,000 particles: 74 and 78 us), and so has a batch, where
+  // some member rebuilds on most steps (64 of them: 563 and 600 us).
+  if (!force && d.n <= kSortOneLaunch) {
+    hipLaunchKernelGGL(k_sort, dim3(nbb + d.sp_blocks), dim3(kBlock), 0, s, d, next, next_vmax, 0, control ? 1 : 0);
+  } else {
+    hipLaunchKernelGGL(k_control_bin, dim3(nbb), dim3(kBlock), 0, s, d, next, next_vmax, force ? 1 : 0,
+                       control ? 1 : 0);
+    hipLaunchKernelGGL(k_scan_permute, dim3(d.sp_blocks), dim3(kBlock), 0, s, dn);
+  }
   with_search_tiles(d, [&](auto t, auto gl) {
     using TC = decltype(t);
     hipLaunchKernelGGL((k_neighbors<TC, decltype(gl)::value>), dim3(d.ntiles), dim3(kSearchThreads), 0, s, dn);

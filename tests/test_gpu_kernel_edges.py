@@ -8,7 +8,7 @@ import pytest
 
 import oracle as O
 from paper_2109_11083_amd import inputs
-from paper_2109_11083_amd.sim import Params, Sim
+from paper_2109_11083_amd.sim import Params, Sim, step_batch
 
 pytestmark = pytest.mark.gpu
 
@@ -104,3 +104,24 @@ def test_list_search_and_forces_at_tile_edges(name, tune):
     Fr, Wr, _ = O.forces(xw, Delta, op)
     assert np.sqrt(((F - Fr) ** 2).sum(axis=0)).max() <= 1e-12 * np.sqrt((Fr ** 2).sum(axis=0).mean())
     assert np.abs(W - Wr).max() <= 1e-12 * np.abs(Wr[:3]).max()
+
+
+# the sort in one launch within a step (up to 65,536 particles) and the two
+# launches of a batch and of larger systems: whole binning blocks of 512, one
+# more, the last size of the one launch and the first of the two.  The same
+# arithmetic, so the states are equal bit for bit, also when calls alternate.
+@pytest.mark.parametrize("n", [512, 1025, 65536, 65537])
+def test_sort_in_one_launch_and_in_two(n):
+    w, p = _lj(n, 0.3, 7, skin=0.3)
+    a, b = Sim(p, w.x, w.u), Sim(p, w.x, w.u)
+    for k in range(4):
+        a.step(6)
+        if k % 2 == 0:
+            step_batch([b], 6)
+        else:
+            b.step(6)
+    (xa, ua, fa, _), (xb, ub, fb, _) = a.state(), b.state()
+    assert a.stats() == b.stats() and a.stats()["rebuilds"] > 1
+    assert np.array_equal(xa, xb) and np.array_equal(ua, ub) and np.array_equal(fa, fb)
+    a.close()
+    b.close()
