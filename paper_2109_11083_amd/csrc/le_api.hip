@@ -201,7 +201,7 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
     t.frc[b] = (double*)take(3 * np * sizeof(double));
     t.tag[b] = (int32_t*)take(np * sizeof(int32_t));
   }
-  t.vt = (p->thermostat == LE_THERMO_DPD) ? (double*)take(4 * np * sizeof(double)) : nullptr;
+  t.vt = (p->thermostat == LE_THERMO_DPD) ? (VtRec*)take(np * sizeof(VtRec)) : nullptr;
   t.slot_of_tag = (int32_t*)take(np * sizeof(int32_t));
   {
     // the buckets of the sort and the halo tables of the lists (see Dev::halo)

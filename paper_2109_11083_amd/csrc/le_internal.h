@@ -67,6 +67,9 @@ struct alignas(64) Flags {
   int32_t max_nb_slot[kSlots * kLineInts];
 };
 
+// One 32-byte gather of a DPD partner.
+struct alignas(32) VtRec { double x, y, z; int32_t tag, pad; };
+
 // Everything a kernel needs, passed by value.
 struct Dev {
   // geometry and physics
@@ -115,7 +118,7 @@ struct Dev {
   double* pos[2];                  // double4 [np] each (x, y, z, wrap counts along y and z)
   double* vel[2];                  // [3][np]
   double* frc[2];                  // [3][np] total force of the current step
-  double* vt;                      // DPD only: double4 [np] (u_x, u_y, u_z, tag) of the current slots,
+  VtRec* vt;                       // DPD only: [np] velocity and tag of the current slots,
                                    // packed before each force evaluation (one gather per partner)
   int32_t* tag[2];                 // slot -> tag
   int32_t* slot_of_tag;            // tag -> slot

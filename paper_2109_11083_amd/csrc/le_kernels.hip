@@ -139,14 +139,15 @@ __device__ __forceinline__ void philox(uint32_t c[4], uint32_t k0, uint32_t k1) 
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c[2];
     uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
     uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-    uint32_t n0 = hi1 ^ c[1] ^ k0;
-    uint32_t n2 = hi0 ^ c[3] ^ k1;
+    // (the three-input exclusive or, one instruction instead of two)
+    uint32_t n0 = __builtin_amdgcn_bitop3_b32(hi1, c[1], k0, 0x96);
+    uint32_t n2 = __builtin_amdgcn_bitop3_b32(hi0, c[3], k1, 0x96);
     c[0] = n0; c[1] = lo1; c[2] = n2; c[3] = lo0;
   }
 }
 
 __device__ __forceinline__ double u01c(uint32_t r) {
-  return ((double)r + 0.5) * (1.0 / 4294967296.0) - 0.5;
+  return fma((double)r, 1.0 / 4294967296.0, 0.5 / 4294967296.0 - 0.5);  // (exact)
 }
 
 // ---------------------------------------------------------- state loading
@@ -1447,22 +1448,16 @@ __device__ __forceinline__ void angle_cos(const double b1[3], const double b2[3]
 __device__ __forceinline__ void dpd_pair(const Dev& d, uint32_t s_lo, uint32_t s_hi, int ti, int tj,
                                          double vx, double vy, double vz, double dx, double dy,
                                          double dz, double r2, double& ax, double& ay, double& az) {
-  const bool in = r2 < d.dpd_rc2;
-  // 1/r from the hardware reciprocal square root and two Newton steps
-  // (within 2 ulp of the quotient), then r = r2 / r: the IEEE square root and
-  // division cost the pair about 14 instructions more
-  const double h = 0.5 * r2;
+  // 1/r from the hardware reciprocal square root (within 2^-22) and one
+  // third-order step (its residual e leaves e^3), then r = r2 / r
   double ir = __builtin_amdgcn_rsq(r2);
-  ir = ir * fma(-h * ir, ir, 1.5);
-  ir = ir * fma(-h * ir, ir, 1.5);
-  const double r = r2 * ir;
-  const double wgt = 1.0 - r * d.dpd_inv_rc;
-  double ev = dx * vx + dy * vy;
-  ev = (ev + dz * vz) * ir;
+  const double e = fma(-(r2 * ir), ir, 1.0);
+  ir = fma(ir * e, fma(e, 0.375, 0.5), ir);
+  const double wgt = fmax(fma(-(r2 * ir), d.dpd_inv_rc, 1.0), 0.0);
+  const double ev = fma(dz, vz, fma(dy, vy, dx * vx)) * ir;
   uint32_t c[4] = {s_lo, s_hi, (uint32_t)min(ti, tj), (uint32_t)max(ti, tj)};
   philox(c, d.seed_lo, d.dpd_key_hi);
-  double f = (-d.dpd_gamma * wgt * wgt * ev + d.dpd_pref * wgt * u01c(c[0])) * ir;
-  f = in ? f : 0.0;
+  const double f = (wgt * ir) * fma(-(d.dpd_gamma * wgt), ev, d.dpd_pref * u01c(c[0]));
   ax = fma(f, dx, ax); ay = fma(f, dy, ay); az = fma(f, dz, az);
 }
 
@@ -1623,7 +1618,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   double w[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   const double4 pi = valid ? pi_ld : make_double4(0.0, 0.0, 0.0, 0.0);
   const uint32_t st_lo = (uint32_t)(uint64_t)c->step, st_hi = (uint32_t)((uint64_t)c->step >> 32);
-  const double4* __restrict__ VT = reinterpret_cast<const double4*>(d.vt);
+  const VtRec* __restrict__ VT = d.vt;
   if (valid) {
     // staged partners (already shifted to their image): the particle's list is
     // a sequence of blocks of 4, of which this thread takes blocks half, half +
@@ -1687,7 +1682,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
 #pragma unroll
       for (int u = 0; u < 4 * GB; ++u) pj[u] = P[sl[u]];
       // DPD: the partners' velocities and tags, one 32-byte gather each
-      double4 vj[DPD ? 4 * GB : 1];
+      VtRec vj[DPD ? 4 * GB : 1];
       if (DPD) {
 #pragma unroll
         for (int u = 0; u < 4 * GB; ++u) vj[u] = VT[sl[u]];
@@ -1695,21 +1690,39 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
         // fence the scheduler sinks each to its use, one wait per gather)
         __builtin_amdgcn_sched_barrier(0);
       }
+      // four at a time: displacements, less the image shifts where any lane has
+      // one (most waves are away from the faces); a DPD image s_y boxes up
+      // streams faster by s_y gamma_dot L_y
 #pragma unroll
-      for (int u = 0; u < 4 * GB; ++u) {
-        int sx, sy, sz;
-        unpack_img((uint8_t)(cq[u >> 2] >> (8 * (u & 3))), sx, sy, sz);
-        sx += sy * W;
-        double dy = (pi.y - pj[u].y) - (double)sy * d.Ly;
-        double dx = ((pi.x - pj[u].x) - (double)sy * Delta) - (double)sx * d.Lx;
-        double dz = (pi.z - pj[u].z) - (double)sz * d.Lz;
-        const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        add_pair<VIR>(lj_masked<MIXED, CAP>(d, r2), dx, dy, dz, fx, fy, fz, w);
-        if (DPD) {
-          // the image s_y boxes up streams faster by s_y gamma_dot L_y
-          const double vx = (u0_ld - vj[u].x) - (double)sy * d.sv;
-          dpd_pair(d, st_lo, st_hi, tag_ld, (int)vj[u].w, vx, u1_ld - vj[u].y, u2_ld - vj[u].z,
-                   dx, dy, dz, r2, gx, gy, gz);
+      for (int k = 0; k < GB; ++k) {
+        double dx[4], dy[4], dz[4], vx[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double4 p = pj[4 * k + u];
+          dx[u] = pi.x - p.x; dy[u] = pi.y - p.y; dz[u] = pi.z - p.z;
+          vx[u] = DPD ? u0_ld - vj[DPD ? 4 * k + u : 0].x : 0.0;
+        }
+        if (__any(cq[k] != 0x01010101u * pack_img(0, 0, 0))) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            int sx, sy, sz;
+            unpack_img((uint8_t)(cq[k] >> (8 * u)), sx, sy, sz);
+            sx += sy * W;
+            dy[u] = dy[u] - (double)sy * d.Ly;
+            dx[u] = (dx[u] - (double)sy * Delta) - (double)sx * d.Lx;
+            dz[u] = dz[u] - (double)sz * d.Lz;
+            if (DPD) vx[u] = vx[u] - (double)sy * d.sv;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const double r2 = fma(dz[u], dz[u], fma(dy[u], dy[u], dx[u] * dx[u]));
+          add_pair<VIR>(lj_masked<MIXED, CAP>(d, r2), dx[u], dy[u], dz[u], fx, fy, fz, w);
+          if (DPD) {
+            const VtRec v = vj[DPD ? 4 * k + u : 0];
+            dpd_pair(d, st_lo, st_hi, tag_ld, v.tag, vx[u], u1_ld - v.y, u2_ld - v.z, dx[u], dy[u], dz[u], r2, gx,
+                     gy, gz);
+          }
         }
       }
     }
@@ -1881,7 +1894,10 @@ __global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, (TC:
 // 0.699 ms per step; the KG melts of the global layout gain nothing from it).
 // Plain DPD steps (global layout, no stress sample): held to 168 VGPRs, three
 // waves per SIMD instead of two, which the kernel reaches without spills (the
-// sampling variant would spill, so it keeps the plain bound).
+// sampling variant would spill, so it keeps the plain bound).  Three-input
+// exclusive ors in the generator, fused multiply-adds in the pair terms and image
+// shifts only where a wave has some took a vector instruction in five out
+// (256,000 LJ particles: 120 -> 113 us); what is left is the gathers.
 template <bool MIXED, bool BONDS>
 __global__ void __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(3)))
     k_force_dpd(Dev d, double* __restrict__ f_out, double* __restrict__ sample_out) {
@@ -1904,12 +1920,12 @@ __device__ __forceinline__ void pack_vt_body(const Dev& d, int bid) {
   const Ctrl* c = d.ctrl;
   const int i = bid * kBlock + threadIdx.x;
   const int np = d.np;
-  double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
+  VtRec v = {0.0, 0.0, 0.0, 0, 0};
   if (i < d.n) {
     const double* U = d.vel[c->aux_cur];
-    v = make_double4(U[i], U[np + i], U[2 * np + i], (double)d.tag[c->aux_cur][i]);
+    v = VtRec{U[i], U[np + i], U[2 * np + i], d.tag[c->aux_cur][i], 0};
   }
-  if (i <= d.n) reinterpret_cast<double4*>(d.vt)[i] = v;
+  if (i <= d.n) d.vt[i] = v;
 }
 
 __global__ void __launch_bounds__(kBlock) k_pack_vt(Dev d) { pack_vt_body(d, blockIdx.x); }
