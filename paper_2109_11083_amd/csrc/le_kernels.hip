@@ -1507,6 +1507,11 @@ __device__ __forceinline__ void block_partials(double* vals, double* out, int lb
 // plain step from 43 to 36.5 us for 256,000 LJ particles and, against gathers from
 // global memory, from 37 to 26.7 us for 400,000 beads (traced); it is bound by the vector unit's
 // issue (53% busy) and the waves' imbalance, six waves per SIMD in 80 registers.
+// DPD steps with the halo gather the velocities (from vt, with the slots kept
+// in LDS beside the positions) of the partners within the DPD cutoff alone: all
+// from memory, four gathers per entry, the kernel waited for them (256,000 LJ
+// particles: 113 -> 93 us; 2000 49 -> 29 us per step), four waves per SIMD in 128
+// registers, two blocks of 57 KB LDS per CU.
 // Without the halo the launch bound of four tiles per block makes the
 // compiler keep fewer registers (more waves; DPD 138 -> 132 us); the launch
 // itself uses one tile.
@@ -1516,7 +1521,6 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   static_assert(!CAP || (!STAGED && !MIXED && MODE != kDpdForce), "capped forces: FP64, global layout");
   constexpr bool VIR = SAMPLE || (MODE == kForcesOnly);
   constexpr bool DPD = MODE == kDpdForce;
-  static_assert(!DPD || !STAGED, "DPD partners come from global memory");
   constexpr int kTh = TC::kForceThreads;                // threads per block
   const int kP = STAGED ? d.tile : kTile;               // particles per block (a power of 2)
   const int TPP = STAGED ? kTh / kP : 1;                // threads per particle
@@ -1528,6 +1532,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   double* const hx = hbuf;
   double* const hy = hbuf + kH;
   double* const hz = hbuf + 2 * kH;
+  __shared__ uint32_t hent[DPD && STAGED ? kH : 1];  // slot and image of every staged position
   __shared__ int skip;
   Ctrl* c = d.ctrl;
   if (threadIdx.x == 0) skip = d.flags->status;
@@ -1604,13 +1609,17 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
         hx[h] = pj[u].x;
         hy[h] = pj[u].y;
         hz[h] = pj[u].z;
+        if (DPD) hent[h] = ent[u];
       }
     };
     stage(std::integral_constant<int, 0>{}, std::integral_constant<int, U0>{}, true);
     if constexpr (U > U0) {
       if (nst > U0 * kTh) stage(std::integral_constant<int, U0>{}, std::integral_constant<int, U>{}, false);
     }
-    if (threadIdx.x == 0) { hx[HALO] = 1e100; hy[HALO] = 1e100; hz[HALO] = 1e100; }
+    if (threadIdx.x == 0) {
+      hx[HALO] = 1e100; hy[HALO] = 1e100; hz[HALO] = 1e100;
+      if (DPD) hent[HALO] = sent;
+    }
     __syncthreads();
   }
   double fx = 0.0, fy = 0.0, fz = 0.0;
@@ -1631,11 +1640,48 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
       double xj[4], yj[4], zj[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) { xj[u] = hx[j[u]]; yj[u] = hy[j[u]]; zj[u] = hz[j[u]]; }
+      if constexpr (DPD && STAGED) {
+        // the velocities of the partners within the DPD cutoff are gathered (of
+        // the others the sentinel's: one line for all) while the conservative
+        // force is computed
+        double dx[4], dy[4], dz[4], r2[4];
+        uint32_t ej[4];
+        VtRec vj[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        double dx = pi.x - xj[u], dy = pi.y - yj[u], dz = pi.z - zj[u];
-        const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        add_pair<VIR>(lj_masked<MIXED>(d, r2), dx, dy, dz, fx, fy, fz, w);
+        for (int u = 0; u < 4; ++u) ej[u] = hent[j[u]];
+        bool image = false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          dx[u] = pi.x - xj[u]; dy[u] = pi.y - yj[u]; dz[u] = pi.z - zj[u];
+          r2[u] = fma(dz[u], dz[u], fma(dy[u], dy[u], dx[u] * dx[u]));
+          vj[u] = VT[r2[u] < d.dpd_rc2 ? ej[u] & kSlotMask : (uint32_t)d.n];
+          image |= ej[u] >> kSlotBits != pack_img(0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          add_pair<VIR>(lj_masked<MIXED>(d, r2[u]), dx[u], dy[u], dz[u], fx, fy, fz, w);
+        double vx[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) vx[u] = u0_ld - vj[u].x;
+        if (__any(image)) {  // the image s_y boxes up streams faster by s_y gamma_dot L_y
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            int sx, sy, sz;
+            unpack_img((uint8_t)(ej[u] >> kSlotBits), sx, sy, sz);
+            vx[u] = vx[u] - (double)sy * d.sv;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          dpd_pair(d, st_lo, st_hi, tag_ld, vj[u].tag, vx[u], u1_ld - vj[u].y, u2_ld - vj[u].z, dx[u], dy[u], dz[u],
+                   r2[u], gx, gy, gz);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          double dx = pi.x - xj[u], dy = pi.y - yj[u], dz = pi.z - zj[u];
+          const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+          add_pair<VIR>(lj_masked<MIXED>(d, r2), dx, dy, dz, fx, fy, fz, w);
+        }
       }
       t0 = t1;
       t1 = t2;
@@ -1654,7 +1700,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
     // GB blocks of 4 per round: one for the plain global layout (fewer
     // gathers in flight leave room for more waves: KG 49 -> 48 us), two with
     // the halo's remainder pieces and with DPD (one block: 138 -> 195 us)
-    constexpr int GB = DPD ? 2 : 1;
+    constexpr int GB = DPD && !STAGED ? 2 : 1;
     uint4 jn[GB];
 #pragma unroll
     for (int k = 0; k < GB; ++k) jn[k] = l4[ooff(half * GB + k)];
@@ -1784,6 +1830,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
       }
     }
   }
+  if (DPD) { fx += gx; fy += gy; fz += gz; }
   if (STAGED) {
     // the other threads of each particle hand over their partial sums (the
     // halo array is free once every thread has left the pair loops); the
@@ -1823,7 +1870,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   } else if (DPD) {
     if (ep) {
       double* F = d.frc[ac];
-      F[i] = fx + gx; F[np + i] = fy + gy; F[2 * np + i] = fz + gz;
+      F[i] = fx; F[np + i] = fy; F[2 * np + i] = fz;
     }
   } else if (ep) {
     double* U = d.vel[ac];
@@ -1879,8 +1926,15 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
   }
 }
 
+// Waves per SIMD that the halo kernels are compiled for: six in 80 registers
+// (plain steps), four in 128 (DPD).
+constexpr int force_waves(int mode, int halo, bool sample) {
+  if (halo == 0) return 1;
+  return mode == kDpdForce ? 4 : (sample || mode == kForcesOnly ? 1 : 6);
+}
+
 template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
-__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, (TC::HALO && !SAMPLE && MODE != kForcesOnly) ? 6 : 1)
+__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, force_waves(MODE, TC::HALO, SAMPLE))
     k_force(Dev d, double* __restrict__ f_out, double* __restrict__ sample_out) {
   (void)sample_out;
   force_body<MODE, MIXED, BONDS, SAMPLE, TC, CAP>(d, xcd_block(d.nblocks), f_out);
@@ -1892,12 +1946,9 @@ __global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, (TC:
 // region); LDS halo: runs of 16 tiles dealt round-robin to the XCDs, which
 // evens out members of unequal cost per tile (64-request batch 0.711 ->
 // 0.699 ms per step; the KG melts of the global layout gain nothing from it).
-// Plain DPD steps (global layout, no stress sample): held to 168 VGPRs, three
+// Plain DPD steps of the global layout (no stress sample): held to 168 VGPRs, three
 // waves per SIMD instead of two, which the kernel reaches without spills (the
-// sampling variant would spill, so it keeps the plain bound).  Three-input
-// exclusive ors in the generator, fused multiply-adds in the pair terms and image
-// shifts only where a wave has some took a vector instruction in five out
-// (256,000 LJ particles: 120 -> 113 us); what is left is the gathers.
+// sampling variant would spill, so it keeps the plain bound).
 template <bool MIXED, bool BONDS>
 __global__ void __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(3)))
     k_force_dpd(Dev d, double* __restrict__ f_out, double* __restrict__ sample_out) {
@@ -1905,7 +1956,7 @@ __global__ void __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(
   force_body<kDpdForce, MIXED, BONDS, false, TileNone, false>(d, xcd_block(d.nblocks), f_out);
 }
 template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
-__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, (TC::HALO && !SAMPLE) ? 6 : 1) k_force_b(Batch b) {
+__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, force_waves(MODE, TC::HALO, SAMPLE)) k_force_b(Batch b) {
   int sm, lb;
   const int g = TC::kSpread ? xcd_spread<16>((int)blockIdx.x, (int)gridDim.x) : xcd_map((int)blockIdx.x, (int)gridDim.x);
   locate(b, g, sm, lb);
@@ -2434,10 +2485,10 @@ hipError_t launch_force(const Dev& d, hipStream_t s, ForceMode mode, bool sample
       else launch_force_t<kStepFused, false>(d, s, f_out, nullptr, e0, e1);
       break;
     case kDpdForce:
-      if (d.staged || !d.vt) return hipErrorInvalidValue;  // DPD partners come from global memory
+      if (!d.vt) return hipErrorInvalidValue;
       hipLaunchKernelGGL(k_pack_vt, dim3(blocks_for(d.n + 1)), dim3(kBlock), 0, s, d);
-      if (sample) launch_force_s<kDpdForce, true, TileNone>(d, s, f_out, sample_out, e0, e1);
-      else launch_force_s<kDpdForce, false, TileNone>(d, s, f_out, nullptr, e0, e1);
+      if (sample) launch_force_t<kDpdForce, true>(d, s, f_out, sample_out, e0, e1);
+      else launch_force_t<kDpdForce, false>(d, s, f_out, nullptr, e0, e1);
       break;
   }
   return hipGetLastError();
@@ -2570,10 +2621,10 @@ hipError_t launch_force_b(const Batch& blk_cur, const Batch& par_cur, const Dev&
       else launch_force_bt<kStepFused, false>(blk_cur, cfg, s);
       break;
     case kDpdForce:
-      if (cfg.staged || !cfg.vt) return hipErrorInvalidValue;
+      if (!cfg.vt) return hipErrorInvalidValue;
       hipLaunchKernelGGL(k_pack_vt_b, grid_of(par_cur), dim3(kBlock), 0, s, par_cur);
-      if (sample) launch_force_bs<kDpdForce, true, TileNone>(blk_cur, cfg, s);
-      else launch_force_bs<kDpdForce, false, TileNone>(blk_cur, cfg, s);
+      if (sample) launch_force_bt<kDpdForce, true>(blk_cur, cfg, s);
+      else launch_force_bt<kDpdForce, false>(blk_cur, cfg, s);
       break;
     default:
       return hipErrorInvalidValue;  // the other modes are not batched

@@ -125,3 +125,26 @@ def test_sort_in_one_launch_and_in_two(n):
     assert np.array_equal(xa, xb) and np.array_equal(ua, ub) and np.array_equal(fa, fb)
     a.close()
     b.close()
+
+
+# DPD partners from the LDS halo against partners from global memory: a ragged
+# small tile, the first size of large tiles, beads with bonds, and rows of a
+# stencil beyond what the halo holds.  The two differ by the rounding of the
+# coordinates' images: a few 1e-16 of the box (20 to 25) against distances of
+# 0.5 and more in forces up to r^-13, 1e-12 of the largest force; mixed
+# precision evaluates the pair force in FP32, 1e-5.
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("mixed", 1e-5)])
+@pytest.mark.parametrize("name", ["lj_1009", "lj_10001", "kg_12000_wide", "slab"])
+def test_dpd_forces_from_the_halo_and_from_memory(name, precision, tol):
+    x, kw = SEARCH[name](3)
+    u = np.random.default_rng(8).normal(size=x.shape)
+    out = []
+    for tune in (0, 2):
+        p = Params(shear_rate=0.2, seed=3, tune=tune, thermostat="dpd", gamma=5.0, precision=precision,
+                   **{"rc": 2.5, "skin": 0.3, **kw})
+        sim = Sim(p, x, u, step0=1237)
+        out.append(sim.state())
+        sim.close()
+    (xa, ua, fa, _), (xb, ub, fb, _) = out
+    assert np.array_equal(xa, xb) and np.array_equal(ua, ub)
+    assert np.abs(fa - fb).max() <= tol * np.abs(fb).max()
