@@ -82,12 +82,22 @@ void plan_tiles(const le_params* p, Geometry* g, double list_pp) {
   const double cell_n = (double)p->n / ((double)g->nc[0] * g->nc[1] * g->nc[2]);
   const bool small = p->n <= (list_pp >= kDensePartners ? kSmallDense : kSmallSparse);
   g->tile = small ? kTileSmall : kTile;
-  double best = 0.0;
+  // The beams of the smallest halo; first among those whose narrower beams at the
+  // box's upper faces (but the last, in the corner) hold two tiles, so that no
+  // tile lies in three even where the density varies: its rows would be walked in
+  // memory (random-walk melts of 3000 and 6000 beads: 85 instead of 58 us an evaluation).
+  double best = 0.0, least = 1e300;
+  bool best_fits = false;
   for (int b = 0; b < 4; ++b)
     for (int a = 0; a < 4; ++a) {
-      const double h = tile_halo(*g, cell_n, g->tile, 1 << a, 1 << b, 3.0);
-      if ((a == 0 && b == 0) || h < best) {
-        best = h;
+      const int h = std::min(1 << a, (int)g->nc[1]), w = std::min(1 << b, (int)g->nc[2]);
+      const int hr = g->nc[1] % h ? g->nc[1] % h : h, wr = g->nc[2] % w ? g->nc[2] % w : w;
+      const bool fits = std::min(hr * w, h * wr) * cell_n * g->nc[0] >= 2.0 * g->tile;
+      const double halo = tile_halo(*g, cell_n, g->tile, 1 << a, 1 << b, 3.0);
+      least = std::min(least, halo);
+      if ((a == 0 && b == 0) || fits > best_fits || (fits == best_fits && halo < best)) {
+        best = halo;
+        best_fits = fits;
         g->by_sh = a;
         g->bz_sh = b;
       }
@@ -98,7 +108,7 @@ void plan_tiles(const le_params* p, Geometry* g, double list_pp) {
   g->halo_cap = g->tiles == kTilesSparse ? TileSparse::HALO : TileDense::HALO;
   // LDS halo at force time when partners per particle clearly outnumber the
   // positions a tile must stage per particle
-  const double halo_pp = best / g->tile;
+  const double halo_pp = least / g->tile;
   // (a small dense system always: it has few tiles, and 1000 particles take 8 us a
   // force evaluation with the halo, 19 without).  The same line with DPD: per step
   // 30,000 LJ particles take 37 with the halo and 51 us without, 256,000 take 126
@@ -196,7 +206,7 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
   t.flags = (Flags*)take(sizeof(Flags));
   t.vmax = (unsigned long long*)take(2 * kSlots * kLineU64 * sizeof(unsigned long long));
   t.scan_status = (unsigned long long*)take((size_t)(g.sp_blocks + kLineU64) * sizeof(unsigned long long));
-  t.binned = t.scan_status + (g.sp_blocks + kLineU64 - 1);  // (a line's length from the first words)
+  t.joined = t.scan_status + (g.sp_blocks + kLineU64 - 3);  // (behind the words of the scan)
   for (int b = 0; b < 2; ++b) {
     t.pos[b] = (double*)take(4 * np * sizeof(double));
     t.vel[b] = (double*)take(3 * np * sizeof(double));
@@ -231,7 +241,7 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
     d->flags = t.flags;
     d->vmax = t.vmax;
     d->scan_status = t.scan_status;
-    d->binned = t.binned;
+    d->joined = t.joined;
     for (int b = 0; b < 2; ++b) {
       d->pos[b] = t.pos[b]; d->vel[b] = t.vel[b]; d->frc[b] = t.frc[b]; d->tag[b] = t.tag[b];
     }

@@ -28,7 +28,8 @@ struct TileSparse { static constexpr int HALO = 1024, kForceThreads = 256; stati
 struct TileDenseGlobal { static constexpr int HALO = 2048; };
 struct TileNone { static constexpr int HALO = 0, kForceThreads = kTile; static constexpr bool kSpread = false; };
 enum { kTilesDense = 0, kTilesSparse = 1 };
-constexpr int kCells = 512;        // cells a tile's halo may have (entries of the staging table)
+constexpr int kCells = 1024;       // cells a tile's halo may have (staging table; 512 were too few for melts of
+                                   // uneven density: 30,000 beads 96 instead of 60 us an evaluation)
 constexpr int kPlainBatch = 8;     // padding of the lists of LDS indices (one 16-byte block)
 constexpr int kOtherBatch = 4;     // padding of the lists of global slots
 constexpr int kStressComps = 12;   // 6 kinetic + 6 virial partial sums per block
@@ -36,7 +37,8 @@ constexpr int kSlots = 64;         // words (one per 128-byte line) a block maxi
 constexpr int kLineInts = 32;      // 32-bit words per 128-byte line
 constexpr int kLineU64 = 16;       // 64-bit words per 128-byte line
 constexpr int kSortParticles = 512;  // particles per block of the scan-and-permute pass (on average)
-constexpr int kSortOneLaunch = 65536;  // particles up to which a step sorts in one launch
+// particles up to which a step rebuilds in one launch, and sorts in one
+constexpr int kOneLaunch = 20000, kSortOneLaunch = 65536;
 constexpr int kBinBlock = 2 * kBlock;  // particles per block of the binning pass (two per thread)
 
 // Mutable per-simulation scalars that live on the device so that a step
@@ -151,7 +153,7 @@ struct Dev {
   unsigned long long* vmax;
   unsigned long long* vmax_other;  // the speed-bound slots paired with ctrl_other
   unsigned long long* scan_status; // [sp_blocks] look-back words of the cell scan
-  unsigned long long* binned;      // blocks of a one-launch sort's binning that are done (zero between rebuilds)
+  unsigned long long* joined;      // [3] blocks done of kernels in one launch (zero between rebuilds)
   int32_t sp_cells, sp_blocks;     // cells per block of the scan-and-permute pass, and its blocks
   Flags* flags;
 };

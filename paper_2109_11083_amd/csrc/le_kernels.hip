@@ -185,7 +185,7 @@ __global__ void k_load_state(Dev d, const double* __restrict__ x0, const double*
     c->rebuild = 0;
     c->wraps = 0;
     d.flags->status = 0;
-    *d.binned = 0ull;
+    d.joined[0] = d.joined[1] = d.joined[2] = 0ull;
     for (int k = 0; k < kSlots * kLineInts; ++k) d.flags->max_nb_slot[k] = 0;
   }
   for (int k = i; k < kSlots * kLineU64; k += gridDim.x * blockDim.x) d.vmax[k] = 0ull;
@@ -298,12 +298,13 @@ __device__ __forceinline__ bool sort_control(const Dev& d, Ctrl* __restrict__ ne
   return go != 0;
 }
 
+template <int TH>
 __device__ __forceinline__ void bin_body(const Dev& d, const Ctrl& sc, int bid) {
   // the look-back words of the scan start cleared (spread over the blocks)
   const int nbb = (d.n + kBinBlock - 1) / kBinBlock;  // blocks of this pass
-  for (int k = bid * kBlock + (int)threadIdx.x; k < d.sp_blocks; k += nbb * kBlock) d.scan_status[k] = 0ull;
-  for (int rd = 0; rd < kBinBlock / kBlock; ++rd) {
-    const int i = bid * kBinBlock + rd * kBlock + (int)threadIdx.x;
+  for (int k = bid * TH + (int)threadIdx.x; k < d.sp_blocks; k += nbb * TH) d.scan_status[k] = 0ull;
+  for (int rd = 0; rd < kBinBlock / TH; ++rd) {
+    const int i = bid * kBinBlock + rd * TH + (int)threadIdx.x;
     int cell = -1, tg = 0;
     if (i < d.n) {
       tg = d.tag[sc.aux_cur][i];
@@ -338,7 +339,7 @@ __global__ void __launch_bounds__(kBlock) k_control_bin(Dev d, Ctrl* __restrict_
                                                         unsigned long long* __restrict__ next_vmax,
                                                         int force, int control) {
   __shared__ Ctrl sc, sn;
-  if (sort_control(d, next, next_vmax, force, control, blockIdx.x, sc, sn)) bin_body(d, sc, blockIdx.x);
+  if (sort_control(d, next, next_vmax, force, control, blockIdx.x, sc, sn)) bin_body<kBlock>(d, sc, blockIdx.x);
 }
 
 // Batched form: every simulation advances its step (control) and writes its
@@ -348,7 +349,7 @@ __global__ void __launch_bounds__(kBlock) k_control_bin_b(Batch b) {
   int sm, bid;
   locate(b, blockIdx.x, sm, bid);
   const Dev& d = stage_dev(b.dev[sm]);
-  if (sort_control(d, d.ctrl_other, d.vmax_other, 0, 1, bid, sc, sn)) bin_body(d, sc, bid);
+  if (sort_control(d, d.ctrl_other, d.vmax_other, 0, 1, bid, sc, sn)) bin_body<kBlock>(d, sc, bid);
 }
 
 // (2) One pass over the cells in blocks of sp_cells consecutive cells.  The
@@ -372,9 +373,10 @@ __device__ __forceinline__ unsigned long long scan_word(int flag, long long v) {
   return ((unsigned long long)flag << 62) | (unsigned long long)v;
 }
 
+template <int TH>
 __device__ __forceinline__ void scan_permute_body(const Dev& d, const Ctrl& cn, int b) {
   __shared__ int lpre[kBlock + 1];  // exclusive prefix of the block's counts, total last
-  __shared__ int wsum[kBlock / 64];
+  __shared__ int wsum[TH / 64];
   __shared__ long long base_sh;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int c0 = b * d.sp_cells;
@@ -388,7 +390,7 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, const Ctrl& cn, 
   if (lane == 63) wsum[wid] = incl;
   __syncthreads();
   int woff = 0, agg = 0;
-  for (int w = 0; w < kBlock / 64; ++w) {
+  for (int w = 0; w < TH / 64; ++w) {
     if (w < wid) woff += wsum[w];
     agg += wsum[w];
   }
@@ -507,10 +509,10 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, const Ctrl& cn, 
     d.tag[ad][ns] = tg;
     d.slot_of_tag[tg] = ns;
   };
-  for (int f0 = threadIdx.x; f0 < agg; f0 += 2 * kBlock) {
+  for (int f0 = threadIdx.x; f0 < agg; f0 += 2 * TH) {
     int ns0, src0, tg0, ns1, src1, tg1;
     locate_f(f0, ns0, src0, tg0);
-    locate_f(f0 + kBlock, ns1, src1, tg1);
+    locate_f(f0 + TH, ns1, src1, tg1);
     const St a0 = load(src0), a1 = load(src1);  // (slot 0 for an empty lane: in bounds, not stored)
     store(ns0, tg0, a0);
     store(ns1, tg1, a1);
@@ -519,7 +521,7 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, const Ctrl& cn, 
 
 __global__ void __launch_bounds__(kBlock) k_scan_permute(Dev d) {
   if (rebuild_off(d)) return;
-  scan_permute_body(d, *d.ctrl, blockIdx.x);
+  scan_permute_body<kBlock>(d, *d.ctrl, blockIdx.x);
 }
 
 // Batched form: the blocks of one simulation are consecutive in the grid, so
@@ -530,34 +532,22 @@ __global__ void __launch_bounds__(kBlock) k_scan_permute_b(Batch b) {
   locate(b, blockIdx.x, sm, bid);
   const Dev& d = stage_dev(b.dev[sm]);
   if (rebuild_off(d)) return;
-  scan_permute_body(d, *d.ctrl, bid);
+  scan_permute_body<kBlock>(d, *d.ctrl, bid);
 }
 
-// (1) and (2) in one launch: the blocks after the binning's wait until all of
-// those, dispatched before them, have counted themselves done, and then scan
-// and permute.  A step that rebuilds nothing pays one empty launch less (2.5
-// us); one that does pays the hand-over, a write-back and a refill of the L2s,
-// which grows with the system.
-__global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
-                                                 unsigned long long* __restrict__ next_vmax, int force,
-                                                 int control) {
-  __shared__ Ctrl sc, sn;
+// Kernels in one launch: blocks count themselves done, and the blocks after them in
+// the grid, dispatched later, wait (bounded) until all have.
+__device__ __forceinline__ void add_count(unsigned long long* count) {
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_fetch_add(count, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool wait_count(const Dev& d, unsigned long long* count, int due) {
   __shared__ int ready;
-  if (!sort_control(d, next, next_vmax, force, control, blockIdx.x, sc, sn)) return;
-  const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
-  if ((int)blockIdx.x < nbb) {
-    bin_body(d, sc, blockIdx.x);
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_add(d.binned, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    return;
-  }
   if (threadIdx.x == 0) {
-    // (the search sets the count back to zero)
-    const unsigned long long due = (unsigned long long)nbb;
     long long spins = 0;
     bool done = false, fault = false;
-    // (a block of the binning that finds a latched error counts nothing)
-    while (!(done = __hip_atomic_load(d.binned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= due) &&
+    // (a block that finds a latched error counts nothing)
+    while (!(done = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (unsigned long long)due) &&
            !(fault = __hip_atomic_load(&d.flags->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) &&
            ++spins < (1ll << 22))
       __builtin_amdgcn_s_sleep(2);
@@ -565,9 +555,24 @@ __global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
     ready = done && __hip_atomic_load(&d.flags->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
   }
   __syncthreads();
-  if (!ready) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  scan_permute_body(d, sn, (int)blockIdx.x - nbb);
+  if (ready) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return ready != 0;
+}
+
+// (1) and (2) in one launch.  A step that rebuilds nothing pays one empty
+// launch less (2.5 us); one that does pays the hand-over, a write-back and a
+// refill of the L2s, which grows with the system.
+__global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
+                                                 unsigned long long* __restrict__ next_vmax, int control) {
+  __shared__ Ctrl sc, sn;
+  if (!sort_control(d, next, next_vmax, 0, control, blockIdx.x, sc, sn)) return;
+  const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
+  if ((int)blockIdx.x < nbb) {
+    bin_body<kBlock>(d, sc, blockIdx.x);
+    add_count(&d.joined[0]);
+  } else if (wait_count(d, &d.joined[0], nbb)) {
+    scan_permute_body<kBlock>(d, sn, (int)blockIdx.x - nbb);  // (the search sets the count back to zero)
+  }
 }
 
 // Neighbour lists of radius r_list through the Lees-Edwards cell stencil.
@@ -686,15 +691,15 @@ struct Seg {
 // {r^2 < r_list^2}.
 //
 // Bound by the vector unit (LJ, 256,000 particles, r_list 3.05: 3200 vector
-// instructions per cluster, 133 us) and, in small systems, by the chain of
+// instructions per cluster, 125 us) and, in small systems, by the chain of
 // phases: against one lane per particle half with the tests on the vector unit, 1000
-// particles take 38 instead of 111 us, 27,000 take 27 instead of 87, 256,000 as long
-// as before and 400,000 beads of a melt 123 instead of 112; the compact halo that it
+// particles take 25 instead of 111 us, 27,000 take 27 instead of 87, 256,000 as long
+// as before and 400,000 beads of a melt 121 instead of 112; the compact halo that it
 // leaves to the force kernel is what the large systems gain from.
 template <int HALO, bool GL>
-__device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
+__device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, const int tile) {
   constexpr int TH = kSearchThreads, NW = TH / 64;
-  static_assert(NW * 16 == kTile && TH == kCells, "one cluster per wave, one table entry per thread");
+  static_assert(NW * 16 == kTile && kCells == 2 * TH, "one cluster per wave, two rounds of table entries");
   constexpr int kLook = 6, kSeen = kLook * TH;  // positions a thread, a tile looks at
   static_assert(kLook * NW <= 64 && kSeen <= 0xffff, "one lane per (round, wave); 16-bit offsets");
   constexpr int kCut = 1 << 30;
@@ -719,10 +724,8 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
   __shared__ Box wbox[NW][2], tbox[2];
   __shared__ int wkept[64], kept_sh;
   __shared__ int wsum[NW], wmax[NW], tot_sh, nseg_sh, nent_sh;
-  Ctrl* c = d.ctrl;
   const int np = d.np, n = d.n, cap = d.cap;
   const int s0 = tile * T;
-  if (tile == 0 && threadIdx.x == 0) *d.binned = 0ull;  // (k_sort's count, for the next rebuild)
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int pn = c->pos_cur, an = c->aux_cur;  // sorted buffers of the new state
   const double4* P = reinterpret_cast<const double4*>(d.pos[pn]);
@@ -794,51 +797,55 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
     }
   }
 
-  // ---- staging table: one cell per thread, then the cells' offsets
+  // ---- staging table: one cell per thread and round, then the cells' offsets
   int all;
   {
-    const int e = (int)threadIdx.x;
-    int st = 0, code = 0, cnt = 0;
-    if (e < nent) {
-      const Seg& s = sgs[nseg == 2 && e >= tb1 ? 1 : 0];
-      const int h2 = s.h + 2, el = e - s.tb;
-      const int row = el / s.nk, kk = el - row * s.nk;
-      const int rz = row / h2, ry = row - rz * h2;
-      int jy = s.y0 - 1 + ry, jz = s.z0 - 1 + rz;
-      const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
-      jy -= sy * d.ny;
-      jz -= sz * d.nz;
-      const int k = s.klo[sy + 1] + kk;
-      if (k <= s.khi[sy + 1]) {
-        const int sx = floor_div(k, d.nx);
-        const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
-        st = d.cell_start[cell];
-        cnt = d.cell_start[cell + 1] - st;
-        code = pack_img(sx, sy, sz);
-      }
-    }
-    cent[e] = og_entry((uint32_t)st, (uint8_t)code);
-    int incl = cnt;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += t;
-    }
-    if (lane == 63) wsum[wv] = incl;
-    if (threadIdx.x == 0) tot_sh = 0;
-    __syncthreads();
-    int off = incl - cnt;
+    // (a second round only for the few tiles with more cells than threads)
     all = 0;
-    for (int w2 = 0; w2 < NW; ++w2) {
-      if (w2 < wv) off += wsum[w2];
-      all += wsum[w2];
+    for (int r = 0; r == 0 || r * TH < nent; ++r) {
+      const int e = r * TH + (int)threadIdx.x;
+      int st = 0, code = 0, cnt = 0;
+      if (e < nent) {
+        const Seg& s = sgs[nseg == 2 && e >= tb1 ? 1 : 0];
+        const int h2 = s.h + 2, el = e - s.tb;
+        const int row = el / s.nk, kk = el - row * s.nk;
+        const int rz = row / h2, ry = row - rz * h2;
+        int jy = s.y0 - 1 + ry, jz = s.z0 - 1 + rz;
+        const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
+        jy -= sy * d.ny;
+        jz -= sz * d.nz;
+        const int k = s.klo[sy + 1] + kk;
+        if (k <= s.khi[sy + 1]) {
+          const int sx = floor_div(k, d.nx);
+          const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
+          st = d.cell_start[cell];
+          cnt = d.cell_start[cell + 1] - st;
+          code = pack_img(sx, sy, sz);
+        }
+      }
+      cent[e] = og_entry((uint32_t)st, (uint8_t)code);
+      int incl = cnt;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += t;
+      }
+      if (r > 0) __syncthreads();  // (wsum is read)
+      if (lane == 63) wsum[wv] = incl;
+      if (threadIdx.x == 0 && r == 0) tot_sh = 0;
+      __syncthreads();
+      int off = all + incl - cnt;
+      for (int w2 = 0; w2 < NW; ++w2) {
+        if (w2 < wv) off += wsum[w2];
+        all += wsum[w2];
+      }
+      coff[e] = off;
+      if (off + cnt <= kSeen) {  // the cells looked at are a prefix of the table
+        for (int k = 0; k < cnt; ++k) ring.map[off + k] = (uint16_t)e;
+        if (all > kSeen || (r + 1) * TH < nent) atomicMax(&tot_sh, off + cnt);
+      }
+      if (threadIdx.x == TH - 1) coff[e + 1] = off + cnt;
     }
-    coff[e] = off;
-    const bool fits = off + cnt <= kSeen;  // the cells looked at are a prefix of the table
-    if (fits)
-      for (int k = 0; k < cnt; ++k) ring.map[off + k] = (uint16_t)e;
-    if (fits && all > kSeen) atomicMax(&tot_sh, off + cnt);
     if (threadIdx.x == 0 && all <= kSeen) tot_sh = all;
-    if (threadIdx.x == TH - 1) coff[kCells] = off + cnt;
     if (threadIdx.x < 2 && (int)threadIdx.x < nseg) {  // the tile's boxes: minimum over the waves
       Box b = wbox[0][threadIdx.x];
       for (int w2 = 1; w2 < NW; ++w2)
@@ -932,13 +939,15 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
     if (h < seen) self_h = ring.map[h];
   }
   {
-    const int e = (int)threadIdx.x;
-    const int o0 = coff[e], o1 = coff[kCells];
-    const int n0 = o0 < seen ? ring.map[o0] : (o0 == seen ? kept_all : kCut);
-    const int n1 = o1 == seen ? kept_all : kCut;
+    const int rounds = nent > TH ? 2 : 1;
+    const int last = coff[rounds * TH];
+    auto kept_before = [&](int o) { return o < seen ? (int)ring.map[o] : (o == seen ? kept_all : kCut); };
+    const int n0 = kept_before(coff[threadIdx.x]), n1 = rounds > 1 ? kept_before(coff[TH + threadIdx.x]) : 0;
+    const int n2 = last == seen ? kept_all : kCut;
     __syncthreads();
-    coff[e] = n0;
-    if (e == 0) coff[kCells] = n1;
+    coff[threadIdx.x] = n0;
+    if (rounds > 1) coff[TH + threadIdx.x] = n1;
+    if (threadIdx.x == 0) coff[rounds * TH] = n2;
   }
   __syncthreads();
 
@@ -1249,7 +1258,36 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const int tile) {
 template <class TC, bool GL>
 __global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) k_neighbors(Dev d) {
   if (rebuild_off(d)) return;  // (the same two words for every wave)
-  neighbors_body<TC::HALO, GL>(d, xcd_block(d.ntiles));
+  if (blockIdx.x == 0 && threadIdx.x == 0) d.joined[0] = 0ull;  // (of k_sort, for the next rebuild)
+  neighbors_body<TC::HALO, GL>(d, d.ctrl, xcd_block(d.ntiles));
+}
+
+// (1) to (3) in one launch.  The blocks of the search wait for all of the scan;
+// the last of them to have waited sets the counts back to zero.
+template <class TC, bool GL>
+__global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(GL && TC::HALO > 1024 ? 2 : 4)))
+    k_rebuild(Dev d, Ctrl* __restrict__ next, unsigned long long* __restrict__ next_vmax, int control) {
+  __shared__ Ctrl sc, sn;
+  if (!sort_control(d, next, next_vmax, 0, control, blockIdx.x, sc, sn)) return;
+  const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
+  int b = (int)blockIdx.x;
+  if (b < nbb) {
+    bin_body<kSearchThreads>(d, sc, b);
+    add_count(&d.joined[0]);
+    return;
+  }
+  b -= nbb;
+  if (b < d.sp_blocks) {
+    if (!wait_count(d, &d.joined[0], nbb)) return;
+    scan_permute_body<kSearchThreads>(d, sn, b);
+    add_count(&d.joined[1]);
+    return;
+  }
+  b -= d.sp_blocks;
+  if (!wait_count(d, &d.joined[1], d.sp_blocks)) return;
+  if (threadIdx.x == 0 && atomicAdd(&d.joined[2], 1ull) == (unsigned long long)d.ntiles - 1ull)
+    d.joined[0] = d.joined[1] = d.joined[2] = 0ull;
+  neighbors_body<TC::HALO, GL>(d, next, xcd_map(b, d.ntiles));
 }
 
 constexpr int kSpreadRun = 4;  // consecutive tiles per run of the batched list search
@@ -1263,7 +1301,7 @@ __global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_pe
   locate(b, xcd_spread<kSpreadRun>((int)blockIdx.x, (int)gridDim.x), sm, tile);
   const Dev& d = stage_dev(b.dev[sm]);
   if (rebuild_off(d)) return;
-  neighbors_body<TC::HALO, GL>(d, tile);
+  neighbors_body<TC::HALO, GL>(d, d.ctrl, tile);
 }
 
 // ---------------------------------------------------------- integrator
@@ -1748,7 +1786,8 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
           dx[u] = pi.x - p.x; dy[u] = pi.y - p.y; dz[u] = pi.z - p.z;
           vx[u] = DPD ? u0_ld - vj[DPD ? 4 * k + u : 0].x : 0.0;
         }
-        if (__any(cq[k] != 0x01010101u * pack_img(0, 0, 0))) {
+        // (without DPD the test costs more than it saves: it spills registers in batches)
+        if (!DPD || __any(cq[k] != 0x01010101u * pack_img(0, 0, 0))) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             int sx, sy, sz;
@@ -1927,10 +1966,13 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
 }
 
 // Waves per SIMD that the halo kernels are compiled for: six in 80 registers
-// (plain steps), four in 128 (DPD).
-constexpr int force_waves(int mode, int halo, bool sample) {
+// (plain steps), four in 128 (DPD); beads in a batch, whose descriptor takes registers
+// too, five (six spill: 16 melts 74 instead of 71 us a step).
+constexpr int force_waves(int mode, int halo, bool sample, bool batch_bonds = false) {
   if (halo == 0) return 1;
-  return mode == kDpdForce ? 4 : (sample || mode == kForcesOnly ? 1 : 6);
+  if (mode == kDpdForce) return 4;
+  if (sample || mode == kForcesOnly) return 1;
+  return batch_bonds && halo == TileSparse::HALO ? 5 : 6;
 }
 
 template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
@@ -1956,7 +1998,7 @@ __global__ void __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(
   force_body<kDpdForce, MIXED, BONDS, false, TileNone, false>(d, xcd_block(d.nblocks), f_out);
 }
 template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
-__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, force_waves(MODE, TC::HALO, SAMPLE)) k_force_b(Batch b) {
+__global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, force_waves(MODE, TC::HALO, SAMPLE, BONDS)) k_force_b(Batch b) {
   int sm, lb;
   const int g = TC::kSpread ? xcd_spread<16>((int)blockIdx.x, (int)gridDim.x) : xcd_map((int)blockIdx.x, (int)gridDim.x);
   locate(b, g, sm, lb);
@@ -2402,14 +2444,23 @@ hipError_t launch_rebuild(const Dev& d, Ctrl* next, unsigned long long* next_vma
   dn.ctrl = next;
   dn.vmax = next_vmax;
   const unsigned nbb = (d.n + kBinBlock - 1) / kBinBlock;
-  // One launch within the steps of up to kSortOneLaunch particles, measured per
-  // step: 65,536 lie between 64,000 LJ particles (32.2 with two launches, 31.4
-  // us with one; 50,000 beads 25.6 and 23.8, 1,000 particles 21.0 and 18.9) and
-  // 256,000 (62.2 and 66.1; 400,000 beads 64.6 and 79.3).  A forced rebuild has
-  // work for both (27,000 particles: 74 and 78 us), and so has a batch, where
-  // some member rebuilds on most steps (64 of them: 563 and 600 us).
+  // Launches within a step, measured per step: one up to kOneLaunch particles (1000:
+  // 15.8 us, with two 18.5, with three 21.0; 17,389 in a graph 19.9, 20.2 and 21.4),
+  // two up to kSortOneLaunch (64,000 LJ particles 31.0, with one 37.1, with three
+  // 32.2; 50,000 beads 23.4, 24.9 and 25.6), three above (256,000 62.2, with two 66.1;
+  // 400,000 beads 64.6 and 79.3).  A forced rebuild has work for all (27,000
+  // particles: 74 us with three, 78 with two), and so has a batch, where some member
+  // rebuilds on most steps (64 of them: 563 and 600 us).
+  if (!force && d.n <= kOneLaunch) {
+    with_search_tiles(d, [&](auto t, auto gl) {
+      using TC = decltype(t);
+      hipLaunchKernelGGL((k_rebuild<TC, decltype(gl)::value>), dim3(nbb + d.sp_blocks + d.ntiles),
+                         dim3(kSearchThreads), 0, s, d, next, next_vmax, control ? 1 : 0);
+    });
+    return hipGetLastError();
+  }
   if (!force && d.n <= kSortOneLaunch) {
-    hipLaunchKernelGGL(k_sort, dim3(nbb + d.sp_blocks), dim3(kBlock), 0, s, d, next, next_vmax, 0, control ? 1 : 0);
+    hipLaunchKernelGGL(k_sort, dim3(nbb + d.sp_blocks), dim3(kBlock), 0, s, d, next, next_vmax, control ? 1 : 0);
   } else {
     hipLaunchKernelGGL(k_control_bin, dim3(nbb), dim3(kBlock), 0, s, d, next, next_vmax, force ? 1 : 0,
                        control ? 1 : 0);
