@@ -148,3 +148,22 @@ def test_dpd_forces_from_the_halo_and_from_memory(name, precision, tol):
     (xa, ua, fa, _), (xb, ub, fb, _) = out
     assert np.array_equal(xa, xb) and np.array_equal(ua, ub)
     assert np.abs(fa - fb).max() <= tol * np.abs(fb).max()
+
+
+# random-walk melts of uneven density: beams narrower than a tile at the box's
+# upper faces, and tiles with more halo cells than the search's block has threads
+@pytest.mark.parametrize("chains,length", [(15, 200), (30, 200), (100, 300)])
+def test_list_search_of_uneven_melts(chains, length):
+    """The pair set is the oracle's, exactly."""
+    x, kw = _melt(chains, length, 0.3)(3)
+    p = Params(shear_rate=0.2, seed=3, **kw)
+    sim = Sim(p, x, np.zeros_like(x), step0=1237)
+    out = sim.build_cells()
+    sim.close()
+    op = _oracle_params(p)
+    Delta = O.offset(1237, p.dt, p.shear_rate, p.box[0], p.box[1])
+    xw, _ = O.le_wrap(x, np.zeros_like(x), Delta, op)
+    ref = O.pairs_cells(xw, Delta, p.box, p.rlist)
+    got = np.sort(out["pairs"][:, 0] * p.n + out["pairs"][:, 1])
+    lo, hi = ref.min(axis=1).astype(np.int64), ref.max(axis=1).astype(np.int64)
+    assert np.array_equal(got, np.sort(lo * p.n + hi))
