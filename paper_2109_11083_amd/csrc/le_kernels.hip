@@ -585,8 +585,8 @@ __global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
 // (cell, image) pair is visited once; with L > 2 r_list at most one image of
 // a particle can lie within r_list, so no pair is counted twice.
 //
-// Tiles.  A tile is T consecutive slots (kTile, or kTileSmall in small systems).  The slots follow the beam order of
-// the cells (cell_slot), so a tile covers a stretch [xa, xb] of one beam, or
+// Tiles.  A tile is T consecutive slots (kTile, or kTileSmall in small
+// systems).  The slots follow the beam order of the cells (cell_slot), so a tile covers a stretch [xa, xb] of one beam, or
 // the end of one and the start of the next (its segments).  The cells that a
 // segment's stencils reach, row by row, are staged into LDS in a fixed order
 // while they fit (HALO positions).  With the halo layout, d.halo
@@ -1544,7 +1544,7 @@ __device__ __forceinline__ void block_partials(double* vals, double* out, int lb
 // melt), lists in blocks of 4 and 22 vector instructions per entry took the
 // plain step from 43 to 36.5 us for 256,000 LJ particles and, against gathers from
 // global memory, from 37 to 26.7 us for 400,000 beads (traced); it is bound by the vector unit's
-// issue (53% busy) and the waves' imbalance, six waves per SIMD in 80 registers.
+// issue (75% busy) and the waves' imbalance, six waves per SIMD in 80 registers.
 // DPD steps with the halo gather the velocities (from vt, with the slots kept
 // in LDS beside the positions) of the partners within the DPD cutoff alone: all
 // from memory, four gathers per entry, the kernel waited for them (256,000 LJ
