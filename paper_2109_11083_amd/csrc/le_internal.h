@@ -61,6 +61,10 @@ struct alignas(64) Ctrl {
 
 enum { kRebuildDue = 1, kRebuildForced = 2 };
 
+// Counts of kernels in one launch: places given out, blocks done of the binning and of
+// the scan-and-permute pass, and blocks of the search that have waited.
+enum { kPlace = 0, kBinned = 1, kSorted = 2, kWaited = 3, kJoined = 4 };
+
 // Sticky status and telemetry shared by both control copies.
 struct alignas(64) Flags {
   int32_t status;        // LE_OK or the first LE_E_* code latched by a kernel
@@ -153,7 +157,7 @@ struct Dev {
   unsigned long long* vmax;
   unsigned long long* vmax_other;  // the speed-bound slots paired with ctrl_other
   unsigned long long* scan_status; // [sp_blocks] look-back words of the cell scan
-  unsigned long long* joined;      // [3] blocks done of kernels in one launch (zero between rebuilds)
+  unsigned long long* joined;      // [kJoined] counts of kernels in one launch (zero between rebuilds)
   int32_t sp_cells, sp_blocks;     // cells per block of the scan-and-permute pass, and its blocks
   Flags* flags;
 };

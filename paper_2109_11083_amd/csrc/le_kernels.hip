@@ -185,7 +185,7 @@ __global__ void k_load_state(Dev d, const double* __restrict__ x0, const double*
     c->rebuild = 0;
     c->wraps = 0;
     d.flags->status = 0;
-    d.joined[0] = d.joined[1] = d.joined[2] = 0ull;
+    for (int k = 0; k < kJoined; ++k) d.joined[k] = 0ull;
     for (int k = 0; k < kSlots * kLineInts; ++k) d.flags->max_nb_slot[k] = 0;
   }
   for (int k = i; k < kSlots * kLineU64; k += gridDim.x * blockDim.x) d.vmax[k] = 0ull;
@@ -288,11 +288,7 @@ __device__ __forceinline__ bool sort_control(const Dev& d, Ctrl* __restrict__ ne
       if (bid == 0) *next = c;
       go = rb ? 1 : 0;
     }
-    if (bid == 0) {
-      if (threadIdx.x < kSlots) next_vmax[threadIdx.x * kLineU64] = 0ull;
-      if (rb)
-        for (int k = threadIdx.x; k < kSlots * kLineInts; k += 64) d.flags->max_nb_slot[k] = 0;
-    }
+    if (bid == 0 && threadIdx.x < kSlots) next_vmax[threadIdx.x * kLineU64] = 0ull;
   }
   __syncthreads();
   return go != 0;
@@ -303,6 +299,8 @@ __device__ __forceinline__ void bin_body(const Dev& d, const Ctrl& sc, int bid) 
   // the look-back words of the scan start cleared (spread over the blocks)
   const int nbb = (d.n + kBinBlock - 1) / kBinBlock;  // blocks of this pass
   for (int k = bid * TH + (int)threadIdx.x; k < d.sp_blocks; k += nbb * TH) d.scan_status[k] = 0ull;
+  if (bid == 0)
+    for (int k = threadIdx.x; k < kSlots * kLineInts; k += TH) d.flags->max_nb_slot[k] = 0;
   for (int rd = 0; rd < kBinBlock / TH; ++rd) {
     const int i = bid * kBinBlock + rd * TH + (int)threadIdx.x;
     int cell = -1, tg = 0;
@@ -535,8 +533,19 @@ __global__ void __launch_bounds__(kBlock) k_scan_permute_b(Batch b) {
   scan_permute_body<kBlock>(d, *d.ctrl, bid);
 }
 
-// Kernels in one launch: blocks count themselves done, and the blocks after them in
-// the grid, dispatched later, wait (bounded) until all have.
+// Kernels in one launch: blocks count themselves done, and the blocks of the next
+// kernel wait until all have.  A block takes its place in the order of the work from
+// a counter when it runs, not from its place in the grid: whatever it waits for is
+// then done or being done by blocks that run already, and the wait ends, however
+// many launches of other streams share the CUs.  (By the place in the grid, blocks
+// that wait may fill the CUs of one XCD for blocks not yet dispatched on another,
+// where the blocks of another launch wait likewise.)  The bound of the spin is never reached.
+__device__ __forceinline__ int take_place(unsigned long long* next_place) {
+  __shared__ int place;
+  if (threadIdx.x == 0) place = (int)atomicAdd(next_place, 1ull);
+  __syncthreads();
+  return place;
+}
 __device__ __forceinline__ void add_count(unsigned long long* count) {
   __syncthreads();
   if (threadIdx.x == 0) __hip_atomic_fetch_add(count, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -567,11 +576,12 @@ __global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
   __shared__ Ctrl sc, sn;
   if (!sort_control(d, next, next_vmax, 0, control, blockIdx.x, sc, sn)) return;
   const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
-  if ((int)blockIdx.x < nbb) {
-    bin_body<kBlock>(d, sc, blockIdx.x);
-    add_count(&d.joined[0]);
-  } else if (wait_count(d, &d.joined[0], nbb)) {
-    scan_permute_body<kBlock>(d, sn, (int)blockIdx.x - nbb);  // (the search sets the count back to zero)
+  const int b = take_place(&d.joined[kPlace]);  // (the search sets the counts back to zero)
+  if (b < nbb) {
+    bin_body<kBlock>(d, sc, b);
+    add_count(&d.joined[kBinned]);
+  } else if (wait_count(d, &d.joined[kBinned], nbb)) {
+    scan_permute_body<kBlock>(d, sn, b - nbb);
   }
 }
 
@@ -1258,7 +1268,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
 template <class TC, bool GL>
 __global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) k_neighbors(Dev d) {
   if (rebuild_off(d)) return;  // (the same two words for every wave)
-  if (blockIdx.x == 0 && threadIdx.x == 0) d.joined[0] = 0ull;  // (of k_sort, for the next rebuild)
+  if (blockIdx.x == 0 && threadIdx.x == 0) d.joined[kPlace] = d.joined[kBinned] = 0ull;  // (of k_sort)
   neighbors_body<TC::HALO, GL>(d, d.ctrl, xcd_block(d.ntiles));
 }
 
@@ -1270,24 +1280,24 @@ __global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_pe
   __shared__ Ctrl sc, sn;
   if (!sort_control(d, next, next_vmax, 0, control, blockIdx.x, sc, sn)) return;
   const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
-  int b = (int)blockIdx.x;
+  int b = take_place(&d.joined[kPlace]);
   if (b < nbb) {
     bin_body<kSearchThreads>(d, sc, b);
-    add_count(&d.joined[0]);
+    add_count(&d.joined[kBinned]);
     return;
   }
   b -= nbb;
   if (b < d.sp_blocks) {
-    if (!wait_count(d, &d.joined[0], nbb)) return;
+    if (!wait_count(d, &d.joined[kBinned], nbb)) return;
     scan_permute_body<kSearchThreads>(d, sn, b);
-    add_count(&d.joined[1]);
+    add_count(&d.joined[kSorted]);
     return;
   }
   b -= d.sp_blocks;
-  if (!wait_count(d, &d.joined[1], d.sp_blocks)) return;
-  if (threadIdx.x == 0 && atomicAdd(&d.joined[2], 1ull) == (unsigned long long)d.ntiles - 1ull)
-    d.joined[0] = d.joined[1] = d.joined[2] = 0ull;
-  neighbors_body<TC::HALO, GL>(d, next, xcd_map(b, d.ntiles));
+  if (!wait_count(d, &d.joined[kSorted], d.sp_blocks)) return;
+  if (threadIdx.x == 0 && atomicAdd(&d.joined[kWaited], 1ull) == (unsigned long long)d.ntiles - 1ull)
+    for (int k = 0; k < kJoined; ++k) d.joined[k] = 0ull;
+  neighbors_body<TC::HALO, GL>(d, &sn, xcd_map(b, d.ntiles));
 }
 
 constexpr int kSpreadRun = 4;  // consecutive tiles per run of the batched list search

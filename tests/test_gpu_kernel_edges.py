@@ -5,6 +5,7 @@ or of scale s within n eps s, with the margin of the bars of
 test_gpu_parity (1e-12 relative)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 from paper_2109_11083_amd import inputs
@@ -167,3 +168,36 @@ def test_list_search_of_uneven_melts(chains, length):
     got = np.sort(out["pairs"][:, 0] * p.n + out["pairs"][:, 1])
     lo, hi = ref.min(axis=1).astype(np.int64), ref.max(axis=1).astype(np.int64)
     assert np.array_equal(got, np.sort(lo * p.n + hi))
+
+
+# the launches whose blocks wait for one another (the whole rebuild up to 20,000
+# particles, the sort up to 65,536), many at a time on streams of their own: more
+# waiting blocks than the GPU holds, in dense small and large tiles, sparse tiles
+# and the global layout.  Each steps as it does alone, bit for bit.
+def test_rebuilds_of_many_streams_at_once():
+    kinds = [("lj_10000", {}), ("lj_10001", {}), ("lj_10000", dict(tune=2)), ("kg_12000_wide", {}),
+             ("lj_16500", dict(thermostat="dpd", gamma=5.0)), ("lj_20001", {})]
+    make = {**SEARCH, "lj_20001": _fluid(20001)}
+
+    def start(k, stream):
+        name, over = kinds[k % len(kinds)]
+        x, kw = make[name](k)
+        u = np.random.default_rng(k).normal(size=x.shape)
+        p = Params(shear_rate=0.2, seed=3 + k, dt=0.002, **{"rc": 2.5, "skin": 0.1, **kw, **over})
+        return Sim(p, x, u, stream=stream)
+
+    alone = []
+    for k in range(12):
+        s = start(k, torch.cuda.Stream())
+        s.step(60)
+        alone.append((s.state(), s.stats()))
+        s.close()
+    sims = [start(k, torch.cuda.Stream()) for k in range(12)]
+    for _ in range(6):
+        for s in sims:
+            s.step(10)
+    for s, (ref, stats) in zip(sims, alone):
+        got = s.state()
+        assert all(np.array_equal(a, b) for a, b in zip(got[:3], ref[:3])) and got[3] == ref[3] == 60
+        assert s.stats() == stats
+        s.close()
