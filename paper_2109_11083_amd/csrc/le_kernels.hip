@@ -170,6 +170,7 @@ __global__ void k_load_state(Dev d, const double* __restrict__ x0, const double*
     const double4 far = make_double4(1e100, 1e100, 1e100, 0.0);
     reinterpret_cast<double4*>(d.pos[0])[n] = far;
     reinterpret_cast<double4*>(d.pos[1])[n] = far;
+    if (d.vt) d.vt[n] = VtRec{0.0, 0.0, 0.0, 0, 0};  // (its DPD record: finite, its weight is 0)
   }
   for (int c = i; c < d.ncell; c += gridDim.x * blockDim.x) d.cell_count[c] = 0;
   if (i == 0) {
@@ -2023,20 +2024,18 @@ __global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, forc
   force_body<MODE, MIXED, BONDS, SAMPLE, TC, CAP>(stage_dev(b.dev[sm]), lb, nullptr);
 }
 
-// DPD: pack the current velocities and tags of every slot (and zeros for the
-// sentinel slot n) into vt, so that the force kernel gathers one 32-byte
-// record per partner.
+// DPD: pack the current velocities and tags of every slot into vt, so that the
+// force kernel gathers one 32-byte record per partner (that of the sentinel slot n
+// never changes).
 __device__ __forceinline__ void pack_vt_body(const Dev& d, int bid) {
   if (d.flags->status) return;
   const Ctrl* c = d.ctrl;
   const int i = bid * kBlock + threadIdx.x;
   const int np = d.np;
-  VtRec v = {0.0, 0.0, 0.0, 0, 0};
   if (i < d.n) {
     const double* U = d.vel[c->aux_cur];
-    v = VtRec{U[i], U[np + i], U[2 * np + i], d.tag[c->aux_cur][i], 0};
+    d.vt[i] = VtRec{U[i], U[np + i], U[2 * np + i], d.tag[c->aux_cur][i], 0};
   }
-  if (i <= d.n) d.vt[i] = v;
 }
 
 __global__ void __launch_bounds__(kBlock) k_pack_vt(Dev d) { pack_vt_body(d, blockIdx.x); }
@@ -2555,7 +2554,7 @@ hipError_t launch_force(const Dev& d, hipStream_t s, ForceMode mode, bool sample
       break;
     case kDpdForce:
       if (!d.vt) return hipErrorInvalidValue;
-      hipLaunchKernelGGL(k_pack_vt, dim3(blocks_for(d.n + 1)), dim3(kBlock), 0, s, d);
+      hipLaunchKernelGGL(k_pack_vt, dim3(blocks_for(d.n)), dim3(kBlock), 0, s, d);
       if (sample) launch_force_t<kDpdForce, true>(d, s, f_out, sample_out, e0, e1);
       else launch_force_t<kDpdForce, false>(d, s, f_out, nullptr, e0, e1);
       break;

@@ -9,7 +9,7 @@ import torch
 
 import oracle as O
 from paper_2109_11083_amd import inputs
-from paper_2109_11083_amd.sim import Params, Sim, step_batch
+from paper_2109_11083_amd.sim import Params, Sim, step_batch, workspace_bytes
 
 pytestmark = pytest.mark.gpu
 
@@ -200,4 +200,25 @@ def test_rebuilds_of_many_streams_at_once():
         got = s.state()
         assert all(np.array_equal(a, b) for a, b in zip(got[:3], ref[:3])) and got[3] == ref[3] == 60
         assert s.stats() == stats
+        s.close()
+
+
+# DPD members of a batch restarted from a state with forces (no evaluation before the
+# first step), in workspaces that held other data: whole blocks of 256 particles and one
+# more, partners from the halo and from memory.  As alone, bit for bit.
+@pytest.mark.parametrize("tune", [0, 2])
+@pytest.mark.parametrize("n", [2048, 2049])
+def test_dpd_restart_in_a_batch(n, tune):
+    w, p = _lj(n, 0.3, 7, skin=0.3, thermostat="dpd", gamma=5.0, tune=tune)
+    f0 = 0.1 * np.random.default_rng(5).normal(size=w.x.shape)
+    sims = []
+    for _ in range(2):
+        ws = torch.full((workspace_bytes(p),), 255, dtype=torch.uint8, device="cuda")
+        sims.append(Sim(p, w.x, w.u, f0=f0, workspace=ws))
+    step_batch(sims[:1], 20)
+    sims[1].step(20)
+    (xa, ua, fa, _), (xb, ub, fb, _) = (s.state() for s in sims)
+    assert np.isfinite(fa).all()
+    assert np.array_equal(xa, xb) and np.array_equal(ua, ub) and np.array_equal(fa, fb)
+    for s in sims:
         s.close()
