@@ -309,7 +309,8 @@ __device__ __forceinline__ void bin_body(const Dev& d, const Ctrl& sc, int bid) 
       tg = d.tag[sc.aux_cur][i];
       const double4 p = reinterpret_cast<const double4*>(d.pos[sc.pos_cur])[i];
       double x = p.x, y = p.y, z = p.z, ky, kz;
-      cross_wrap(d, sc.Delta, x, y, z, ky, kz);
+      // (here too: all such particles meet in one cell, whose bucket they may overflow)
+      if (!cross_wrap(d, sc.Delta, x, y, z, ky, kz)) latch(d.flags, LE_E_NONFINITE);
       int ix = cell_index(x, d.inv_lx, d.nx);
       int iy = cell_index(y, d.inv_ly, d.ny);
       int iz = cell_index(z, d.inv_lz, d.nz);

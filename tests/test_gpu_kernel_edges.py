@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import oracle as O
+from paper_2109_11083_amd import binding as B
 from paper_2109_11083_amd import inputs
 from paper_2109_11083_amd.sim import Params, Sim, step_batch, workspace_bytes
 
@@ -222,3 +223,21 @@ def test_dpd_restart_in_a_batch(n, tune):
     assert np.array_equal(xa, xb) and np.array_equal(ua, ub) and np.array_equal(fa, fb)
     for s in sims:
         s.close()
+
+
+# non-finite positions are reported as such, one or all of them (all meet in one
+# cell, more than its bucket holds)
+@pytest.mark.parametrize("bad", [1, 1000])
+def test_nonfinite_positions_are_reported(bad):
+    w, p = _lj(1000, 0.3, 7)
+    x = w.x.copy()
+    x[1, :bad] = np.nan
+    sim = Sim(p, x, w.u)
+    assert sim.stats()["status"] == B.LE_E_NONFINITE
+    sim.close()
+    xt = torch.as_tensor(x, device="cuda")
+    f = torch.empty((3, p.n), dtype=torch.float64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    B.le_forces_static(p.to_c(), xt.data_ptr(), f.data_ptr(), None, status.data_ptr(), 0,
+                       torch.cuda.current_stream().cuda_stream)
+    assert int(status.cpu()[0]) == B.LE_E_NONFINITE
