@@ -418,7 +418,11 @@ __device__ __forceinline__ void scan_permute_body(const Dev& d, const Ctrl& cn, 
       const int first2 = inc ? __builtin_ctzll(inc) : 64;
       const unsigned long long need = first2 >= 63 ? ~0ull : ((2ull << first2) - 1ull);
       if (zero & need) {  // a predecessor in reach has not published yet
-        if (++spins > (1ll << 22)) {
+        // (nor will it after a latched error: blocks that find one at their start leave)
+        ++spins;
+        const bool fault =
+            (spins & 15) == 0 && __hip_atomic_load(&d.flags->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+        if (fault || spins > (1ll << 22)) {
           if (lane == 0) latch(d.flags, LE_E_STATE);
           prefix = -1;  // no prefix: the block moves nothing
           break;

@@ -3,6 +3,8 @@ rounds, remainders, the smallest and largest of a range), against the FP64
 oracle.  Tolerances: counts and pair sets exact; sums of n terms of one sign
 or of scale s within n eps s, with the margin of the bars of
 test_gpu_parity (1e-12 relative)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -241,3 +243,19 @@ def test_nonfinite_positions_are_reported(bad):
     B.le_forces_static(p.to_c(), xt.data_ptr(), f.data_ptr(), None, status.data_ptr(), 0,
                        torch.cuda.current_stream().cuda_stream)
     assert int(status.cpu()[0]) == B.LE_E_NONFINITE
+
+
+# an error that the sort's first blocks latch while later ones have not started
+# (3000 blocks): those leave, and no block waits for what they would have published
+def test_sort_ends_after_an_error_in_its_first_blocks():
+    w, p = _lj(1_500_000, 0.0, 7)
+    u = w.u.copy()
+    u[2] = np.nan
+    Sim(p, w.x, w.u).close()
+    t0 = time.perf_counter()
+    sim = Sim(p, w.x, u)
+    status = sim.stats()["status"]
+    elapsed = time.perf_counter() - t0
+    assert status == B.LE_E_NONFINITE
+    assert elapsed < 2.0  # (the bound of the wait is reached after some seconds)
+    sim.close()
