@@ -55,7 +55,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Geometry {
   int32_t nc[3];
   double rc, rlist;
-  int32_t cap;                  // list capacity per particle
+  int32_t cap, units;           // list capacity per particle: entries, units of 16 bytes
   int64_t np;
   int32_t staged, tiles;        // pair layout and tile configuration (kTiles*)
   int32_t tile, halo_cap, ntiles, nblocks;
@@ -163,8 +163,8 @@ le_status validate(const le_params* p, Geometry* g) {
   if ((int64_t)g->nc[0] * g->nc[1] * g->nc[2] > (int64_t)0x7fffffff - 1) return LE_E_GEOMETRY;
   g->rc = rc;
   g->rlist = rlist;
-  // capacity of a particle's list: max_neighbors, or twice the mean of the
-  // density with a margin, in two halves of whole blocks of 8 entries
+  // entries of a particle's list: max_neighbors, or twice the mean of the
+  // density with a margin
   const double rho = (double)p->n / (p->box[0] * p->box[1] * p->box[2]);
   const double list_pp = 4.0 / 3.0 * M_PI * rlist * rlist * rlist * rho;  // mean partners per particle
   {
@@ -180,6 +180,12 @@ le_status validate(const le_params* p, Geometry* g) {
     g->bcap = ((int32_t)ceil(cap) + 7) / 8 * 8;
   }
   plan_tiles(p, g, list_pp);
+  // Units of the list.  Global layout: 4 entries each, the staged and the walked ones
+  // padded apart.  Halo layout: room for as many staged (8 a unit) and as
+  // many walked ones (4 a unit) at the same time, less, in small tiles, the
+  // room that their larger halo tables take; in any mix `cap` of them.
+  g->units = g->cap / 4 + 1;
+  if (g->staged) g->units = std::max(g->units, g->cap / 8 * 3 - (g->tile == kTileSmall ? 8 : 0));
   {
     // about kSortParticles particles per block of the scan-and-permute pass
     const int64_t ncell = (int64_t)g->nc[0] * g->nc[1] * g->nc[2];
@@ -224,7 +230,7 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
   }
   t.cell_count = (int32_t*)take(ncell * sizeof(int32_t));
   t.cell_start = (int32_t*)take((ncell + 1) * sizeof(int32_t));
-  t.nl = (uint4*)take((size_t)(g.cap / 4) * np * sizeof(uint4));
+  t.nl = (uint4*)take((size_t)g.units * np * sizeof(uint4));
   t.n_plain = (int32_t*)take(np * sizeof(int32_t));
   t.n_og = (int32_t*)take(np * sizeof(int32_t));
   t.tile_nstage = (int32_t*)take((size_t)g.ntiles * sizeof(int32_t));
@@ -319,6 +325,7 @@ void fill_geometry(const le_params* p, const Geometry& g, Dev* d) {
   d->n = (int32_t)p->n;
   d->np = (int32_t)g.np;
   d->cap = g.cap;
+  d->units = g.units;
   d->by_sh = g.by_sh; d->bz_sh = g.bz_sh;
   d->tile = g.tile; d->tile_sh = __builtin_ctz((unsigned)g.tile); d->halo_cap = g.halo_cap;
   d->staged = g.staged; d->tiles = g.tiles;

@@ -103,7 +103,8 @@ struct Dev {
   double inv_vol;
   int32_t nx, ny, nz, ncell;
   int32_t n, np;                   // particles, padded stride (np > n: slot n is a far-away sentinel)
-  int32_t cap;                     // capacity of a particle's list (a multiple of 8)
+  int32_t cap, units;              // capacity of a particle's list: entries (a multiple of 16) of either
+                                   // kind, and units of 16 bytes (see nl)
   int32_t by_sh, bz_sh;            // log2 of the rows of a beam along y and z (see cell_slot)
   int32_t tile, tile_sh, halo_cap; // particles per tile and their log2, positions it may stage
   int32_t chain_len;
@@ -133,7 +134,7 @@ struct Dev {
                                    // cell, in arrival order
   int32_t* cell_count;             // [ncell]
   int32_t* cell_start;             // [ncell + 1]
-  // Neighbour lists: cap / 4 units of 16 bytes per particle, unit u of particles
+  // Neighbour lists: `units` units of 16 bytes per particle, unit u of particles
   // i, i + 1, ... contiguous (u np + i).
   //   partners found in the tile's staged halo, from unit 0 up: LDS indices, 8 (16-bit)
   //     per unit (halo layout), or slots in global memory in the low kSlotBits bits with

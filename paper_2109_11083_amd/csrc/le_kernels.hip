@@ -623,7 +623,7 @@ __global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
 // walked entries from the back.
 __device__ __forceinline__ size_t unit_front(const Dev& d, int b, int i) { return (size_t)b * d.np + i; }
 __device__ __forceinline__ size_t unit_back(const Dev& d, int b, int i) {
-  return (size_t)(d.cap / 4 - 1 - b) * d.np + i;
+  return (size_t)(d.units - 1 - b) * d.np + i;
 }
 
 // Unwrapped x-cell range [klo, khi] reached from cells xa..xb of a row across
@@ -729,7 +729,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   constexpr int kCut = 1 << 30;
   const int T = d.tile;  // (of small tiles the first waves take the clusters)
   constexpr int RS = 13;            // words per lane of the ring: 26 LDS indices, odd stride (banks)
-  constexpr int PAD = GL ? 4 : 8;  // list padding (entries per 16-byte block)
+  constexpr int PAD = GL ? 4 : 8;  // list padding (entries per unit of 16 bytes)
   // x, y, z, |x|^2 (spare entries: a round may read up to 31 past the halo; the
   // stride keeps the four components on different banks)
   __shared__ float hc[4][HALO + 48];
@@ -748,7 +748,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   __shared__ Box wbox[NW][2], tbox[2];
   __shared__ int wkept[64], kept_sh;
   __shared__ int wsum[NW], wmax[NW], tot_sh, nseg_sh, nent_sh;
-  const int np = d.np, n = d.n, cap = d.cap;
+  const int np = d.np, n = d.n, units = d.units;
   const int s0 = tile * T;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int pn = c->pos_cur, an = c->aux_cur;  // sorted buffers of the new state
@@ -983,7 +983,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   int nog = 0;   // entries of rows that were not staged (the same in the four lanes)
   uint32_t walked = 0;
   auto og_store = [&](int k, uint32_t e) {
-    if (k < cap) reinterpret_cast<uint32_t*>(d.nl + unit_back(d, k >> 2, i))[k & 3] = e;
+    if ((k >> 2) < units) reinterpret_cast<uint32_t*>(d.nl + unit_back(d, k >> 2, i))[k & 3] = e;
   };
   // full blocks leave the rings, lanes of a particle in order of q (called by the whole wave)
   auto flush = [&]() {
@@ -994,7 +994,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
       uint32_t t[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) t[k] = rw[k];
-      if ((blk + 1) * 8 <= cap) {
+      if ((blk + 1) * (8 / PAD) <= units) {
         if constexpr (GL) {
           d.nl[unit_front(d, 2 * blk, i)] = make_uint4(hent[t[0] & 0xffff], hent[t[0] >> 16], hent[t[1] & 0xffff],
                                                           hent[t[1] >> 16]);
@@ -1235,7 +1235,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
     const int b0 = nblk * (8 / PAD);  // blocks of PAD entries written so far
     if (valid) {
       for (int b = q; b * PAD < restp; b += 4) {
-        if ((b0 + b + 1) * PAD > cap) continue;
+        if (b0 + b >= units) continue;
         if constexpr (GL) {
           const uint16_t* e = t16 + 4 * b;
           d.nl[unit_front(d, b0 + b, i)] = make_uint4(hent[e[0]], hent[e[1]], hent[e[2]], hent[e[3]]);
@@ -1258,7 +1258,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   }
   if (!valid || q != 0) return;
   int nst = nblk * 8 + restp, nogp = (nog + kOtherBatch - 1) / kOtherBatch * kOtherBatch;
-  if (nst + nogp > cap) {
+  if (max(nst, nogp) > d.cap || nst / PAD + nogp / kOtherBatch > units) {
     latch(d.flags, LE_E_CAPACITY);
     nst = nogp = 0;
   } else {
@@ -1753,7 +1753,7 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
     // a particle take rounds in turn.
     const int nfo = STAGED ? 0 : d.n_plain[i] / kOtherBatch;
     const int nbo = nfo + d.n_og[i] / kOtherBatch;
-    const int last_ob = d.cap / kOtherBatch - 1;
+    const int last_ob = d.units - 1;
     auto ooff = [&](int q) -> size_t {
       const int b = STAGED || q >= nfo ? last_ob - min(q - nfo, last_ob) : q;
       return (size_t)b * np + i;

@@ -259,3 +259,25 @@ def test_sort_ends_after_an_error_in_its_first_blocks():
     assert status == B.LE_E_NONFINITE
     assert elapsed < 2.0  # (the bound of the wait is reached after some seconds)
     sim.close()
+
+
+# 14 partners each (a body-centred lattice in few, full cells, of which a tile's halo
+# holds a part), where the lists have room for 16: whatever the mix of staged
+# and walked partners
+@pytest.mark.parametrize("tune", [0, 1, 2])
+def test_list_capacity_in_any_mix(tune):
+    m, L = 12, 30.0
+    g = np.arange(m) * (L / m)
+    a = np.stack([v.ravel() for v in np.meshgrid(g, g, g, indexing="ij")])
+    x = np.concatenate([a, a + 0.5 * L / m], axis=1) + np.random.default_rng(1).uniform(0.0, 0.01, (3, 2 * m ** 3))
+    p = Params(n=x.shape[1], box=(L, L, L), rc=2.6, skin=0.2, cells=(3, 3, 3), max_neighbors=16, tune=tune)
+    sim = Sim(p, x, np.zeros_like(x))
+    out = sim.build_cells()
+    F, W = sim.forces()
+    assert sim.stats()["max_neighbors"] == 14
+    sim.close()
+    assert len(out["pairs"]) == 7 * p.n
+    Fr, Wr, _ = O.forces(x, 0.0, _oracle_params(p))
+    # (in a perfect lattice the forces cancel: against the force of one pair)
+    assert np.abs(F - Fr).max() <= 1e-12 * 24.0 / 2.165 ** 7 * 14
+    assert np.abs(W - Wr).max() <= 1e-12 * np.abs(Wr[:3]).max()
