@@ -300,8 +300,7 @@ void fill_geometry(const le_params* p, const Geometry& g, Dev* d) {
   d->mass = p->mass;
   d->eps24 = 24.0 * p->eps;
   d->sig2 = p->sigma * p->sigma;
-  d->lj_b = d->eps24 * (d->sig2 * d->sig2 * d->sig2);
-  d->lj_a = 2.0 * d->lj_b * (d->sig2 * d->sig2 * d->sig2);
+  d->lj_c = 2.0 * d->eps24 / d->sig2;
   d->rc2 = g.rc * g.rc;
   d->rlist = g.rlist;
   d->rlist2 = g.rlist * g.rlist;

@@ -95,7 +95,7 @@ struct Dev {
   double dpd_rc2, dpd_inv_rc;      // DPD: r_c^2 and 1 / r_c of the weight omega
   double mass;
   double eps24, sig2;              // 24 eps, sigma^2
-  double lj_a, lj_b;               // 48 eps sigma^12, 24 eps sigma^6
+  double lj_c;                     // 48 eps / sigma^2
   double rc2, rlist, rlist2;       // cutoff^2, list radius, list radius^2
   double fene_k, fene_r02;
   double angle_k;                  // cosine angle term of the chains (0: none)

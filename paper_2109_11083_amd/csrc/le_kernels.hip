@@ -1433,7 +1433,10 @@ __device__ __forceinline__ void add_pair(double f, double dx, double dy, double 
 }
 
 // Scalar LJ force factor f (force on i = f d) for r^2 = r2, zero outside the
-// cutoff: f = r^-8 (A r^-6 - B), A = 48 eps sigma^12, B = 24 eps sigma^6.
+// cutoff: f = 24 eps s^3 (2 s^3 - 1) / r^2 with s = sigma^2 / r^2.  The FP64 form without
+// a cap leaves the factor 48 eps / sigma^2 (Dev::lj_c) to the sums over pairs and
+// returns s^4 (s^3 - 1/2): powers of the ratio alone, which do not under- or
+// overflow for small or large units of length.
 // Branch-free so that the candidates of one batch are independent
 // instruction streams the compiler can interleave.  The FP64 form is bound by
 // the vector unit's issue, so it counts instructions: 1/r^2 from the hardware
@@ -1458,9 +1461,10 @@ __device__ __forceinline__ double lj_masked(const Dev& d, double r2) {
     const double e = fma(-r2, inv, 1.0);
     inv = fma(inv, fma(e, e, e), inv);
     inv = __hiloint2double(in ? __double2hiint(inv) : 0, __double2loint(inv));
-    const double i2 = inv * inv;
-    double f = (i2 * i2) * fma(d.lj_a, i2 * inv, -d.lj_b);
+    const double s = d.sig2 * inv, s2 = s * s;
+    double f = (s2 * s2) * fma(s2, s, -0.5);
     if (CAP) {
+      f = d.lj_c * f;
       const double lim = d.force_cap / sqrt(r2);
       f = fmin(fmax(f, -lim), lim);
     }
@@ -1835,6 +1839,10 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
         }
       }
     }
+    }
+    if (!MIXED && !CAP) {  // (see lj_masked)
+      fx *= d.lj_c; fy *= d.lj_c; fz *= d.lj_c;
+      if (VIR) for (int q = 0; q < 6; ++q) w[q] *= d.lj_c;
     }
     if (BONDS && half == 0) {
       // FENE (Eq. fene), always float64; displacement by the nearest image

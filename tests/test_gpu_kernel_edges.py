@@ -281,3 +281,24 @@ def test_list_capacity_in_any_mix(tune):
     # (in a perfect lattice the forces cancel: against the force of one pair)
     assert np.abs(F - Fr).max() <= 1e-12 * 24.0 / 2.165 ** 7 * 14
     assert np.abs(W - Wr).max() <= 1e-12 * np.abs(Wr[:3]).max()
+
+
+# lengths in a unit of 2^90 (an exact scaling): sigma^12 is no double, but the forces are
+# those of sigma = 1 in that unit
+@pytest.mark.parametrize("tune,force_cap", [(1, 0.0), (2, 0.0), (0, 1e6)])
+@pytest.mark.parametrize("name", ["lj_1009", "kg_2000"])
+def test_forces_in_small_units_of_length(name, tune, force_cap):
+    x, kw = SEARCH[name](3)
+    kw = {"rc": 2.5, "skin": 0.3, **kw}
+    out = []
+    for e in (0, -90):
+        c = 2.0 ** e
+        k = dict(kw, rc=kw["rc"] * c, skin=kw["skin"] * c, box=tuple(L * c for L in kw["box"]), sigma=c,
+                 fene_r0=1.5 * c, fene_k=30.0 / c ** 2, force_cap=force_cap / c)
+        sim = Sim(Params(shear_rate=0.2, seed=3, tune=tune, **k), x * c, np.zeros_like(x), step0=1237)
+        F, W = sim.forces()
+        sim.close()
+        out.append((F * c, W))
+    (Fa, Wa), (Fb, Wb) = out
+    assert np.abs(Fa - Fb).max() <= 1e-12 * np.sqrt((Fa ** 2).sum(axis=0).mean())
+    assert np.abs(Wa - Wb).max() <= 1e-12 * np.abs(Wa[:3]).max()
