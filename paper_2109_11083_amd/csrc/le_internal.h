@@ -28,8 +28,6 @@ struct TileSparse { static constexpr int HALO = 1024, kForceThreads = 256; stati
 struct TileDenseGlobal { static constexpr int HALO = 2048; };
 struct TileNone { static constexpr int HALO = 0, kForceThreads = kTile; static constexpr bool kSpread = false; };
 enum { kTilesDense = 0, kTilesSparse = 1 };
-constexpr int kCells = 1024;       // cells a tile's halo may have (staging table; 512 were too few for melts of
-                                   // uneven density: 30,000 beads 96 instead of 60 us an evaluation)
 constexpr int kPlainBatch = 8;     // padding of the lists of LDS indices (one 16-byte block)
 constexpr int kOtherBatch = 4;     // padding of the lists of global slots
 constexpr int kStressComps = 12;   // 6 kinetic + 6 virial partial sums per block

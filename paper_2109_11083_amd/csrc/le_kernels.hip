@@ -723,10 +723,12 @@ struct Seg {
 template <int HALO, bool GL>
 __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, const int tile) {
   constexpr int TH = kSearchThreads, NW = TH / 64;
-  static_assert(NW * 16 == kTile && kCells == 2 * TH, "one cluster per wave, two rounds of table entries");
+  constexpr int kCells = TH;  // cells a tile's halo may have (staging table, one per thread)
+  static_assert(NW * 16 == kTile, "one cluster per wave");
   constexpr int kLook = 6, kSeen = kLook * TH;  // positions a thread, a tile looks at
   static_assert(kLook * NW <= 64 && kSeen <= 0xffff, "one lane per (round, wave); 16-bit offsets");
   constexpr int kCut = 1 << 30;
+  constexpr int kFull = 8;  // particles above which a cell that is walked counts as full
   const int T = d.tile;  // (of small tiles the first waves take the clusters)
   constexpr int RS = 13;            // words per lane of the ring: 26 LDS indices, odd stride (banks)
   constexpr int PAD = GL ? 4 : 8;  // list padding (entries per unit of 16 bytes)
@@ -792,8 +794,10 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
     s.tb = g == 0 ? 0 : first;
     if (threadIdx.x < 2) sgs[threadIdx.x] = s;
     if (threadIdx.x == 1) {
-      nseg_sh = ns;
-      nent_sh = ns == 0 ? 0 : min(ns == 1 ? first : first + cells, kCells);
+      // (more cells than the table holds are nearly empty, and better walked)
+      const int all = ns == 0 ? 0 : (ns == 1 ? first : first + cells);
+      nseg_sh = all <= kCells ? ns : 0;
+      nent_sh = all <= kCells ? all : 0;
     }
   }
   __syncthreads();
@@ -821,54 +825,49 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
     }
   }
 
-  // ---- staging table: one cell per thread and round, then the cells' offsets
-  int all;
-  {
-    // (a second round only for the few tiles with more cells than threads)
-    all = 0;
-    for (int r = 0; r == 0 || r * TH < nent; ++r) {
-      const int e = r * TH + (int)threadIdx.x;
-      int st = 0, code = 0, cnt = 0;
-      if (e < nent) {
-        const Seg& s = sgs[nseg == 2 && e >= tb1 ? 1 : 0];
-        const int h2 = s.h + 2, el = e - s.tb;
-        const int row = el / s.nk, kk = el - row * s.nk;
-        const int rz = row / h2, ry = row - rz * h2;
-        int jy = s.y0 - 1 + ry, jz = s.z0 - 1 + rz;
-        const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
-        jy -= sy * d.ny;
-        jz -= sz * d.nz;
-        const int k = s.klo[sy + 1] + kk;
-        if (k <= s.khi[sy + 1]) {
-          const int sx = floor_div(k, d.nx);
-          const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
-          st = d.cell_start[cell];
-          cnt = d.cell_start[cell + 1] - st;
-          code = pack_img(sx, sy, sz);
-        }
+  // ---- staging table: one cell per thread, then the cells' offsets (uniform
+  // branches: a tile that stages nothing goes on to its walk)
+  if (nseg > 0) {
+    const int e = (int)threadIdx.x;
+    int st = 0, code = 0, cnt = 0;
+    if (e < nent) {
+      const Seg& s = sgs[nseg == 2 && e >= tb1 ? 1 : 0];
+      const int h2 = s.h + 2, el = e - s.tb;
+      const int row = el / s.nk, kk = el - row * s.nk;
+      const int rz = row / h2, ry = row - rz * h2;
+      int jy = s.y0 - 1 + ry, jz = s.z0 - 1 + rz;
+      const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
+      jy -= sy * d.ny;
+      jz -= sz * d.nz;
+      const int k = s.klo[sy + 1] + kk;
+      if (k <= s.khi[sy + 1]) {
+        const int sx = floor_div(k, d.nx);
+        const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
+        st = d.cell_start[cell];
+        cnt = d.cell_start[cell + 1] - st;
+        code = pack_img(sx, sy, sz);
       }
-      cent[e] = og_entry((uint32_t)st, (uint8_t)code);
-      int incl = cnt;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-      }
-      if (r > 0) __syncthreads();  // (wsum is read)
-      if (lane == 63) wsum[wv] = incl;
-      if (threadIdx.x == 0 && r == 0) tot_sh = 0;
-      __syncthreads();
-      int off = all + incl - cnt;
-      for (int w2 = 0; w2 < NW; ++w2) {
-        if (w2 < wv) off += wsum[w2];
-        all += wsum[w2];
-      }
-      coff[e] = off;
-      if (off + cnt <= kSeen) {  // the cells looked at are a prefix of the table
-        for (int k = 0; k < cnt; ++k) ring.map[off + k] = (uint16_t)e;
-        if (all > kSeen || (r + 1) * TH < nent) atomicMax(&tot_sh, off + cnt);
-      }
-      if (threadIdx.x == TH - 1) coff[e + 1] = off + cnt;
     }
+    cent[e] = og_entry((uint32_t)st, (uint8_t)code);
+    int incl = cnt;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) wsum[wv] = incl;
+    if (threadIdx.x == 0) tot_sh = 0;
+    __syncthreads();
+    int off = incl - cnt, all = 0;
+    for (int w2 = 0; w2 < NW; ++w2) {
+      if (w2 < wv) off += wsum[w2];
+      all += wsum[w2];
+    }
+    coff[e] = off;
+    if (off + cnt <= kSeen) {  // the cells looked at are a prefix of the table
+      for (int k = 0; k < cnt; ++k) ring.map[off + k] = (uint16_t)e;
+      if (all > kSeen) atomicMax(&tot_sh, off + cnt);
+    }
+    if (threadIdx.x == TH - 1) coff[TH] = off + cnt;
     if (threadIdx.x == 0 && all <= kSeen) tot_sh = all;
     if (threadIdx.x < 2 && (int)threadIdx.x < nseg) {  // the tile's boxes: minimum over the waves
       Box b = wbox[0][threadIdx.x];
@@ -880,10 +879,10 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
     }
   }
   __syncthreads();
-  const int seen = tot_sh;
+  const int seen = nseg > 0 ? tot_sh : 0;
   // ---- stage the positions within reach of the segment's box: LDS position =
   // the number of kept ones before it, in the order of the table
-  {
+  if (nseg > 0) {
     int slot[kLook], code[kLook];
     float x[kLook], y[kLook], z[kLook];
     unsigned long long kept[kLook];
@@ -951,7 +950,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   if (threadIdx.x < 4) hc[threadIdx.x][kPad] = threadIdx.x == 3 ? 1e30f : 0.0f;
   if (GL && threadIdx.x == 0) hent[HALO] = og_entry((uint32_t)n, pack_img(0, 0, 0));
   __syncthreads();
-  const int kept_all = kept_sh;
+  const int kept_all = nseg > 0 ? kept_sh : 0;
   if (threadIdx.x == 0) d.tile_nstage[tile] = min(kept_all, HALO);
   // the particle's own LDS position (its plain image), and the cells' offsets
   // among the kept positions (kCut: beyond what was looked at)
@@ -959,19 +958,15 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   if (valid && nseg > 0) {
     const Seg& s = sgs[gi];
     const int e = s.tb + ((iz - s.z0 + 1) * (s.h + 2) + (iy - s.y0 + 1)) * s.nk + (ix - s.xa + 1);
-    const int h = e < nent ? coff[e] + (i - (int)(cent[e] & kSlotMask)) : seen;
+    const int h = coff[e] + (i - (int)(cent[e] & kSlotMask));
     if (h < seen) self_h = ring.map[h];
   }
-  {
-    const int rounds = nent > TH ? 2 : 1;
-    const int last = coff[rounds * TH];
+  if (nseg > 0) {
     auto kept_before = [&](int o) { return o < seen ? (int)ring.map[o] : (o == seen ? kept_all : kCut); };
-    const int n0 = kept_before(coff[threadIdx.x]), n1 = rounds > 1 ? kept_before(coff[TH + threadIdx.x]) : 0;
-    const int n2 = last == seen ? kept_all : kCut;
+    const int before = kept_before(coff[threadIdx.x]), last = kept_before(coff[TH]);
     __syncthreads();
-    coff[threadIdx.x] = n0;
-    if (rounds > 1) coff[TH + threadIdx.x] = n1;
-    if (threadIdx.x == 0) coff[rounds * TH] = n2;
+    coff[threadIdx.x] = before;
+    if (threadIdx.x == 0) coff[TH] = last;
   }
   __syncthreads();
 
@@ -981,7 +976,6 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   int cnt = 0;   // entries in this lane's ring
   int nblk = 0;  // blocks of eight written for the particle (the same in its four lanes)
   int nog = 0;   // entries of rows that were not staged (the same in the four lanes)
-  uint32_t walked = 0;
   auto og_store = [&](int k, uint32_t e) {
     if ((k >> 2) < units) reinterpret_cast<uint32_t*>(d.nl + unit_back(d, k >> 2, i))[k & 3] = e;
   };
@@ -1012,7 +1006,7 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
   };
   const size_t hbase = (size_t)tile * HALO;
   auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-  for (int g = 0; g < (nseg == 0 ? 1 : nseg); ++g) {
+  for (int g = 0; g < nseg; ++g) {
     const Seg& s = sgs[g];
     const int y0 = uni(s.y0), z0 = uni(s.z0), h2 = uni(s.h) + 2, nk = uni(s.nk), stb = uni(s.tb);
     const bool low = y0 == 0, high = y0 + h2 - 2 == d.ny;  // the beam touches a gradient face
@@ -1023,12 +1017,9 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
     // (sorted along the beam), rows of y and z from their masks
     const int first = __builtin_ctzll(lanes), last = 15 - __builtin_clz((unsigned)(lanes & 0xffffull) << 16);
     const int xlo = __builtin_amdgcn_readlane(ix, first), xhi = __builtin_amdgcn_readlane(ix, last);
-    int ym = 0;
-    if (nseg > 0) {
-      ym = in_seg ? (1 << (iy - y0)) | (1 << (16 + iz - z0)) : 0;
-      for (int o = 8; o > 0; o >>= 1) ym |= __shfl_xor(ym, o, 64);
-      ym = __builtin_amdgcn_readfirstlane(ym);
-    }
+    int ym = in_seg ? (1 << (iy - y0)) | (1 << (16 + iz - z0)) : 0;
+    for (int o = 8; o > 0; o >>= 1) ym |= __shfl_xor(ym, o, 64);
+    ym = __builtin_amdgcn_readfirstlane(ym);
     const int ylo = __builtin_ctz((ym & 0xffff) | 0x10000), yhi = 31 - __builtin_clz((ym & 0xffff) | 1);
     const int zlo = __builtin_ctz(((unsigned)ym >> 16) | 0x10000), zhi = 31 - __builtin_clz(((unsigned)ym >> 16) | 1);
     // cells along x of the cluster's rows, by image sy
@@ -1107,30 +1098,25 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
     };
-    // rows of the box: lane r finds the LDS range of row r (and whether it was
-    // staged)
-    const int ry0 = nseg > 0 ? ylo : 0, nry = nseg > 0 ? yhi - ylo + 3 : 3;
-    const int rz0 = nseg > 0 ? zlo : 0, nrz = nseg > 0 ? zhi - zlo + 3 : 3;
-    const int nrow = nry * nrz;
+    // rows of the box: lane r finds the LDS range of row r, if it was staged
+    const int nry = yhi - ylo + 3, nrow = nry * (zhi - zlo + 3);
     for (int r0 = 0; r0 < nrow; r0 += 64) {
       int row_a = 0, row_b = 0, row_ry = 0, row_rz = 0;
       bool row_staged = false;
       if (r0 + lane < nrow) {
         row_rz = (r0 + lane) / nry;
-        row_ry = ry0 + (r0 + lane) - row_rz * nry;
-        row_rz += rz0;
-        if (nseg > 0) {
-          const int jy0 = y0 - 1 + row_ry;
-          const int syu = jy0 < 0 ? -1 : (jy0 >= d.ny ? 1 : 0);
-          const int rb = stb + (row_rz * h2 + row_ry) * nk;
-          const int lo = s.klo[syu + 1];
-          const int k0 = syu == 0 ? ka[1] : (syu < 0 ? ka[0] : ka[2]);
-          const int k1 = syu == 0 ? kb[1] : (syu < 0 ? kb[0] : kb[2]);
-          row_staged = rb + nk <= nent && coff[min(rb + nk, kCells)] <= HALO;
-          if (row_staged) {
-            row_a = coff[rb + (k0 - lo)];
-            row_b = coff[rb + (k1 - lo) + 1];
-          }
+        row_ry = ylo + (r0 + lane) - row_rz * nry;
+        row_rz += zlo;
+        const int jy0 = y0 - 1 + row_ry;
+        const int syu = jy0 < 0 ? -1 : (jy0 >= d.ny ? 1 : 0);
+        const int rb = stb + (row_rz * h2 + row_ry) * nk;
+        const int lo = s.klo[syu + 1];
+        const int k0 = syu == 0 ? ka[1] : (syu < 0 ? ka[0] : ka[2]);
+        const int k1 = syu == 0 ? kb[1] : (syu < 0 ? kb[0] : kb[2]);
+        row_staged = coff[rb + nk] <= HALO;
+        if (row_staged) {
+          row_a = coff[rb + (k0 - lo)];
+          row_b = coff[rb + (k1 - lo) + 1];
         }
       }
       const bool row_self = row_ry > ylo && row_ry < yhi + 2 && row_rz > zlo && row_rz < zhi + 2;
@@ -1170,43 +1156,75 @@ __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, cons
         if (pass == 0) nself = nc;
       }
       test(nc, nself);
-      unsigned long long walk = __ballot(r0 + lane < nrow && !row_staged);
-      while (walk) {
-        // a row that was not staged: the four lanes of each particle walk the
-        // cells of its own stencil in global memory with the exact test
-        const int r = __builtin_ctzll(walk);
-        walk &= walk - 1ull;
-        const int ry = __builtin_amdgcn_readlane(row_ry, r), rz = __builtin_amdgcn_readlane(row_rz, r);
-        const int dyc = nseg > 0 ? y0 - 1 + ry - iy : ry - 1, dzc = nseg > 0 ? z0 - 1 + rz - iz : rz - 1;
-        bool more = in_seg && dyc >= -1 && dyc <= 1 && dzc >= -1 && dzc <= 1;
-        int jy = iy + dyc, jz = iz + dzc;
-        const int sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
-        jy -= sy * d.ny;
-        jz -= sz * d.nz;
-        int k = 0, khi = -1, slot = 0, end = 0, sx = 0;
-        if (more) x_range(d, ix, ix, sy, Delta, rmarg, k, khi);
-        while (__any(more)) {
-          bool in = false;
-          if (more && slot >= end) {
-            if (k > khi) {
-              more = false;
-            } else {
-              sx = floor_div(k, d.nx);
-              const int cell = cell_slot(d, k - sx * d.nx, jy, jz);
-              slot = d.cell_start[cell] + q;
-              end = d.cell_start[cell + 1];
-              ++k;
-            }
-          } else if (more) {
-            in = !(slot == i && sx == 0 && sy == 0 && sz == 0) &&
-                 in_list_exact(d, pi, P[slot], (double)sx * d.Lx, (double)sy * d.Ly, (double)sz * d.Lz,
-                               (double)sy * Delta);
-            walked = og_entry((uint32_t)slot, pack_img(sx, sy, sz));
-            slot += 4;
+    }
+  }
+  // ---- rows that were not staged (the tile lies in more than two beams, or its halo has
+  // too many cells or positions): the four lanes of a particle walk the rows of its
+  // own stencil in global memory with the exact test, three rows at once, one cell
+  // a lane, or where cells are full all four lanes one cell.  (Row by row of the whole
+  // tile, up to a hundred where cells are nearly empty, the search of 200,000 particles at
+  // density 0.007 took 353 us instead of 94; one cell a lane alone 138 us in a
+  // droplet of 19 per cell instead of 120.)
+  if (nseg == 0 || coff[nent] > HALO) {
+    for (int dzc = -1; dzc <= 1; ++dzc) {
+      int jz = iz + dzc;
+      const int sz = jz < 0 ? -1 : (jz >= d.nz ? 1 : 0);
+      jz -= sz * d.nz;
+      // the three rows of a plane together: their cells' bounds are fetched at once
+      int k[3], khi[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        bool walk = valid;
+        if (nseg > 0) {
+          const Seg& s = sgs[gi];
+          walk = valid && coff[s.tb + ((iz - s.z0 + 1 + dzc) * (s.h + 2) + (iy - s.y0 + r) + 1) * s.nk] > HALO;
+        }
+        const int jy = iy + r - 1;
+        k[r] = 0;
+        khi[r] = -1;
+        if (walk) x_range(d, ix, ix, jy < 0 ? -1 : (jy >= d.ny ? 1 : 0), Delta, rmarg, k[r], khi[r]);
+      }
+      while (__any(k[0] <= khi[0] || k[1] <= khi[1] || k[2] <= khi[2])) {
+        int sx[3], start[3], stop[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          const int jy = iy + r - 1, sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0);
+          sx[r] = start[r] = stop[r] = 0;
+          if (k[r] + q <= khi[r]) {
+            sx[r] = floor_div(k[r] + q, d.nx);
+            const int cell = cell_slot(d, k[r] + q - sx[r] * d.nx, jy - sy * d.ny, jz);
+            start[r] = d.cell_start[cell];
+            stop[r] = d.cell_start[cell + 1];
           }
+          k[r] += 4;
+        }
+        auto try_slot = [&](int r, int slot, int end, int cx, double4 pj) {
+          const int jy = iy + r - 1, sy = jy < 0 ? -1 : (jy >= d.ny ? 1 : 0);
+          const bool in = slot < end && !(slot == i && cx == 0 && sy == 0 && sz == 0) &&
+                          in_list_exact(d, pi, pj, (double)cx * d.Lx, (double)sy * d.Ly, (double)sz * d.Lz,
+                                        (double)sy * Delta);
           const unsigned long long mine = (__ballot(in) >> p16) & 0x0001000100010001ull;
-          if (in) og_store(nog + __popcll(mine & ((1ull << (16 * q)) - 1ull)), walked);
+          if (in) og_store(nog + __popcll(mine & ((1ull << (16 * q)) - 1ull)),
+                           og_entry((uint32_t)slot, pack_img(cx, sy, sz)));
           nog += __popcll(mine);
+        };
+        if (__any(max(stop[0] - start[0], max(stop[1] - start[1], stop[2] - start[2])) > kFull)) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+            for (int c = 0; c < 4; ++c) {
+              const int from = p16 + 16 * c;
+              const int cx = __shfl(sx[r], from, 64), end = __shfl(stop[r], from, 64);
+              for (int slot = __shfl(start[r], from, 64) + q; __any(slot < end); slot += 4)
+                try_slot(r, slot, end, cx, P[slot < end ? slot : s0]);
+            }
+        } else {
+          while (__any(start[0] < stop[0] || start[1] < stop[1] || start[2] < stop[2])) {
+            double4 pj[3];
+#pragma unroll
+            for (int r = 0; r < 3; ++r) pj[r] = P[start[r] < stop[r] ? start[r] : s0];
+#pragma unroll
+            for (int r = 0; r < 3; ++r) try_slot(r, start[r]++, stop[r], sx[r], pj[r]);
+          }
         }
       }
     }

@@ -302,3 +302,51 @@ def test_forces_in_small_units_of_length(name, tune, force_cap):
     (Fa, Wa), (Fb, Wb) = out
     assert np.abs(Fa - Fb).max() <= 1e-12 * np.sqrt((Fa ** 2).sum(axis=0).mean())
     assert np.abs(Wa - Wb).max() <= 1e-12 * np.abs(Wa[:3]).max()
+
+
+def _lattice(density, L):
+    a = density ** (-1.0 / 3.0)
+    g = np.arange(int(L / a)) * a
+    x = np.stack([v.ravel() for v in np.meshgrid(g, g, g, indexing="ij")])
+    return x + np.random.default_rng(3).uniform(0.0, 0.1, x.shape)
+
+
+def _thin(n, L):
+    return np.random.default_rng(3).uniform(0.0, L, (3, n)), dict(n=n, box=(L, L, L))
+
+
+def _part(L, keep):
+    x = _lattice(0.8, L)
+    x = x[:, keep(x / L)]
+    return x, dict(n=x.shape[1], box=(L, L, L), max_neighbors=400)
+
+
+# cells that are nearly empty (tiles in one, two and more beams, with more halo cells than
+# the search's table), and dense parts of mostly empty boxes, at a gradient face and away
+UNEVEN = {"gas_1000_50": lambda: _thin(1000, 50.0), "gas_1000_100": lambda: _thin(1000, 100.0),
+          "gas_5000_90": lambda: _thin(5000, 90.0), "gas_20000_90": lambda: _thin(20000, 90.0),
+          "drop": lambda: _part(50.0, lambda s: ((s - 0.5) ** 2).sum(axis=0) < 0.09),
+          "film": lambda: _part(40.0, lambda s: s[1] < 0.2),
+          "slab": lambda: _part(40.0, lambda s: s[2] < 0.2)}
+
+
+@pytest.mark.parametrize("tune", [1, 2])
+@pytest.mark.parametrize("name", list(UNEVEN))
+def test_list_search_of_gases_and_dense_parts(name, tune):
+    """The pair set is the oracle's, exactly; forces and virial within 1e-12 of the largest."""
+    x, kw = UNEVEN[name]()
+    p = Params(shear_rate=0.2, seed=3, tune=tune, skin=0.3, **kw)
+    sim = Sim(p, x, np.zeros_like(x), step0=1237)
+    out = sim.build_cells()
+    F, W = sim.forces()
+    sim.close()
+    op = _oracle_params(p)
+    Delta = O.offset(1237, p.dt, p.shear_rate, p.box[0], p.box[1])
+    xw, _ = O.le_wrap(x, np.zeros_like(x), Delta, op)
+    ref = O.pairs_cells(xw, Delta, p.box, p.rlist)
+    got = np.sort(out["pairs"][:, 0] * p.n + out["pairs"][:, 1])
+    lo, hi = ref.min(axis=1).astype(np.int64), ref.max(axis=1).astype(np.int64)
+    assert np.array_equal(got, np.sort(lo * p.n + hi))
+    Fr, Wr, _ = O.forces(xw, Delta, op)
+    assert np.abs(F - Fr).max() <= 1e-12 * np.abs(Fr).max()
+    assert np.abs(W - Wr).max() <= 1e-12 * np.abs(Wr).max()
