@@ -211,8 +211,8 @@ size_t carve(const le_params* p, const Geometry& g, char* base, Dev* d, le_sim* 
   t.ctrl = (Ctrl*)take(2 * sizeof(Ctrl));
   t.flags = (Flags*)take(sizeof(Flags));
   t.vmax = (unsigned long long*)take(2 * kSlots * kLineU64 * sizeof(unsigned long long));
-  t.scan_status = (unsigned long long*)take((size_t)(g.sp_blocks + kLineU64) * sizeof(unsigned long long));
-  t.joined = t.scan_status + (g.sp_blocks + kLineU64 - kJoined);  // (behind the words of the scan)
+  t.scan_status = (unsigned long long*)take((size_t)(g.sp_blocks + (kJoined + 1) * kJoinedLine) * sizeof(unsigned long long));
+  t.joined = t.scan_status + g.sp_blocks + kJoinedLine;  // (behind the words of the scan)
   for (int b = 0; b < 2; ++b) {
     t.pos[b] = (double*)take(4 * np * sizeof(double));
     t.vel[b] = (double*)take(3 * np * sizeof(double));

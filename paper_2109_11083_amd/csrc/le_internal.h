@@ -62,6 +62,7 @@ enum { kRebuildDue = 1, kRebuildForced = 2 };
 // Counts of kernels in one launch: places given out, blocks done of the binning and of
 // the scan-and-permute pass, and blocks of the search that have waited.
 enum { kPlace = 0, kBinned = 1, kSorted = 2, kWaited = 3, kJoined = 4 };
+constexpr int kJoinedLine = 32;    // 64-bit words between the counts (blocks that wait poll one of them)
 
 // Sticky status and telemetry shared by both control copies.
 struct alignas(64) Flags {
