@@ -35,8 +35,9 @@ constexpr int kSlots = 64;         // words (one per 128-byte line) a block maxi
 constexpr int kLineInts = 32;      // 32-bit words per 128-byte line
 constexpr int kLineU64 = 16;       // 64-bit words per 128-byte line
 constexpr int kSortParticles = 512;  // particles per block of the scan-and-permute pass (on average)
-// particles up to which a step rebuilds in one launch, and sorts in one
-constexpr int kOneLaunch = 20000, kSortOneLaunch = 65536;
+// particles up to which a step rebuilds in one launch, and sorts in one, and the blocks
+// such a launch may have (see launch_rebuild)
+constexpr int kOneLaunch = 20000, kSortOneLaunch = 65536, kWaitBlocks = 512;
 constexpr int kBinBlock = 2 * kBlock;  // particles per block of the binning pass (two per thread)
 
 // Mutable per-simulation scalars that live on the device so that a step

@@ -584,8 +584,8 @@ __device__ __forceinline__ bool wait_count(const Dev& d, unsigned long long* cou
 }
 
 // (1) and (2) in one launch.  A step that rebuilds nothing pays one empty
-// launch less (2.5 us); one that does pays the hand-over, a write-back and a
-// refill of the L2s, which grows with the system.
+// launch less; one that does pays the hand-over, a write-back and a
+// refill of the L2s, which grows with the system (see launch_rebuild).
 __global__ void __launch_bounds__(kBlock) k_sort(Dev d, Ctrl* __restrict__ next,
                                                  unsigned long long* __restrict__ next_vmax, int control) {
   __shared__ Ctrl sc, sn;
@@ -2492,15 +2492,25 @@ hipError_t launch_rebuild(const Dev& d, Ctrl* next, unsigned long long* next_vma
   Dev dn = d;
   dn.ctrl = next;
   dn.vmax = next_vmax;
-  const unsigned nbb = (d.n + kBinBlock - 1) / kBinBlock;
-  // Launches within a step, measured per step: one up to kOneLaunch particles (1000:
-  // 15.8 us, with two 18.5, with three 21.0; 17,389 in a graph 19.9, 20.2 and 21.4),
-  // two up to kSortOneLaunch (64,000 LJ particles 31.0, with one 37.1, with three
-  // 32.2; 50,000 beads 23.4, 24.9 and 25.6), three above (256,000 62.2, with two 66.1;
-  // 400,000 beads 64.6 and 79.3).  A forced rebuild has work for all (27,000
+  const int nbb = (d.n + kBinBlock - 1) / kBinBlock;
+  // Launches within a step: one up to kOneLaunch particles, two up to kSortOneLaunch,
+  // three above.  Fewer save 2.2 us each in a step that rebuilds nothing and cost the
+  // hand-over in one that does, so the lines move with the life of the lists.  In us a
+  // step (one, two, three launches), lists that live for 10 to 14 steps: 17,389 LJ particles 17.0,
+  // 19.7, 22.6; 24,000 17.7, 19.3, 22.6; 40,000 22.8, 23.3, 25.6; 64,000 27.2, 24.0, 26.5; 80,000
+  // 31.9, 29.9, 30.4; 100,000 38.6, 35.0, 34.7; beads 30,000 15.2, 17.2, 20.4; 50,000 19.5, 18.8, 21.1;
+  // 130,000 29.5, 24.1, 24.6; 200,000 40.1, 34.5, 31.9.  Lists that live for 4: 30,000 24.5, 23.3, 25.9;
+  // 64,000 39.2, 30.1, 30.2; 80,000 45.6, 38.9, 37.0.  A forced rebuild has work for all (27,000
   // particles: 74 us with three, 78 with two), and so has a batch, where some member
   // rebuilds on most steps (64 of them: 563 and 600 us).
-  if (!force && d.n <= kOneLaunch) {
+  // Nearly empty cells make many blocks of the scan, which the search's blocks
+  // dwarf and every step launches, so the blocks are limited too: a gas of 1000 with
+  // 333 blocks takes 11.9, 14.4 and 17.6 us, with 616 14.0, 15.3 and 17.9 (and 14.2 and, with
+  // three, 13.3 where an empty launch costs 1.3 us), with 4,819 38.3, 25.6 and 19.9;
+  // 10,000 with 681 17.1, 16.9 and 18.7; 60,000 with 700 blocks of the sort 21.5 with two
+  // and with three.
+  const bool few_sort = nbb + d.sp_blocks <= kWaitBlocks, few = nbb + d.sp_blocks + d.ntiles <= kWaitBlocks;
+  if (!force && d.n <= kOneLaunch && few) {
     with_search_tiles(d, [&](auto t, auto gl) {
       using TC = decltype(t);
       hipLaunchKernelGGL((k_rebuild<TC, decltype(gl)::value>), dim3(nbb + d.sp_blocks + d.ntiles),
@@ -2508,7 +2518,7 @@ hipError_t launch_rebuild(const Dev& d, Ctrl* next, unsigned long long* next_vma
     });
     return hipGetLastError();
   }
-  if (!force && d.n <= kSortOneLaunch) {
+  if (!force && d.n <= kSortOneLaunch && few_sort) {
     hipLaunchKernelGGL(k_sort, dim3(nbb + d.sp_blocks), dim3(kBlock), 0, s, d, next, next_vmax, control ? 1 : 0);
   } else {
     hipLaunchKernelGGL(k_control_bin, dim3(nbb), dim3(kBlock), 0, s, d, next, next_vmax, force ? 1 : 0,

@@ -350,3 +350,41 @@ def test_list_search_of_gases_and_dense_parts(name, tune):
     Fr, Wr, _ = O.forces(xw, Delta, op)
     assert np.abs(F - Fr).max() <= 1e-12 * np.abs(Fr).max()
     assert np.abs(W - Wr).max() <= 1e-12 * np.abs(Wr).max()
+
+
+# Steps alone (the rebuild in one launch up to 20,000 particles, the sort in one up to
+# 65,536, separate launches above and where nearly empty cells make more than 512
+# blocks) against a batch's separate launches, bit for bit: both lines, a ragged size
+# between, a gas on either side of the limit of blocks, and every kind of tile.
+STEPS = {"lj_20000": (_fluid(20000), {}), "lj_20001": (_fluid(20001), {}), "lj_33333": (_fluid(33333), {}),
+         "gas_1000_130": (lambda seed: _thin(1000, 130.0), {}), "gas_1000_150": (lambda seed: _thin(1000, 150.0), {}),
+         "gas_30000_130": (lambda seed: _thin(30000, 130.0), {}), "gas_30000_170": (lambda seed: _thin(30000, 170.0), {}),
+         "lj_1009_global": (_fluid(1009), dict(tune=2)), "lj_16500_global": (_fluid(16500), dict(tune=2)),
+         "lj_1009_dpd": (_fluid(1009), dict(thermostat="dpd", gamma=5.0)),
+         "kg_2010": (_melt(30, 67, 0.6), {}), "kg_12000_wide": (_melt(60, 200, 1.2), dict(skin=0.4)),
+         "kg_12000_global": (_melt(60, 200, 0.6), dict(tune=2))}
+
+
+@pytest.mark.parametrize("name", list(STEPS))
+def test_steps_alone_and_in_a_batch(name):
+    make, over = STEPS[name]
+    x, kw = make(3)
+    if name.startswith("gas"):  # no overlaps: a jittered lattice
+        m = int(np.ceil(kw["n"] ** (1.0 / 3.0)))
+        g = np.arange(m) * (kw["box"][0] / m)
+        x = np.stack([v.ravel() for v in np.meshgrid(g, g, g, indexing="ij")])[:, :kw["n"]]
+        x = x + np.random.default_rng(4).uniform(0.0, 0.4 * kw["box"][0] / m, x.shape)
+    u = np.random.default_rng(8).normal(size=x.shape)
+    p = Params(shear_rate=0.3, seed=7, dt=0.004, **{"rc": 2.5, "skin": 0.3, **kw, **over})
+    a, b = Sim(p, x, u), Sim(p, x, u)
+    for k in range(3):
+        a.step(8)
+        if k < 2:
+            step_batch([b], 8)
+        else:
+            b.step(8)
+    (xa, ua, fa, _), (xb, ub, fb, _) = a.state(), b.state()
+    assert a.stats() == b.stats() and a.stats()["rebuilds"] > 2
+    assert np.array_equal(xa, xb) and np.array_equal(ua, ub) and np.array_equal(fa, fb)
+    a.close()
+    b.close()
