@@ -388,3 +388,20 @@ def test_steps_alone_and_in_a_batch(name):
     assert np.array_equal(xa, xb) and np.array_equal(ua, ub) and np.array_equal(fa, fb)
     a.close()
     b.close()
+
+
+# the reported order over several blocks of cells (one block of 1024 cells, one cell
+# more than that, and 215,940), cells of unequal edges
+@pytest.mark.parametrize("cells", [(16, 8, 8), (41, 5, 5), (59, 61, 60)])
+def test_cell_order_over_many_cells(cells):
+    box = tuple(3.0 * c for c in cells)
+    x = np.random.default_rng(6).uniform(0.0, 1.0, (3, 5000)) * np.array(box)[:, None]
+    p = Params(n=5000, box=box, shear_rate=0.2, rc=2.5, skin=0.3, cells=cells)
+    sim = Sim(p, x, np.zeros_like(x), step0=1237)
+    out = sim.build_cells(want_pairs=False)
+    again = sim.build_cells(want_pairs=False)
+    sim.close()
+    xw, _ = O.le_wrap(x, np.zeros_like(x), O.offset(1237, p.dt, p.shear_rate, box[0], box[1]), _oracle_params(p))
+    ref_cells, ref_order = O.cells(xw, cells, box)
+    for o in (out, again):
+        assert np.array_equal(o["cell_of"], ref_cells) and np.array_equal(o["order"], ref_order)
