@@ -2175,7 +2175,8 @@ __global__ void k_ctrl_copy(const Ctrl* __restrict__ src, Ctrl* __restrict__ dst
 // matching lab u_x) to its own row of LDS sums, the waves of a block are added
 // in wave order and the blocks in a fixed tree, so the sums are reproducible.
 // Cell-sorted particles of one wave fall into a few bins, so a wave takes one
-// bin at a time: all lanes of that bin by one butterfly.  At most kObsBlocks
+// bin at a time: all lanes of that bin by one butterfly, and, past a few, one particle
+// at a time (1000 particles and 256 bins 30 us by butterflies alone).  At most kObsBlocks
 // blocks (two a CU; a block takes several rounds of kBlock particles), and a
 // final pass over many blocks: with one thread per bin over the particles of
 // a block and one block over all partial rows, 256,000 particles and 50 bins took
@@ -2184,6 +2185,9 @@ constexpr int kObsStride = 3 * LE_MAX_BINS + 4;
 constexpr int kObsBlocks = 512;
 constexpr int kObsCols = 16;  // columns per block of the final pass
 constexpr int kObsRows = kBlock / kObsCols;
+constexpr int kObsBins = 8;    // bins that a wave takes by butterflies
+constexpr int kObsLane = LE_MAX_BINS / 64;  // bins a lane keeps after those
+static_assert(LE_MAX_BINS % 64 == 0, "whole bins per lane");
 
 static inline int obs_blocks(int n) {
   const int nb = (n + kBlock - 1) / kBlock;
@@ -2193,6 +2197,11 @@ static inline int obs_blocks(int n) {
 __device__ __forceinline__ double wave_sum(double v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
+}
+
+__device__ __forceinline__ double read_lane(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
 __global__ void __launch_bounds__(kBlock) k_obs_partial(Dev d, int nbins, int nblk) {
@@ -2227,7 +2236,7 @@ __global__ void __launch_bounds__(kBlock) k_obs_partial(Dev d, int nbins, int nb
       v[1] += ux; v[2] += u1; v[3] += u2;
     }
     unsigned long long rem = __ballot(b >= 0);
-    while (rem) {
+    for (int k = 0; k < kObsBins && rem; ++k) {
       const int bb = __builtin_amdgcn_readlane(b, __builtin_ctzll(rem));
       const bool mine = b == bb;
       const unsigned long long m = __ballot(mine);
@@ -2238,6 +2247,22 @@ __global__ void __launch_bounds__(kBlock) k_obs_partial(Dev d, int nbins, int nb
         acc[wid][nbins + bb] += su;
         acc[wid][2 * nbins + bb] += sk;
       }
+    }
+    if (rem) {  // many bins: a lane keeps every 64th, and the particles left go by one at a time
+      double s[kObsLane][3] = {};
+      while (rem) {
+        const int l = __builtin_ctzll(rem);
+        rem &= rem - 1ull;
+        const int bb = __builtin_amdgcn_readlane(b, l);
+        const double xl = read_lane(ux, l), kl = read_lane(mc2, l);
+#pragma unroll
+        for (int q = 0; q < kObsLane; ++q)
+          if (bb == lane + 64 * q) { s[q][0] += 1.0; s[q][1] += xl; s[q][2] += kl; }
+      }
+#pragma unroll
+      for (int q = 0; q < kObsLane; ++q)
+        if (lane + 64 * q < nbins)
+          for (int a = 0; a < 3; ++a) acc[wid][a * nbins + lane + 64 * q] += s[q][a];
     }
   }
 #pragma unroll

@@ -405,3 +405,9 @@ def test_cell_order_over_many_cells(cells):
     ref_cells, ref_order = O.cells(xw, cells, box)
     for o in (out, again):
         assert np.array_equal(o["cell_of"], ref_cells) and np.array_equal(o["order"], ref_order)
+
+
+# as many bins in a wave as it has lanes, one bin, and just what it takes one by one
+@pytest.mark.parametrize("nbins", [1, 9, 256])
+def test_observables_with_few_particles_per_bin(nbins):
+    test_observables_rounds(1000, nbins)
