@@ -2017,8 +2017,13 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
 }
 
 // Waves per SIMD that the halo kernels are compiled for: six in 80 registers
-// (plain steps), four in 128 (DPD); beads in a batch, whose descriptor takes registers
-// too, five (six spill: 16 melts 74 instead of 71 us a step).
+// (plain steps), four in 128 (DPD); beads of sparse tiles in a batch, whose descriptor takes
+// registers too, five (six spill: 16 melts 74 instead of 71 us a step).  Beads of dense
+// tiles in a batch stay at six and spill 52 bytes: their blocks of eight waves fit a CU three
+// times at six and twice at five or four (8 x 20,000 beads with a cutoff of 2.5: 70.6 us a step, 75.3
+// at four); so do sampled DPD steps, 20 to 64 bytes, at four (8 x 20,000 particles 118 us, at
+// three 135).  Without the halo the compiler chooses (DPD of 256,000 from
+// global memory: 145 us a step; held to three waves it spills, 148).
 constexpr int force_waves(int mode, int halo, bool sample, bool batch_bonds = false) {
   if (halo == 0) return 1;
   if (mode == kDpdForce) return 4;
@@ -2039,15 +2044,6 @@ __global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, forc
 // region); LDS halo: runs of 16 tiles dealt round-robin to the XCDs, which
 // evens out members of unequal cost per tile (64-request batch 0.711 ->
 // 0.699 ms per step; the KG melts of the global layout gain nothing from it).
-// Plain DPD steps of the global layout (no stress sample): held to 168 VGPRs, three
-// waves per SIMD instead of two, which the kernel reaches without spills (the
-// sampling variant would spill, so it keeps the plain bound).
-template <bool MIXED, bool BONDS>
-__global__ void __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(3)))
-    k_force_dpd(Dev d, double* __restrict__ f_out, double* __restrict__ sample_out) {
-  (void)sample_out;
-  force_body<kDpdForce, MIXED, BONDS, false, TileNone, false>(d, xcd_block(d.nblocks), f_out);
-}
 template <int MODE, bool MIXED, bool BONDS, bool SAMPLE, class TC, bool CAP = false>
 __global__ void __launch_bounds__(TC::HALO ? TC::kForceThreads : 4 * kTile, force_waves(MODE, TC::HALO, SAMPLE, BONDS)) k_force_b(Batch b) {
   int sm, lb;
@@ -2606,15 +2602,7 @@ static void launch_force_s(const Dev& d, hipStream_t s, double* f_out, double* s
       return;
     }
   }
-  if constexpr (MODE == kDpdForce && !SAMPLE && !STAGED) {
-    if (mixed) {
-      if (bonds) launch_k(k_force_dpd<true, true>, g, b, s, e0, e1, d, f_out, so);
-      else launch_k(k_force_dpd<true, false>, g, b, s, e0, e1, d, f_out, so);
-    } else {
-      if (bonds) launch_k(k_force_dpd<false, true>, g, b, s, e0, e1, d, f_out, so);
-      else launch_k(k_force_dpd<false, false>, g, b, s, e0, e1, d, f_out, so);
-    }
-  } else if (mixed) {
+  if (mixed) {
     if (bonds) launch_k(k_force<MODE, true, true, SAMPLE, TC>, g, b, s, e0, e1, d, f_out, so);
     else launch_k(k_force<MODE, true, false, SAMPLE, TC>, g, b, s, e0, e1, d, f_out, so);
   } else {

@@ -45,3 +45,15 @@ def test_blocks_count_themselves_done_after_every_waves_stores(code_object):
             barrier = max(j for j in range(k) if ins[j].startswith("s_barrier"))
             before = ins[max(barrier - 3, 0):barrier]
             assert any(re.match(r"s_waitcnt .*vmcnt\(0\)", i) for i in before), (before, ins[barrier:k + 1])
+
+
+def test_search_and_plain_steps_keep_their_registers(code_object):
+    """No scratch in the list search, in any launch form, nor in the force kernel of a
+    plain step of one simulation."""
+    f, _ = code_object
+    notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", f], check=True, capture_output=True, text=True).stdout
+    found = dict(re.findall(r"\.name:\s+(\S+).*?\.private_segment_fixed_size: (\d+)", notes, re.S))
+    # (k_force<kStepFused = 1 or kDpdForce = 4, ., ., no sample, ...>)
+    kernels = [n for n in found if re.search(r"k_neighbors|k_rebuild|k_sort|k_forceILi[14]ELb[01]ELb[01]ELb0E", n)]
+    assert len(kernels) >= 12
+    assert [n for n in kernels if int(found[n])] == []
