@@ -90,7 +90,8 @@ typedef int32_t le_status;
                                 j's image (s_y gamma_dot L_y e_x), w = 1 - r / dpd_rc:
                                 F_i += [-gamma w^2 (e . v_ij) + sqrt(24 gamma kT / dt) w theta_ij] e,
                                 F_j -= the same; theta_ij shared by the pair.  Conserves momentum.
-                                Requires the global-memory pair layout (tune 0 or 2).           */
+                                tune 0 or 2 (with 0 dense systems take partners' positions from
+                                the LDS halo, velocities from global memory); not tune 1.       */
 #define LE_THERMO_LANGEVIN_LAB 2 /* Eq. langevin with the friction on the lab velocity u (the
                                 paper's xi_abs, Section 3.1): F_i += -gamma m u_i + noise       */
 

@@ -193,10 +193,10 @@ __global__ void k_load_state(Dev d, const double* __restrict__ x0, const double*
 }
 
 // ------------------------------------------------------------- rebuild
-// Three kernels, each an empty launch unless the lists are rebuilt for the
-// current state: (1) advance the step and decide, then crossing + wrap + bin,
-// (2) cell-count scan and, block by block, rank by tag + permute, (3)
-// neighbour lists.
+// Three parts: (1) advance the step and decide, then bin by the cell of the crossed and
+// wrapped position, (2) cell-count scan and, block by block, rank by tag, cross, wrap and
+// permute, (3) neighbour lists.  They are three launches, two or one (launch_rebuild),
+// each an empty one unless the lists are rebuilt for the current state.
 
 // Advance the step counter and the offset, adopt the drifted positions, and
 // decide whether the neighbour lists must be rebuilt before the next force
@@ -1308,7 +1308,7 @@ __global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_pe
 // (1) to (3) in one launch.  The blocks of the search wait for all of the scan;
 // the last of them to have waited sets the counts back to zero.
 template <class TC, bool GL>
-__global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(GL && TC::HALO > 1024 ? 2 : 4)))
+__global__ void __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4)))
     k_rebuild(Dev d, Ctrl* __restrict__ next, unsigned long long* __restrict__ next_vmax, int control) {
   __shared__ Ctrl sc, sn;
   if (!sort_control(d, next, next_vmax, 0, control, blockIdx.x, sc, sn)) return;
@@ -1783,8 +1783,8 @@ __device__ __forceinline__ void force_body(const Dev& d, const int lb, double* _
     };
     const uint4* __restrict__ l4 = d.nl;
     // GB blocks of 4 per round: one for the plain global layout (fewer
-    // gathers in flight leave room for more waves: KG 49 -> 48 us), two with
-    // the halo's remainder pieces and with DPD (one block: 138 -> 195 us)
+    // gathers in flight leave room for more waves: KG 49 -> 48 us) and for the rows that the
+    // halo did not hold, two for DPD from global memory (one block: 138 -> 195 us)
     constexpr int GB = DPD && !STAGED ? 2 : 1;
     uint4 jn[GB];
 #pragma unroll
