@@ -715,12 +715,12 @@ struct Seg {
 // inside it the plain FP64 displacement, so the list is exactly
 // {r^2 < r_list^2}.
 //
-// Bound by the vector unit (LJ, 256,000 particles, r_list 3.05: 3200 vector
-// instructions per cluster, 125 us) and, in small systems, by the chain of
+// Bound by the vector unit (LJ, 256,000 particles, r_list 3.05: 2850 vector
+// instructions per cluster, 130 us, 62% busy) and, in small systems, by the chain of
 // phases: against one lane per particle half with the tests on the vector unit, 1000
-// particles take 25 instead of 111 us, 27,000 take 27 instead of 87, 256,000 as long
-// as before and 400,000 beads of a melt 121 instead of 112; the compact halo that it
-// leaves to the force kernel is what the large systems gain from.
+// particles take 25 instead of 111 us, 27,000 take 26 instead of 87, 256,000 as long
+// as before and 400,000 beads of a melt 119 instead of 112 (65% busy); the compact halo
+// that it leaves to the force kernel is what the large systems gain from.
 template <int HALO, bool GL>
 __device__ __forceinline__ void neighbors_body(const Dev& d, const Ctrl* c, const int tile) {
   constexpr int TH = kSearchThreads, NW = TH / 64;
@@ -1591,7 +1591,7 @@ __device__ __forceinline__ void block_partials(double* vals, double* out, int lb
 // melt), lists in blocks of 4 and 22 vector instructions per entry took the
 // plain step from 43 to 36.5 us for 256,000 LJ particles and, against gathers from
 // global memory, from 37 to 26.7 us for 400,000 beads (traced); it is bound by the vector unit's
-// issue (75% busy) and the waves' imbalance, six waves per SIMD in 80 registers.
+// issue (77% busy) and the waves' imbalance, six waves per SIMD in 80 registers.
 // DPD steps with the halo gather the velocities (from vt, with the slots kept
 // in LDS beside the positions) of the partners within the DPD cutoff alone: all
 // from memory, four gathers per entry, the kernel waited for them (256,000 LJ
