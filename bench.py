@@ -248,7 +248,7 @@ def roofline_of(r, kind, precision, skin, dpd=False):
         roof = dict(bound="alu", achieved=round(achieved, 4), peak=PEAK_FP64_TFLOPS, unit="TFLOP/s",
                     frac=round(achieved / PEAK_FP64_TFLOPS, 5), traffic=traffic,
                     flops_per_particle=round(flops_pp, 1),
-                    kernel=("k_force_dpd (LJ + DPD pair terms; the kicks and drift follow in "
+                    kernel=("k_force (LJ + DPD pair terms; the kicks and drift follow in "
                             "k_integrate), plain steps") if dpd else
                     "k_force (fused LJ force, Langevin, velocity Verlet), plain steps")
     roof.update(avg_kernel_us=round(avg_s * 1e6, 3), launches=force_n,
